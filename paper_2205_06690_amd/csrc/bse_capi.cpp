@@ -18,6 +18,7 @@
 #include "bse_kernels.h"
 #include "prop_kernels.h"
 #include "clean_mfma.h"
+#include "clean_f64.h"
 #include "contract_mfma.h"
 #include "host_math.h"
 
@@ -184,7 +185,6 @@ struct bse_system {
   DBuf d, u, dens, wpol, q, rho64, work, work64, part, part32, gpart, coef, coefE, E, pq_d, flags;
   DBuf pscale;    // [B][3] row sums of q, then [B] per-pair scales of the packed Poisson solves
   DBuf normpart;  // partial norms of the unperturbed set (check at the cleaning steps)
-  int nchunk = 0;
   // A / spectrum state
   int a_no = 0, a_nc = 0;
   DBuf wij;       // [n_ij][ng] FP64 W_ij of the valence pairs
@@ -287,12 +287,11 @@ void ensure_batch(bse_system* s, int B) {
   s->rho64.alloc(sizeof(double) * ng * B);
   s->work.alloc(sizeof(C) * ng * (size_t)((B + 1) / 2));
   s->E.alloc(sizeof(C) * ng * L);
-  const int chunk = 4096;
-  s->nchunk = (int)((ng + chunk - 1) / chunk);
   const int F = B * L;
-  s->part.alloc(sizeof(cplx<double>) * (size_t)s->nchunk * std::max(F, L) * (S + 1));
-  s->coef.alloc(sizeof(cplx<double>) * (size_t)F * (S + 1));
-  if (sizeof(T) == 4) {
+  s->coef.alloc(sizeof(cplx<double>) * (size_t)(F + L) * (S + 1));
+  if (sizeof(T) == 8) {
+    s->part.alloc(sizeof(cplx<double>) * coef64_part_entries(F, L, S, ng));
+  } else {
     s->part32.alloc(sizeof(float) * clean_scratch_floats(F, L, S, ng));
     s->gpart.alloc(sizeof(cplx<double>) * edot_part_entries(F, L, S, ng));
   }
@@ -326,7 +325,6 @@ void clean(bse_system* s, int B, int from_mid, const cplx<T>* H) {
   c.ng = s->ng;
   c.dt = (T)s->cfg.dt;
   c.from_mid = from_mid;
-  c.chunk = 4096;
   c.part = s->part.as<cplx<double>>();
   c.coef = s->coef.as<cplx<double>>();
   c.coefE = s->coefE.as<cplx<double>>();

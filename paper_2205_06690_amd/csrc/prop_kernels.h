@@ -67,10 +67,9 @@ template <typename T> struct CleanArgs {
   size_t ng;
   T dt;
   int from_mid;
-  int chunk;
-  cplx<double>* part;  // [nchunk][F][S+1]
-  cplx<double>* coef;  // [F][S+1]
-  cplx<double>* coefE; // [L][S+1]
+  cplx<double>* part;  // FP64 mode: partial coefficients (coef64_part_entries)
+  cplx<double>* coef;  // [F][S+1]; FP64 mode [F + L][S+1], the unperturbed set's rows last
+  cplx<double>* coefE; // [L][S+1] (mixed precision)
   const double* n0;    // [L]
   int renorm;
   double dv;

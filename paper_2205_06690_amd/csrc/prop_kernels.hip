@@ -14,6 +14,7 @@
 #include "fft_lines.h"
 #include "prop_kernels.h"
 #include "clean_mfma.h"
+#include "clean_f64.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -1182,34 +1183,6 @@ __global__ void k_kick(const double* __restrict__ q, const double* __restrict__ 
   d[(size_t)f * ng + i] = cmk<C>((T)0, (T)(-v));
 }
 
-// end-of-step state from the mid-step one: d <- Ph (d - i dt/2 u_b H_l) and
-// E_l = Ph H_l (from_mid = 1); E_l = Ph H_l only (0); at t = 0 E_l is the
-// real eta_l(0) itself (2).
-template <typename T>
-__global__ void k_clean_finish(cplx<T>* __restrict__ d, const T* __restrict__ u,
-                               const cplx<T>* __restrict__ H, const cplx<T>* __restrict__ ph,
-                               const double* __restrict__ eta0, cplx<T>* __restrict__ E, int L,
-                               size_t ng, T dt, int from_mid) {
-  using C = cplx<T>;
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int f = blockIdx.y;
-  if (i >= ng) return;
-  const int b = f / L, l = f % L;
-  if (from_mid == 2) {
-    if (f < L) E[(size_t)l * ng + i] = cmk<C>((T)eta0[(size_t)l * ng + i], (T)0);
-    return;
-  }
-  const C p = ph[i];
-  const C h = H[(size_t)l * ng + i];
-  if (f < L) E[(size_t)l * ng + i] = cmul(p, h);
-  if (from_mid == 1) {
-    C v = d[(size_t)f * ng + i];
-    const T cu = (T)0.5 * dt * u[(size_t)b * ng + i];
-    v = cmk<C>(v.x + cu * h.y, v.y - cu * h.x);
-    d[(size_t)f * ng + i] = cmul(p, v);
-  }
-}
-
 // dn_b = 4 sum_l Re(conj(E_l) d_{b,l})
 template <typename T>
 __global__ void k_density_end(const cplx<T>* __restrict__ d, const cplx<T>* __restrict__ E,
@@ -1230,102 +1203,6 @@ __global__ void k_density_end(const cplx<T>* __restrict__ d, const cplx<T>* __re
 // ---------------------------------------------------------------------------
 // cleaning (Eq. 15, linearised): d <- Q d - Re<E_l, Q d>/||eta_l(0)||^2 E_l
 // ---------------------------------------------------------------------------
-// partial coefficients over a chunk of grid points:
-//   part[chunk][f][s] = sum_{r in chunk} phi_s(r) d_f(r)   (s < S)
-//   part[chunk][f][S] = sum_{r in chunk} conj(E_l(f)) d_f(r)
-// tile: 32 fields x 32 states per block, 256 threads, 2x2 per thread.
-constexpr int CT_F = 32, CT_S = 32, CT_R = 32;
-template <typename T>
-__global__ void __launch_bounds__(256) k_clean_coef(const cplx<T>* __restrict__ d, int F,
-                                                    const T* __restrict__ phi, int S,
-                                                    const cplx<T>* __restrict__ E, int L,
-                                                    size_t ng, int chunk,
-                                                    cplx<double>* __restrict__ part) {
-  using C = cplx<T>;
-  __shared__ C sd[CT_F][CT_R + 1];
-  __shared__ T sp[CT_S][CT_R + 1];
-  const int f0 = blockIdx.x * CT_F;
-  const int s0 = blockIdx.y * CT_S;  // s == S row block also carries the E dot
-  const int kc = blockIdx.z;
-  const size_t r0 = (size_t)kc * chunk;
-  const size_t r1 = min(ng, r0 + (size_t)chunk);
-  const int tid = threadIdx.x;
-  const int tf = tid / 16, ts = tid % 16;
-  C acc[2][2];
-  C acce[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    acce[i] = cmk<C>(0, 0);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = cmk<C>(0, 0);
-  }
-  const bool do_e = (s0 == 0);
-  for (size_t rb = r0; rb < r1; rb += CT_R) {
-    for (int e = tid; e < CT_F * CT_R; e += 256) {
-      const int ff = e / CT_R, rr = e % CT_R;
-      const int f = f0 + ff;
-      const size_t r = rb + rr;
-      sd[ff][rr] = (f < F && r < r1) ? d[(size_t)f * ng + r] : cmk<C>(0, 0);
-    }
-    for (int e = tid; e < CT_S * CT_R; e += 256) {
-      const int ss = e / CT_R, rr = e % CT_R;
-      const int s = s0 + ss;
-      const size_t r = rb + rr;
-      sp[ss][rr] = (s < S && r < r1) ? phi[(size_t)s * ng + r] : (T)0;
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (int rr = 0; rr < CT_R; ++rr) {
-      const C d0 = sd[tf * 2][rr], d1 = sd[tf * 2 + 1][rr];
-      const T p0 = sp[ts * 2][rr], p1 = sp[ts * 2 + 1][rr];
-      acc[0][0] = cmk<C>(acc[0][0].x + d0.x * p0, acc[0][0].y + d0.y * p0);
-      acc[0][1] = cmk<C>(acc[0][1].x + d0.x * p1, acc[0][1].y + d0.y * p1);
-      acc[1][0] = cmk<C>(acc[1][0].x + d1.x * p0, acc[1][0].y + d1.y * p0);
-      acc[1][1] = cmk<C>(acc[1][1].x + d1.x * p1, acc[1][1].y + d1.y * p1);
-    }
-    if (do_e && ts == 0) {
-      for (int i = 0; i < 2; ++i) {
-        const int f = f0 + tf * 2 + i;
-        if (f >= F) continue;
-        const int l = f % L;
-        for (int rr = 0; rr < CT_R; ++rr) {
-          const size_t r = rb + rr;
-          if (r >= r1) break;
-          const C ee = E[(size_t)l * ng + r];
-          acce[i] = cadd(acce[i], cmulc(sd[tf * 2 + i][rr], ee));
-        }
-      }
-    }
-    __syncthreads();
-  }
-  cplx<double>* out = part + (size_t)kc * F * (S + 1);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int f = f0 + tf * 2 + i;
-    if (f >= F) continue;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int s = s0 + ts * 2 + j;
-      if (s < S) out[(size_t)f * (S + 1) + s] = cmk<cplx<double>>(acc[i][j].x, acc[i][j].y);
-    }
-    if (do_e && ts == 0) out[(size_t)f * (S + 1) + S] = cmk<cplx<double>>(acce[i].x, acce[i].y);
-  }
-}
-
-// reduce partials over chunks; coef[f][s] = h^3 sum (s < S); coef[f][S] = h^3 <E,d>
-__global__ void k_clean_reduce(const cplx<double>* __restrict__ part, int nchunk, int FS,
-                               double dv, cplx<double>* __restrict__ coef) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= FS) return;
-  double x = 0, y = 0;
-  for (int k = 0; k < nchunk; ++k) {
-    const cplx<double> v = part[(size_t)k * FS + i];
-    x += v.x;
-    y += v.y;
-  }
-  coef[i] = cmk<cplx<double>>(x * dv, y * dv);
-}
-
 // renormalisation factor per field: c_f = Re(<E,d> - sum_s conj(De[l][s]) C[f][s]) / N0_l;
 // one wave per field, lanes over s, a fixed shuffle tree
 __global__ void __launch_bounds__(256) k_clean_renorm(cplx<double>* __restrict__ coef, int F, int S,
@@ -1345,67 +1222,6 @@ __global__ void __launch_bounds__(256) k_clean_renorm(cplx<double>* __restrict__
   if (lane == 0) {
     const double v = c[S].x - r;
     c[S] = cmk<cplx<double>>(renorm ? v / n0[l] : 0.0, 0.0);
-  }
-}
-
-// d_f(r) -= sum_s C[f][s] phi_s(r) + c_f E_l(r)
-// block: 64 grid points x up to 16 fields of one chunk; coefficients staged in LDS
-template <typename T>
-__global__ void __launch_bounds__(256) k_clean_update(cplx<T>* __restrict__ d, int F,
-                                                      const T* __restrict__ phi, int S,
-                                                      const cplx<T>* __restrict__ E, int L,
-                                                      size_t ng,
-                                                      const cplx<double>* __restrict__ coef) {
-  using C = cplx<T>;
-  constexpr int FB = 16, RB = 64, SB = 128;
-  __shared__ C sc[FB][SB + 1];
-  __shared__ T sphi[32][RB];
-  const size_t r0 = (size_t)blockIdx.x * RB;
-  const int fb0 = blockIdx.y * FB;
-  const int tid = threadIdx.x;
-  const int rr = tid % RB, fq = tid / RB;  // 4 field groups of 4
-  const size_t r = r0 + rr;
-  C acc[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) acc[i] = cmk<C>(0, 0);
-  for (int sb = 0; sb < S; sb += SB) {
-    const int sn = min(SB, S - sb);
-    __syncthreads();
-    for (int e = tid; e < FB * sn; e += 256) {
-      const int ff = e / sn, ss = e % sn;
-      const int f = fb0 + ff;
-      const cplx<double> v = (f < F) ? coef[(size_t)f * (S + 1) + sb + ss] : cmk<cplx<double>>(0, 0);
-      sc[ff][ss] = cmk<C>((T)v.x, (T)v.y);
-    }
-    for (int s2 = 0; s2 < sn; s2 += 32) {
-      const int sm = min(32, sn - s2);
-      __syncthreads();
-      for (int e = tid; e < 32 * RB; e += 256) {
-        const int ss = e / RB, q = e % RB;
-        sphi[ss][q] = (ss < sm && r0 + q < ng) ? phi[(size_t)(sb + s2 + ss) * ng + r0 + q] : (T)0;
-      }
-      __syncthreads();
-      for (int ss = 0; ss < sm; ++ss) {
-        const T p = sphi[ss][rr];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const C c = sc[fq * 4 + i][s2 + ss];
-          acc[i] = cmk<C>(acc[i].x + c.x * p, acc[i].y + c.y * p);
-        }
-      }
-    }
-  }
-  if (r >= ng) return;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int f = fb0 + fq * 4 + i;
-    if (f >= F) continue;
-    const int l = f % L;
-    const T cr = (T)coef[(size_t)f * (S + 1) + S].x;
-    const C e = E[(size_t)l * ng + r];
-    C v = d[(size_t)f * ng + r];
-    v = cmk<C>(v.x - acc[i].x - cr * e.x, v.y - acc[i].y - cr * e.y);
-    d[(size_t)f * ng + r] = v;
   }
 }
 
@@ -1946,27 +1762,17 @@ hipError_t launch_clean(const CleanArgs<T>& a, hipStream_t st) {
     e = launch_update_x3(a.d, a.F, ps, a.E, a.L, a.ng, a.coef, a.part32, st, mid);
     if (e != hipSuccess) return e;
   } else {
-    // 1. end-of-step state and E = Ph H
-    hipLaunchKernelGGL((k_clean_finish<T>), pw_grid(a.ng, a.F), dim3(256), 0, st, a.d, a.u, a.H,
-                       a.ph, a.eta0, a.E, a.L, a.ng, a.dt, a.from_mid);
-    // 2. coefficients of d against phi_s and E_l, and of E_l against phi_s
-    const int nchunk = (int)((a.ng + a.chunk - 1) / a.chunk);
-    dim3 g1((a.F + CT_F - 1) / CT_F, (S + CT_S - 1) / CT_S, nchunk);
-    hipLaunchKernelGGL((k_clean_coef<T>), g1, dim3(256), 0, st, a.d, a.F, a.phi, S, a.E, a.L, a.ng,
-                       a.chunk, a.part);
-    hipLaunchKernelGGL(k_clean_reduce, dim3((a.F * (S + 1) + 255) / 256), dim3(256), 0, st, a.part,
-                       nchunk, a.F * (S + 1), a.dv, a.coef);
-    dim3 g2((a.L + CT_F - 1) / CT_F, (S + CT_S - 1) / CT_S, nchunk);
-    hipLaunchKernelGGL((k_clean_coef<T>), g2, dim3(256), 0, st, a.E, a.L, a.phi, S, a.E, a.L, a.ng,
-                       a.chunk, a.part);
-    hipLaunchKernelGGL(k_clean_reduce, dim3((a.L * (S + 1) + 255) / 256), dim3(256), 0, st, a.part,
-                       nchunk, a.L * (S + 1), a.dv, a.coefE);
+    // the same steps in FP64 (clean_f64.hip); the unperturbed set's
+    // coefficients are the last L rows of coef
+    hipLaunchKernelGGL((k_clean_e<T>), pw_grid(a.ng, a.L), dim3(256), 0, st, a.H, a.ph, a.eta0, a.E,
+                       a.ng, a.from_mid == 2 ? 1 : 0);
+    const MidArgs64 mid{a.from_mid == 1 ? 1 : 0, a.u, a.H, a.ph, 0.5 * a.dt};
+    hipError_t e = launch_coef_f64(a.d, a.F, a.phi, S, a.E, a.L, a.ng, a.dv, a.part, a.coef, st, mid);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_clean_renorm, dim3((a.F + 3) / 4), dim3(256), 0, st, a.coef, a.F, S,
-                       a.coefE, a.n0, a.L, a.renorm);
-    // 3. update
-    dim3 g3((unsigned)((a.ng + 63) / 64), (a.F + 15) / 16);
-    hipLaunchKernelGGL((k_clean_update<T>), g3, dim3(256), 0, st, a.d, a.F, a.phi, S, a.E, a.L,
-                       a.ng, a.coef);
+                       a.coef + (size_t)a.F * (S + 1), a.n0, a.L, a.renorm);
+    e = launch_update_f64(a.d, a.F, a.phi, S, a.E, a.L, a.ng, a.coef, st, mid);
+    if (e != hipSuccess) return e;
   }
   // 4. density of the cleaned state
   hipLaunchKernelGGL((k_density_end<T>), pw_grid(a.ng, a.F / a.L), dim3(256), 0, st, a.d, a.E,
