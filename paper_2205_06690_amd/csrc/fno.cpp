@@ -109,8 +109,7 @@ void ensure(bse_fno* f, int B) {
   f->GU.alloc(sizeof(float2) * (size_t)B * W * f->K);
   f->GV.alloc(sizeof(float2) * (size_t)B * W * f->K);
   const int ci = f->cfg.cin;
-  f->part.alloc(sizeof(float) * std::max(fno_outer_part_len(W, W, B, f->ng),
-                                         fno_outer_part_len(W, std::max(ci, 1), B, f->ng)));
+  f->part.alloc(sizeof(double) * std::max(fno_outer_part_len(W, W, B, f->ng), fno_outer_part_len(W, ci, B, f->ng)));
   f->gy.alloc(sizeof(float) * (size_t)B * f->ng);
   f->y.alloc(sizeof(float) * (size_t)B * f->ng);
   f->loss_part.alloc(sizeof(double) * 2 * (size_t)B * fno_loss_blocks(f->ng));
@@ -163,13 +162,13 @@ double loss_grad(bse_fno* f, int B, const float* x, const float* t) {
   FCK(hipMemcpyAsync(f->tn.p, tn.data(), sizeof(double) * B, hipMemcpyHostToDevice, st));
   FCK(fno_loss_grad(f->y.f(), t, f->tn.d(), B, f->ng, f->gy.f(), st));
   float* g = f->grad.f();
-  FCK(fno_outer(f->gy.f(), 1, f->h[L].f(), W, B, f->ng, f->part.f(), g + f->off_Q, g + f->off_q0, st));
+  FCK(fno_outer(f->gy.f(), 1, f->h[L].f(), W, B, f->ng, f->part.d(), g + f->off_Q, g + f->off_q0, st));
   float* gh = f->gh_a.f();
   float* gn = f->gh_b.f();
   FCK(fno_proj_bwd(f->gy.f(), prm(f, f->off_Q), W, B, f->ng, gh, st));
   for (int l = L - 1; l >= 0; --l) {
     if (l < L - 1) FCK(fno_gelu_bwd(gh, f->z[l].f(), (size_t)B * W * f->ng, st));
-    FCK(fno_outer(gh, W, f->h[l].f(), W, B, f->ng, f->part.f(), g + f->off_W[l], g + f->off_b[l], st));
+    FCK(fno_outer(gh, W, f->h[l].f(), W, B, f->ng, f->part.d(), g + f->off_W[l], g + f->off_b[l], st));
     FCK(fno_fft_fwd(n, gh, B * W, f->tw.c(), m, 1, f->work.c(), f->GU.c(), st));
     FCK(fno_spec_mix_bwd(f->V[l].c(), f->GU.c(), reinterpret_cast<const float2*>(prm(f, f->off_R[l])),
                          B, W, f->K, f->GV.c(), reinterpret_cast<float2*>(g + f->off_R[l]), f->mix_path,
@@ -178,7 +177,7 @@ double loss_grad(bse_fno* f, int B, const float* x, const float* t) {
     FCK(fno_pointwise_bwd(gh, W, prm(f, f->off_W[l]), W, B, f->ng, gn, st));
     std::swap(gh, gn);
   }
-  FCK(fno_outer(gh, W, x, ci, B, f->ng, f->part.f(), g + f->off_P, g + f->off_p, st));
+  FCK(fno_outer(gh, W, x, ci, B, f->ng, f->part.d(), g + f->off_P, g + f->off_p, st));
   return loss;
 }
 

@@ -26,7 +26,7 @@ hipError_t fno_pointwise_bwd(const float* gz, int Cout, const float* Wm, int Cin
                              float* gin, hipStream_t st);
 hipError_t fno_gelu_bwd(float* gh, const float* z, size_t n, hipStream_t st);
 size_t fno_outer_part_len(int Co, int Ci, int B, size_t ng);
-hipError_t fno_outer(const float* A, int Co, const float* X, int Ci, int B, size_t ng, float* part,
+hipError_t fno_outer(const float* A, int Co, const float* X, int Ci, int B, size_t ng, double* part,
                      float* gW, float* gb, hipStream_t st);
 hipError_t fno_proj_bwd(const float* gy, const float* Q, int C, int B, size_t ng, float* gh, hipStream_t st);
 int fno_loss_blocks(size_t ng);

@@ -204,3 +204,28 @@ def test_gather_under_cube_symmetries():
                        bad.get("fm", 0), xd.data_ptr(), td.data_ptr())
         assert e.value.code == bse.BSE_ERR_ARG
     net.close()
+
+
+@pytest.mark.parametrize("n,cin,W,B", [(16, 1, 1, 1), (16, 17, 15, 3), (16, 33, 49, 2), (16, 64, 64, 1), (32, 2, 17, 5)])
+def test_outer_products_channel_tiles(n, cin, W, B):
+    """Gradients of the pointwise layers at channel counts around the 16-wide
+    tiles and wave splits, with x at an address that is only 4-byte aligned.
+    FP32 chains of 64 points: about eps sqrt(64) = 5e-7 per sum."""
+    import torch
+    from paper_2205_06690_amd import bse
+    m, L = 2, 1
+    rng = np.random.default_rng(W)
+    net = bse.Fno(n, cin=cin, width=W, modes=m, layers=L, max_batch=B, bf16_weights=False, seed=4)
+    x = rng.standard_normal((B, cin, n, n, n)).astype(np.float32)
+    t = rng.standard_normal((B, n, n, n)).astype(np.float32)
+    buf = torch.empty(x.size + 1, dtype=torch.float32, device="cuda")
+    buf[1:].copy_(torch.from_numpy(x.ravel()))
+    td = torch.from_numpy(t).cuda()
+    loss, g = net.loss_grad(B, buf.data_ptr() + 4, td.data_ptr())
+    loss_o, g_o = ofno.loss_and_grad(flat_to_dict(net.get_params(compute=True), cin, W, m, L), x.astype(np.float64),
+                                     t.astype(np.float64), n, m, L)
+    gd = flat_to_dict(g, cin, W, m, L)
+    for k in ("P", "p", "Q", "q0", "W0", "b0"):
+        e = np.linalg.norm(gd[k] - g_o[k]) / np.linalg.norm(g_o[k])
+        say(f"outer n={n} cin={cin} W={W} B={B} {k}: {e:.1e}")
+        assert e < 2e-5, k
