@@ -67,7 +67,7 @@ struct bse_fno {
   int cap = 0;
   int mix_path = 0;   // per-mode channel mix: 0 matrix cores, 1 vector FMA
   std::vector<Buf> h, z, V;
-  Buf s, gh_a, gh_b, work, U, GU, GV, part, gy, y, loss_part, tn;
+  Buf gh_a, gh_b, work, U, GU, GV, part, gy, y, loss_part, tn;
   Buf gidx;   // sample indices of bse_fno_gather
 };
 
@@ -101,10 +101,9 @@ void ensure(bse_fno* f, int B) {
   for (auto& b : f->h) b.alloc(act);
   for (auto& b : f->z) b.alloc(act);
   for (auto& b : f->V) b.alloc(sizeof(float2) * (size_t)B * W * f->K);
-  f->s.alloc(act);
   f->gh_a.alloc(act);
   f->gh_b.alloc(act);
-  f->work.alloc(sizeof(float2) * (size_t)B * W * f->ng);
+  f->work.alloc(sizeof(float2) * (size_t)B * W * f->cfg.n * 2 * f->cfg.modes * f->cfg.modes);
   f->U.alloc(sizeof(float2) * (size_t)B * W * f->K);
   f->GU.alloc(sizeof(float2) * (size_t)B * W * f->K);
   f->GV.alloc(sizeof(float2) * (size_t)B * W * f->K);
@@ -119,29 +118,30 @@ void ensure(bse_fno* f, int B) {
 
 const float* prm(const bse_fno* f, size_t off) { return f->compute.f() + off; }
 
-// y [B][ng] from x [B][cin][ng]; activations kept for backward
-void forward(bse_fno* f, int B, const float* x, float* y) {
+// y [B][ng] from x [B][cin][ng]; keep: the pre-activations the backward pass
+// reads are stored (the layers' inputs and spectra always are)
+void forward(bse_fno* f, int B, const float* x, float* y, bool keep) {
   const int W = f->cfg.width, L = f->cfg.layers, m = f->cfg.modes, n = f->cfg.n;
   hipStream_t st = f->stream;
-  FCK(fno_pointwise(x, f->cfg.cin, prm(f, f->off_P), prm(f, f->off_p), W, nullptr, B, f->ng, 0,
-                    nullptr, f->h[0].f(), st));
+  FCK(fno_pointwise(x, f->cfg.cin, prm(f, f->off_P), prm(f, f->off_p), W, B, f->ng, f->h[0].f(), st));
   for (int l = 0; l < L; ++l) {
+    const bool last = l == L - 1;
     FCK(fno_fft_fwd(n, f->h[l].f(), B * W, f->tw.c(), m, 0, f->work.c(), f->V[l].c(), st));
     FCK(fno_spec_mix(f->V[l].c(), reinterpret_cast<const float2*>(prm(f, f->off_R[l])), B, W, f->K,
                      f->U.c(), f->mix_path, st));
-    FCK(fno_fft_inv(n, f->U.c(), B * W, f->tw.c(), m, 1, f->work.c(), f->s.f(), 0, st));
-    FCK(fno_pointwise(f->h[l].f(), W, prm(f, f->off_W[l]), prm(f, f->off_b[l]), W, f->s.f(), B,
-                      f->ng, l < L - 1 ? 1 : 0, f->z[l].f(), f->h[l + 1].f(), st));
+    FCK(fno_x_inv(n, f->U.c(), B * W, f->tw.c(), m, 1, f->work.c(), st));
+    const FnoLayerArgs a{f->h[l].f(), prm(f, f->off_W[l]), 0, prm(f, f->off_b[l]), W, B, m, f->work.c(), f->tw.c(),
+                         last ? 0 : 1, keep && !last ? f->z[l].f() : nullptr, nullptr, f->h[l + 1].f()};
+    FCK(fno_layer(n, a, st));
   }
-  FCK(fno_pointwise(f->h[L].f(), W, prm(f, f->off_Q), prm(f, f->off_q0), 1, nullptr, B, f->ng, 0,
-                    nullptr, y, st));
+  FCK(fno_pointwise(f->h[L].f(), W, prm(f, f->off_Q), prm(f, f->off_q0), 1, B, f->ng, y, st));
 }
 
 // loss and gradient (into f->grad)
 double loss_grad(bse_fno* f, int B, const float* x, const float* t) {
   const int W = f->cfg.width, L = f->cfg.layers, m = f->cfg.modes, n = f->cfg.n, ci = f->cfg.cin;
   hipStream_t st = f->stream;
-  forward(f, B, x, f->y.f());
+  forward(f, B, x, f->y.f(), true);
   const int nbb = fno_loss_blocks(f->ng);
   FCK(fno_loss_partial(f->y.f(), t, B, f->ng, f->loss_part.d(), st));
   std::vector<double> lp(2 * (size_t)B * nbb);
@@ -167,14 +167,16 @@ double loss_grad(bse_fno* f, int B, const float* x, const float* t) {
   float* gn = f->gh_b.f();
   FCK(fno_proj_bwd(f->gy.f(), prm(f, f->off_Q), W, B, f->ng, gh, st));
   for (int l = L - 1; l >= 0; --l) {
-    if (l < L - 1) FCK(fno_gelu_bwd(gh, f->z[l].f(), (size_t)B * W * f->ng, st));
     FCK(fno_outer(gh, W, f->h[l].f(), W, B, f->ng, f->part.d(), g + f->off_W[l], g + f->off_b[l], st));
     FCK(fno_fft_fwd(n, gh, B * W, f->tw.c(), m, 1, f->work.c(), f->GU.c(), st));
     FCK(fno_spec_mix_bwd(f->V[l].c(), f->GU.c(), reinterpret_cast<const float2*>(prm(f, f->off_R[l])),
                          B, W, f->K, f->GV.c(), reinterpret_cast<float2*>(g + f->off_R[l]), f->mix_path,
                          st));
-    FCK(fno_fft_inv(n, f->GV.c(), B * W, f->tw.c(), m, 0, f->work.c(), gn, 0, st));
-    FCK(fno_pointwise_bwd(gh, W, prm(f, f->off_W[l]), W, B, f->ng, gn, st));
+    FCK(fno_x_inv(n, f->GV.c(), B * W, f->tw.c(), m, 0, f->work.c(), st));
+    // to the layer below, through its gelu
+    const FnoLayerArgs a{gh, prm(f, f->off_W[l]), 1, nullptr, W, B, m, f->work.c(), f->tw.c(),
+                         0, nullptr, l > 0 ? f->z[l - 1].f() : nullptr, gn};
+    FCK(fno_layer(n, a, st));
     std::swap(gh, gn);
   }
   FCK(fno_outer(gh, W, x, ci, B, f->ng, f->part.d(), g + f->off_P, g + f->off_p, st));
@@ -249,7 +251,6 @@ bse_status bse_fno_create(const bse_fno_config* cfg, bse_fno** out) {
     }
     f->tw.alloc(sizeof(float2) * c.n);
     FCK(hipMemcpy(f->tw.p, tw.data(), sizeof(float2) * c.n, hipMemcpyHostToDevice));
-    fno_configure(c.n);
     FCK(hipDeviceSynchronize());
   } catch (...) {
     delete f;
@@ -302,7 +303,7 @@ bse_status bse_fno_forward(bse_fno* f, int32_t B, const void* x_dev, void* y_dev
   FAPI_BEGIN
   check_batch(f, B);
   if (!x_dev || !y_dev) ffail(BSE_ERR_ARG, "null buffer");
-  forward(f, B, reinterpret_cast<const float*>(x_dev), reinterpret_cast<float*>(y_dev));
+  forward(f, B, reinterpret_cast<const float*>(x_dev), reinterpret_cast<float*>(y_dev), false);
   FCK(hipStreamSynchronize(f->stream));
   FAPI_END
 }

@@ -5,14 +5,28 @@
 
 namespace bse {
 bool fno_grid_supported(int n);
-void fno_configure(int n);
-// V[F][K] = DFT of real fields on the kept modes (times c_k/ng if ck)
-hipError_t fno_fft_fwd(int n, const float* in, int F, const float2* tw, int m, int ck, float2* work,
+// V[F][K] = DFT of real fields on the kept modes (times c_k/ng if ck);
+// P [F][n][2 m^2] takes the planes' kept columns on the way
+hipError_t fno_fft_fwd(int n, const float* in, int F, const float2* tw, int m, int ck, float2* P,
                        float2* V, hipStream_t st);
-// out[F][ng] (=, or += when accumulate) = Re unnormalised inverse DFT of U on the kept modes
-// (U times c_k/ng if ck)
-hipError_t fno_fft_inv(int n, const float2* U, int F, const float2* tw, int m, int ck, float2* work,
-                       float* out, int accumulate, hipStream_t st);
+// P[F][n][2 m^2] = unnormalised inverse DFT along x of U on the kept modes (U times c_k/ng if ck)
+hipError_t fno_x_inv(int n, const float2* U, int F, const float2* tw, int m, int ck, float2* P, hipStream_t st);
+// q[b][o] = sum_i M[o][i] in[b][i] + bias[o] + Re inverse (y, z) DFT of P[b][o];
+// zout = q; out = gelu(q) (act) or q, times gelu'(zg) where zg is given
+struct FnoLayerArgs {
+  const float* in;      // [B][W][ng]
+  const float* M;       // [W][W]; trans: its transpose is applied
+  int trans;
+  const float* bias;    // nullable [W]
+  int W, B, m;
+  const float2* P;      // [B W][n][2 m^2]
+  const float2* tw;
+  int act;
+  float* zout;          // nullable [B][W][ng]
+  const float* zg;      // nullable [B][W][ng]
+  float* out;           // [B][W][ng]
+};
+hipError_t fno_layer(int n, const FnoLayerArgs& a, hipStream_t st);
 // per-mode channel mix U[b][o][k] = sum_i V[b][i][k] R[k][i][o] and its two
 // backward products; path 0: matrix cores (up to 32 channels), 1: vector FMA
 hipError_t fno_spec_mix(const float2* V, const float2* R, int B, int C, int K, float2* U, int path,
@@ -20,11 +34,7 @@ hipError_t fno_spec_mix(const float2* V, const float2* R, int B, int C, int K, f
 hipError_t fno_spec_mix_bwd(const float2* V, const float2* GU, const float2* R, int B, int C, int K,
                             float2* GV, float2* GR, int path, hipStream_t st);
 hipError_t fno_pointwise(const float* in, int Cin, const float* Wm, const float* bias, int Cout,
-                         const float* add, int B, size_t ng, int act, float* zout, float* out,
-                         hipStream_t st);
-hipError_t fno_pointwise_bwd(const float* gz, int Cout, const float* Wm, int Cin, int B, size_t ng,
-                             float* gin, hipStream_t st);
-hipError_t fno_gelu_bwd(float* gh, const float* z, size_t n, hipStream_t st);
+                         int B, size_t ng, float* out, hipStream_t st);
 size_t fno_outer_part_len(int Co, int Ci, int B, size_t ng);
 hipError_t fno_outer(const float* A, int Co, const float* X, int Ci, int B, size_t ng, double* part,
                      float* gW, float* gb, hipStream_t st);

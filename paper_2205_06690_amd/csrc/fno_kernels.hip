@@ -2,11 +2,10 @@
 // for gfx950 (FP32 activations and accumulation, weights rounded to BF16).
 //
 // Spectral convolution on the kept modes K = {kx, ky in [-m, m), kz in
-// [0, m)}: a truncated 3-D DFT (full y-z plane transforms, then x lines of
-// the kept (ky, kz) columns only, gathered to [field][K]), a per-mode
-// complex channel mix, and the adjoint path (scatter to the kept columns,
-// inverse x lines, inverse y-z planes, real part).  The DFT machinery is the
-// LDS four-step line transform of fft_lines.h.
+// [0, m)}: a truncated 3-D DFT that forms the kept frequencies only (planes to
+// the kept (ky, kz), then x lines), a per-mode complex channel mix, and the
+// adjoint path, whose last axes are part of the GEMM of the pointwise layer.
+// The codelets are those of fft_lines.h.
 #include <hip/hip_runtime.h>
 
 #include "fft_lines.h"
@@ -16,10 +15,6 @@
 
 namespace bse {
 
-template <int N> constexpr int fplane_stride() { return N + 1; }
-template <int N> __device__ __forceinline__ int fplane_idx(int e) {
-  return (e / N) * fplane_stride<N>() + (e % N);
-}
 // the twiddle table copied into LDS (the transforms then read it through the
 // LDS counter, not behind the vector-memory loads of the data)
 template <int N>
@@ -27,171 +22,172 @@ __device__ __forceinline__ void fno_tw_lds(float2* t, const float2* __restrict__
   for (int i = tid; i < N; i += nthr) t[i] = tw[i];
 }
 
-// scrambled slot of natural frequency index k (inverse of scr2k)
-template <int N> __device__ __forceinline__ int k2scr(int k) {
+// ---------------------------------------------------------------------------
+// Truncated transforms.  Only K's frequencies are ever formed: with N = N1 N2
+// (j = j1 N2 + j2, k1 = k mod N1),
+//   X[k]  = sum_j2 w^(j2 k) A[k1][j2],  A[k1][j2] = DFT_N1 over j1 of x,
+//   x[j]  = DFT_N1^-1 over k1 of  sum_{k = k1 mod N1} U[k] w^(-j2 k),
+// so an axis costs its N1-point codelets and N2 products per kept frequency,
+// and what passes between the axes is the kept part: planes P[field][x][c],
+// c = (ky + m) m + kz, 2 m^2 of the N^2 values of a plane.
+// ---------------------------------------------------------------------------
+template <int N> struct FnoGeo {
+  static constexpr int N1 = Fac<N>::N1, N2 = Fac<N>::N2;
+  static constexpr int S = N + 8;                        // LDS row of y values: eight rows on distinct banks
+  static constexpr int G = N * N2 < 256 ? 256 / (N * N2) : 1;   // planes a block takes at once
+  static constexpr int IPT = G * N * N2 / 256;
+};
+
+// real planes -> kept (ky, kz): z rows from registers (lanes over j2, then y),
+// then the y lines of the m kept kz.  A block walks `per` groups of G planes,
+// the next group's loads in flight.  Bound by reading the field once and by
+// its four barriers: 64^3, 256 fields, m = 8, 268 MB in 82 us (3.3 TB/s) plus
+// 6 us for the x lines, against 287 + 29 us for full plane transforms that
+// wrote all N^2 complex values of a plane and gathered the kept ones.
+template <int N, int MM>
+__global__ void __launch_bounds__(256) k_fno_plane_fwd(const float* __restrict__ in, unsigned np, int per,
+                                                       const float2* __restrict__ tw, int m_,
+                                                       float2* __restrict__ out) {
+  using Ge = FnoGeo<N>;
+  constexpr int N1 = Ge::N1, N2 = Ge::N2, S = Ge::S, G = Ge::G, IPT = Ge::IPT, ZS = N + 1;
+  extern __shared__ unsigned char smem_raw[];
+  const int m = MM ? MM : m_, ncol = 2 * m * m, tid = threadIdx.x;
+  float2* t = reinterpret_cast<float2*>(smem_raw);
+  float2* Z = t + G * N * S;
+  float2* twl = Z + G * m * ZS;
+  fno_tw_lds<N>(twl, tw, tid, 256);
+  float a[IPT][N1];
+  auto load = [&](unsigned p) {
+#pragma unroll
+    for (int it = 0; it < IPT; ++it) {
+      const int w = tid + 256 * it;
+      const unsigned pp = min(p + (unsigned)(w / (N * N2)), np - 1);
+      const float* src = in + (size_t)pp * (N * N) + (size_t)((w / N2) % N) * N + w % N2;
+#pragma unroll
+      for (int j1 = 0; j1 < N1; ++j1) a[it][j1] = src[j1 * N2];
+    }
+  };
+  const unsigned p0 = blockIdx.x * (unsigned)(per * G);
+  load(p0);
+  for (int q = 0; q < per; ++q) {
+    const unsigned p = p0 + q * G;
+    if (p >= np) break;
+#pragma unroll
+    for (int it = 0; it < IPT; ++it) {
+      const int w = tid + 256 * it, g = w / (N * N2), y = (w / N2) % N, j2 = w % N2;
+      float2 v[N1];
+#pragma unroll
+      for (int j1 = 0; j1 < N1; ++j1) v[j1] = make_float2(a[it][j1], 0.f);
+      Dft<N1, -1, float2>::run(v);
+#pragma unroll
+      for (int k1 = 0; k1 < N1; ++k1)
+        if (k1 < m) t[(g * N + k1 * N2 + j2) * S + y] = v[k1];
+    }
+    __syncthreads();
+    if (q + 1 < per && p + G < np) load(p + G);
+    for (int w = tid; w < G * m * N; w += 256) {
+      const int y = w % N, k = (w / N) % m, g = w / (N * m);
+      const float2* r = t + (g * N + (k % N1) * N2) * S + y;
+      float2 acc = r[0];
+#pragma unroll
+      for (int j2 = 1; j2 < N2; ++j2) acc = cadd(acc, cmul(r[j2 * S], twl[(j2 * k) % N]));
+      Z[(g * m + k) * ZS + y] = acc;
+    }
+    __syncthreads();
+    for (int w = tid; w < G * m * N2; w += 256) {
+      const int kz = w % m, j2 = (w / m) % N2, g = w / (m * N2);
+      float2 v[N1];
+#pragma unroll
+      for (int j1 = 0; j1 < N1; ++j1) v[j1] = Z[(g * m + kz) * ZS + j1 * N2 + j2];
+      Dft<N1, -1, float2>::run(v);
+#pragma unroll
+      for (int k1 = 0; k1 < N1; ++k1) t[g * N * S + (k1 * N2 + j2) * m + kz] = v[k1];
+    }
+    __syncthreads();
+    for (int w = tid; w < G * ncol; w += 256) {
+      const int c = w % ncol, g = w / ncol, kz = c % m, k = (c / m - m + N) % N;
+      const float2* r = t + g * N * S + (k % N1) * N2 * m + kz;
+      float2 acc = r[0];
+#pragma unroll
+      for (int j2 = 1; j2 < N2; ++j2) acc = cadd(acc, cmul(r[j2 * m], twl[(j2 * k) % N]));
+      if (p + g < np) out[(size_t)(p + g) * ncol + c] = acc;
+    }
+    __syncthreads();
+  }
+}
+
+// x lines of KC kept columns, P[f][x][c] -> V[f][kx][c] (times c_k/ng if
+// ck_scale); V's mode order is kx-major, then ky, then kz
+constexpr int KC = 32;
+template <int N>
+__global__ void __launch_bounds__(256) k_fno_x_fwd(const float2* __restrict__ P, const float2* __restrict__ tw, int m,
+                                                   int ck_scale, float2* __restrict__ V) {
   constexpr int N1 = Fac<N>::N1, N2 = Fac<N>::N2;
-  return (k % N1) * N2 + k / N1;
-}
-
-// ---------------------------------------------------------------------------
-// truncated forward DFT: real fields [F][ng] -> V[F][K] (times c_k/ng if
-// ck_scale, else times 1)
-// ---------------------------------------------------------------------------
-template <int N>
-__global__ void __launch_bounds__(256) k_fno_yz_fwd_t(const float* __restrict__ in,
-                                                     float2* __restrict__ work,
-                                                     const float2* __restrict__ tw) {
-  extern __shared__ unsigned char smem_raw[];
-  float2* s = reinterpret_cast<float2*>(smem_raw);
-  constexpr int P = N * N, S = fplane_stride<N>(), NT = 256;
-  const size_t ng = (size_t)N * N * N;
-  const int x = blockIdx.x, f = blockIdx.y, tid = threadIdx.x;
-  const float* src = in + (size_t)f * ng + (size_t)x * P;
-  float2* twl = s + N * S;
-  fno_tw_lds<N>(twl, tw, tid, NT);
-  for (int e = tid; e < P; e += NT) s[fplane_idx<N>(e)] = make_float2(src[e], 0.f);
-  __syncthreads();
-  NoMul nm;
-  stageA_fwd<N>(s, N, S, 1, twl, tid, NT, true);
-  __syncthreads();
-  stageB<N, 0>(s, N, S, 1, twl, tid, NT, true, nm);
-  __syncthreads();
-  stageA_fwd<N>(s, N, 1, S, twl, tid, NT, true);
-  __syncthreads();
-  stageB<N, 0>(s, N, 1, S, twl, tid, NT, true, nm);
-  __syncthreads();
-  float2* dst = work + (size_t)f * ng + (size_t)x * P;
-  for (int e = tid; e < P; e += NT) dst[e] = s[fplane_idx<N>(e)];
-}
-
-// kept columns: 2m x m (ky, kz); block = (field, group of KC columns)
-constexpr int KC = 16;
-template <int N>
-__global__ void __launch_bounds__(256) k_fno_x_gather(const float2* __restrict__ work,
-                                                      const float2* __restrict__ tw, int m,
-                                                      int ck_scale, float2* __restrict__ V) {
-  __shared__ float2 s[N * KC];
+  __shared__ float2 t[N * KC];
   __shared__ float2 twl[N];
-  fno_tw_lds<N>(twl, tw, threadIdx.x, 256);
-  const size_t ng = (size_t)N * N * N;
-  const int f = blockIdx.y, tid = threadIdx.x;
-  const int ncol = 2 * m * m;
-  const int K = 2 * m * 2 * m * m;
-  const int col0 = blockIdx.x * KC;
-  // load x lines of KC kept columns (zero past the last column)
-  for (int e = tid; e < N * KC; e += 256) {
-    const int x = e / KC, c = e % KC;
-    const int col = col0 + c;
+  const int f = blockIdx.y, tid = threadIdx.x, ncol = 2 * m * m, c0 = blockIdx.x * KC;
+  fno_tw_lds<N>(twl, tw, tid, 256);
+  for (int w = tid; w < N2 * KC; w += 256) {
+    const int c = w % KC, j2 = w / KC;
+    if (c0 + c >= ncol) continue;
+    const float2* src = P + ((size_t)f * N + j2) * ncol + c0 + c;
+    float2 v[N1];
+#pragma unroll
+    for (int j1 = 0; j1 < N1; ++j1) v[j1] = src[(size_t)j1 * N2 * ncol];
+    Dft<N1, -1, float2>::run(v);
+#pragma unroll
+    for (int k1 = 0; k1 < N1; ++k1) t[(k1 * N2 + j2) * KC + c] = v[k1];
+  }
+  __syncthreads();
+  const float inv = 1.0f / ((float)N * N * N);
+  for (int w = tid; w < 2 * m * KC; w += 256) {
+    const int c = w % KC, jx = w / KC, k = (jx - m + N) % N;
+    if (c0 + c >= ncol) continue;
+    const float2* r = t + (k % N1) * N2 * KC + c;
+    float2 acc = r[0];
+#pragma unroll
+    for (int j2 = 1; j2 < N2; ++j2) acc = cadd(acc, cmul(r[j2 * KC], twl[(j2 * k) % N]));
+    if (ck_scale) acc = cscale(acc, ((c0 + c) % m == 0 ? 1.0f : 2.0f) * inv);
+    V[((size_t)f * 2 * m + jx) * ncol + c0 + c] = acc;
+  }
+}
+
+// adjoint of k_fno_x_fwd: U[f][kx][c] (times c_k/ng if ck_scale) -> P[f][x][c]
+template <int N>
+__global__ void __launch_bounds__(256) k_fno_x_inv(const float2* __restrict__ U, const float2* __restrict__ tw, int m,
+                                                   int ck_scale, float2* __restrict__ P) {
+  constexpr int N1 = Fac<N>::N1, N2 = Fac<N>::N2;
+  __shared__ float2 t[N * KC];
+  __shared__ float2 twl[N];
+  const int f = blockIdx.y, tid = threadIdx.x, ncol = 2 * m * m, c0 = blockIdx.x * KC;
+  fno_tw_lds<N>(twl, tw, tid, 256);
+  const float inv = 1.0f / ((float)N * N * N);
+  for (int w = tid; w < 2 * m * KC; w += 256) {
+    const int c = w % KC, jx = w / KC;
     float2 v = make_float2(0.f, 0.f);
-    if (col < ncol) {
-      const int jy = col / m, kz = col % m;
-      const int ky = jy - m;                     // signed
-      const int ys = k2scr<N>((ky + N) % N), zs = k2scr<N>(kz);
-      v = work[(size_t)f * ng + (size_t)x * N * N + (size_t)ys * N + zs];
+    if (c0 + c < ncol) {
+      v = U[((size_t)f * 2 * m + jx) * ncol + c0 + c];
+      if (ck_scale) v = cscale(v, ((c0 + c) % m == 0 ? 1.0f : 2.0f) * inv);
     }
-    s[x * KC + c] = v;
+    t[jx * KC + c] = v;
   }
   __syncthreads();
-  NoMul nm;
-  stageA_fwd<N>(s, KC, 1, KC, twl, tid, 256, true);
-  __syncthreads();
-  stageB<N, 0>(s, KC, 1, KC, twl, tid, 256, true, nm);
-  __syncthreads();
-  const float inv = 1.0f / (float)ng;
-  for (int e = tid; e < 2 * m * KC; e += 256) {
-    const int jx = e / KC, c = e % KC;
-    const int col = col0 + c;
-    if (col >= ncol) continue;
-    const int jy = col / m, kz = col % m;
-    const int kx = jx - m;
-    float2 v = s[k2scr<N>((kx + N) % N) * KC + c];
-    if (ck_scale) {
-      const float sc = (kz == 0 ? 1.0f : 2.0f) * inv;
-      v.x *= sc;
-      v.y *= sc;
+  for (int w = tid; w < N2 * KC; w += 256) {
+    const int c = w % KC, j2 = w / KC;
+    if (c0 + c >= ncol) continue;
+    float2 v[N1];
+#pragma unroll
+    for (int k1 = 0; k1 < N1; ++k1) {
+      float2 acc = make_float2(0.f, 0.f);
+      for (int k = k1; k < m; k += N1) acc = cadd(acc, cmulc(t[(k + m) * KC + c], twl[(j2 * k) % N]));
+      for (int k = N - N1 + k1; k >= N - m; k -= N1)
+        acc = cadd(acc, cmulc(t[(k - N + m) * KC + c], twl[(j2 * k) % N]));
+      v[k1] = acc;
     }
-    // mode index: kx-major, then ky, then kz
-    V[(size_t)f * K + ((size_t)jx * 2 * m + jy) * m + kz] = v;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// adjoint: U[F][K] (times c_k/ng if ck_scale) -> real fields [F][ng]
-// (out = result, or out += result when accumulate)
-// ---------------------------------------------------------------------------
-template <int N>
-__global__ void __launch_bounds__(256) k_fno_x_scatter(const float2* __restrict__ U,
-                                                       const float2* __restrict__ tw, int m,
-                                                       int ck_scale, float2* __restrict__ work) {
-  __shared__ float2 s[N * KC];
-  __shared__ float2 twl[N];
-  fno_tw_lds<N>(twl, tw, threadIdx.x, 256);
-  const size_t ng = (size_t)N * N * N;
-  const int f = blockIdx.y, tid = threadIdx.x;
-  const int ncol = 2 * m * m;
-  const int K = 2 * m * 2 * m * m;
-  const int col0 = blockIdx.x * KC;
-  for (int e = tid; e < N * KC; e += 256) s[e] = make_float2(0.f, 0.f);
-  __syncthreads();
-  const float inv = 1.0f / (float)ng;
-  for (int e = tid; e < 2 * m * KC; e += 256) {
-    const int jx = e / KC, c = e % KC;
-    const int col = col0 + c;
-    if (col >= ncol) continue;
-    const int jy = col / m, kz = col % m;
-    const int kx = jx - m;
-    float2 v = U[(size_t)f * K + ((size_t)jx * 2 * m + jy) * m + kz];
-    if (ck_scale) {
-      const float sc = (kz == 0 ? 1.0f : 2.0f) * inv;
-      v.x *= sc;
-      v.y *= sc;
-    }
-    s[k2scr<N>((kx + N) % N) * KC + c] = v;
-  }
-  __syncthreads();
-  NoMul nm;
-  stageB<N, 1>(s, KC, 1, KC, twl, tid, 256, true, nm);
-  __syncthreads();
-  stageC_inv<N>(s, KC, 1, KC, tid, 256, true);
-  __syncthreads();
-  for (int e = tid; e < N * KC; e += 256) {
-    const int x = e / KC, c = e % KC;
-    const int col = col0 + c;
-    if (col >= ncol) continue;
-    const int jy = col / m, kz = col % m;
-    const int ky = jy - m;
-    const int ys = k2scr<N>((ky + N) % N), zs = k2scr<N>(kz);
-    work[(size_t)f * ng + (size_t)x * N * N + (size_t)ys * N + zs] = s[x * KC + c];
-  }
-}
-
-template <int N>
-__global__ void __launch_bounds__(256) k_fno_yz_inv(const float2* __restrict__ work,
-                                                    const float2* __restrict__ tw,
-                                                    float* __restrict__ out, int accumulate) {
-  extern __shared__ unsigned char smem_raw[];
-  float2* s = reinterpret_cast<float2*>(smem_raw);
-  constexpr int P = N * N, S = fplane_stride<N>(), NT = 256;
-  const size_t ng = (size_t)N * N * N;
-  const int x = blockIdx.x, f = blockIdx.y, tid = threadIdx.x;
-  const float2* src = work + (size_t)f * ng + (size_t)x * P;
-  float2* twl = s + N * S;
-  fno_tw_lds<N>(twl, tw, tid, NT);
-  for (int e = tid; e < P; e += NT) s[fplane_idx<N>(e)] = src[e];
-  __syncthreads();
-  NoMul nm;
-  stageB<N, 1>(s, N, S, 1, twl, tid, NT, true, nm);
-  __syncthreads();
-  stageC_inv<N>(s, N, S, 1, tid, NT, true);
-  __syncthreads();
-  stageB<N, 1>(s, N, 1, S, twl, tid, NT, true, nm);
-  __syncthreads();
-  stageC_inv<N>(s, N, 1, S, tid, NT, true);
-  __syncthreads();
-  float* dst = out + (size_t)f * ng + (size_t)x * P;
-  for (int e = tid; e < P; e += NT) {
-    const float v = s[fplane_idx<N>(e)].x;
-    dst[e] = accumulate ? dst[e] + v : v;
+    Dft<N1, +1, float2>::run(v);
+    float2* dst = P + ((size_t)f * N + j2) * ncol + c0 + c;
+#pragma unroll
+    for (int j1 = 0; j1 < N1; ++j1) dst[(size_t)j1 * N2 * ncol] = v[j1];
   }
 }
 
@@ -436,16 +432,15 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
   return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * expf(-0.5f * z * z) * 0.3989422804014327f;
 }
 
-// out[b][o][r] = sum_i Wm[o][i] in[b][i][r] + bias[o] (+ add[b][o][r]);
-// act: 0 none, 1 gelu (pre-activation kept in zout when non-null).
-// CIN/COUT > 0: compile-time channel counts (inputs stay in registers).
+// out[b][o][r] = sum_i Wm[o][i] in[b][i][r] + bias[o] (the lift and the
+// projection).  CIN/COUT > 0: compile-time channel counts (inputs stay in
+// registers).
 constexpr int PW_MAXC = 64;
 template <int CIN, int COUT>
 __global__ void __launch_bounds__(256) k_pointwise(const float* __restrict__ in, int Cin_,
                                                    const float* __restrict__ Wm,
-                                                   const float* __restrict__ bias, int Cout_,
-                                                   const float* __restrict__ add, size_t ng, int act,
-                                                   float* __restrict__ zout, float* __restrict__ out) {
+                                                   const float* __restrict__ bias, int Cout_, size_t ng,
+                                                   float* __restrict__ out) {
   const int Cin = CIN > 0 ? CIN : Cin_;
   const int Cout = COUT > 0 ? COUT : Cout_;
   __shared__ float sw[PW_MAXC * PW_MAXC];
@@ -466,43 +461,187 @@ __global__ void __launch_bounds__(256) k_pointwise(const float* __restrict__ in,
 #pragma unroll
     for (int i = 0; i < (CIN > 0 ? CIN : PW_MAXC); ++i)
       if (i < Cin) acc += sw[o * Cin + i] * xin[i];
-    const size_t oi = ((size_t)b * Cout + o) * ng + r;
-    if (add) acc += add[oi];
-    if (zout) zout[oi] = acc;
-    out[oi] = act ? gelu_f(acc) : acc;
+    out[((size_t)b * Cout + o) * ng + r] = acc;
   }
 }
 
-// gin[b][i][r] += sum_o Wm[o][i] gz[b][o][r]
-template <int COUT>
-__global__ void __launch_bounds__(256) k_pointwise_bwd(const float* __restrict__ gz, int Cout_,
-                                                       const float* __restrict__ Wm, int Cin,
-                                                       size_t ng, float* __restrict__ gin) {
-  const int Cout = COUT > 0 ? COUT : Cout_;
-  __shared__ float sw[PW_MAXC * PW_MAXC];
-  for (int e = threadIdx.x; e < Cin * Cout; e += 256) sw[e] = Wm[e];
+// One Fourier layer behind the channel mix, on the FP32 matrix cores: for a
+// row of z points (b, x, y)
+//   q[o][z] = sum_i M[o][i] in[i][z] + bias[o] + Re sum_kz Y[o][kz] e^(i kz z)
+// is one GEMM with contraction over [i | Re kz, Im kz], Y the inverse y
+// transform of the kept plane P (rows of eight or so y lines at a time in
+// LDS), so the spectral part never exists as a field.  Then
+//   forward:  zout = q (kept for the backward pass when given),
+//             out = gelu(q) (act) or q
+//   backward: (M = W^T through trans, no bias) out = q gelu'(zg) when zg is
+//             given: the gradient in front of the previous layer's gelu.
+// Lane l supplies row l % 16 of M or Y and points CT (l % 16) .. of the CT
+// column tiles (one 16-byte load per channel at 64 points a row) and holds
+// rows 4 (l / 16) + v of those points, so rows of `out` are written whole.
+// A block takes one x plane's y = j1 N2 + j2 for nj values of j2; a wave
+// takes one y at a time with the next one's loads in flight.  KQ > 0: m <= 8,
+// the z phases in registers.  Bound by the fields read and written and by
+// erff: at 64^3, 32 channels, batch 8 (all three fields) 0.20 ms for 805 MB,
+// batch 3 without zout 69 us for 201 MB, against 281 (inverse planes) + 50
+// (scatter) + 71 (clearing the work array) + 259 us (pointwise) at batch 8,
+// and in the backward pass 179 (pointwise) + 224 us (gelu').
+template <int N, int T, int KQ>
+__global__ void __launch_bounds__(256, T <= 2 ? 2 : 1)
+    k_fno_layer(const float* __restrict__ in, const float* __restrict__ M, int trans, const float* __restrict__ bias,
+                int W, const float2* __restrict__ P, int m, const float2* __restrict__ tw, int nj, int act,
+                float* __restrict__ zout, const float* __restrict__ zg, float* __restrict__ out) {
+  constexpr int N1 = Fac<N>::N1, N2 = Fac<N>::N2, CT = N / 16, WP = 16 * T;
+  typedef float vec __attribute__((ext_vector_type(CT)));
+  extern __shared__ unsigned char smem_raw[];
+  const int ks = KQ ? KQ : (2 * m + 3) / 4, Qp = 4 * ks + 4;
+  float* yc = reinterpret_cast<float*>(smem_raw);               // [row][o][2 kz, 2 kz + 1]
+  float2* twl = reinterpret_cast<float2*>(yc + N1 * nj * WP * Qp);
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
+  const int ngr = N2 / nj, x = blockIdx.x / ngr, j20 = (blockIdx.x % ngr) * nj, b = blockIdx.y;
+  const size_t ng = (size_t)N * N * N;
+  const int ncol = 2 * m * m;
+  fno_tw_lds<N>(twl, tw, tid, 256);
+  float am[T][4 * T];
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int s = 0; s < 4 * T; ++s) {
+      const int o = 16 * t + lr, i = 4 * s + lk;
+      am[t][s] = (o < W && i < W) ? (trans ? M[i * W + o] : M[o * W + i]) : 0.f;
+    }
+  float ab[T][4];
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) ab[t][v] = (bias && 16 * t + 4 * lk + v < W) ? bias[16 * t + 4 * lk + v] : 0.f;
+  const int nrow = N1 * nj, wv = tid >> 6;
+  auto row_off = [&](int r) -> size_t {
+    return (size_t)x * N * N + (size_t)((r % N1) * N2 + j20 + r / N1) * N;
+  };
+  // channels past the last: a copy of it times a zero of M
+  vec nx[4 * T];
+  auto load = [&](int r) {
+    const float* src = in + (size_t)b * W * ng + row_off(r) + CT * lr;
+#pragma unroll
+    for (int s = 0; s < 4 * T; ++s) nx[s] = *reinterpret_cast<const vec*>(src + (size_t)min(4 * s + lk, W - 1) * ng);
+  };
+  if (wv < nrow) load(wv);
   __syncthreads();
-  const size_t r = (size_t)blockIdx.x * 256 + threadIdx.x;
-  const int b = blockIdx.y;
-  if (r >= ng) return;
-  float g[COUT > 0 ? COUT : PW_MAXC];
+  // inverse y transform of the kept plane for this block's rows
+  for (int w = tid; w < W * m; w += 256) {
+    const int o = w / m, kz = w % m;
+    const float2* src = P + ((size_t)(b * W + o) * N + x) * ncol + kz;
+    for (int jj = 0; jj < nj; ++jj) {
+      const int j2 = j20 + jj;
+      float2 v[N1];
 #pragma unroll
-  for (int o = 0; o < (COUT > 0 ? COUT : PW_MAXC); ++o)
-    if (o < Cout) g[o] = gz[((size_t)b * Cout + o) * ng + r];
-#pragma unroll 4
-  for (int i = 0; i < Cin; ++i) {
-    float acc = 0.f;
+      for (int k1 = 0; k1 < N1; ++k1) {
+        float2 acc = make_float2(0.f, 0.f);
+        for (int k = k1; k < m; k += N1) acc = cadd(acc, cmulc(src[(k + m) * m], twl[(j2 * k) % N]));
+        for (int k = N - N1 + k1; k >= N - m; k -= N1)
+          acc = cadd(acc, cmulc(src[(k - N + m) * m], twl[(j2 * k) % N]));
+        v[k1] = acc;
+      }
+      Dft<N1, +1, float2>::run(v);
 #pragma unroll
-    for (int o = 0; o < (COUT > 0 ? COUT : PW_MAXC); ++o)
-      if (o < Cout) acc += sw[o * Cin + i] * g[o];
-    gin[((size_t)b * Cin + i) * ng + r] += acc;
+      for (int j1 = 0; j1 < N1; ++j1)
+        *reinterpret_cast<float2*>(yc + ((jj * N1 + j1) * WP + o) * Qp + 2 * kz) = v[j1];
+    }
   }
-}
-
-// gz = gh * gelu'(z)   (in place on gh)
-__global__ void k_gelu_bwd(float* __restrict__ gh, const float* __restrict__ z, size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) gh[i] *= gelu_grad_f(z[i]);
+  // contraction entries past the last frequency
+  const int np = 4 * ks - 2 * m;
+  for (int w = tid; w < nrow * WP * np; w += 256) yc[(w / np) * Qp + 2 * m + w % np] = 0.f;
+  float tq[KQ ? KQ : 1][CT];
+  auto phase = [&](int s, int c) -> float {
+    const int q = 4 * s + lk, kz = q >> 1;
+    const float2 e = twl[(kz * (CT * lr + c)) % N];
+    return kz < m ? ((q & 1) ? e.y : e.x) : 0.f;
+  };
+  if (KQ) {
+#pragma unroll
+    for (int s = 0; s < KQ; ++s)
+#pragma unroll
+      for (int c = 0; c < CT; ++c) tq[s][c] = phase(s, c);
+  }
+  __syncthreads();
+  for (int r = wv; r < nrow; r += 4) {
+    vec cx[4 * T];
+#pragma unroll
+    for (int s = 0; s < 4 * T; ++s) cx[s] = nx[s];
+    if (r + 4 < nrow) load(r + 4);
+    mf4 acc[T][CT];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int c = 0; c < CT; ++c) acc[t][c] = mf4{ab[t][0], ab[t][1], ab[t][2], ab[t][3]};
+    const float* yr = yc + (size_t)r * WP * Qp + lr * Qp + lk;
+    if (KQ) {
+#pragma unroll
+      for (int s = 0; s < KQ; ++s)
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+          const float ay = yr[16 * t * Qp + 4 * s];
+#pragma unroll
+          for (int c = 0; c < CT; ++c) acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(ay, tq[s][c], acc[t][c], 0, 0, 0);
+        }
+    } else {
+      for (int s = 0; s < ks; ++s) {
+        float e[CT];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) e[c] = phase(s, c);
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+          const float ay = yr[16 * t * Qp + 4 * s];
+#pragma unroll
+          for (int c = 0; c < CT; ++c) acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(ay, e[c], acc[t][c], 0, 0, 0);
+        }
+      }
+    }
+    // the channels in chains of 16, added to the spectral part's: shorter
+    // FP32 chains than one over everything
+#pragma unroll
+    for (int h = 0; h < T; ++h) {
+      mf4 part[T][CT];
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) part[t][c] = mf4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 4 * h; s < 4 * h + 4; ++s)
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+          for (int c = 0; c < CT; ++c)
+            part[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(am[t][s], cx[s][c], part[t][c], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) acc[t][c] += part[t][c];
+    }
+    const size_t off = (size_t)b * W * ng + row_off(r) + CT * lr;
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int o = 16 * t + 4 * lk + v;
+        if (o >= W) continue;
+        const size_t oi = off + (size_t)o * ng;
+        vec q;
+#pragma unroll
+        for (int c = 0; c < CT; ++c) q[c] = acc[t][c][v];
+        if (zout) *reinterpret_cast<vec*>(zout + oi) = q;
+        if (act) {
+#pragma unroll
+          for (int c = 0; c < CT; ++c) q[c] = gelu_f(q[c]);
+        }
+        if (zg) {
+          const vec zv = *reinterpret_cast<const vec*>(zg + oi);
+#pragma unroll
+          for (int c = 0; c < CT; ++c) q[c] *= gelu_grad_f(zv[c]);
+        }
+        *reinterpret_cast<vec*>(out + oi) = q;
+      }
+  }
 }
 
 // Outer products over points, gW[o][i] = sum_{b,r} A[b][o][r] X[b][i][r] and
@@ -718,31 +857,61 @@ __global__ void k_round_copy(const float* __restrict__ src, float* __restrict__ 
 // ---------------------------------------------------------------------------
 template <int N>
 struct FnoLaunch {
-  static hipError_t fwd(const float* in, int F, const float2* tw, int m, int ck, float2* work,
-                        float2* V, hipStream_t st) {
-    const size_t sm = sizeof(float2) * (N * fplane_stride<N>() + N);
-    hipLaunchKernelGGL(k_fno_yz_fwd_t<N>, dim3(N, F), dim3(256), sm, st, in, work, tw);
-    const int ncol = 2 * m * m;
-    hipLaunchKernelGGL(k_fno_x_gather<N>, dim3((ncol + KC - 1) / KC, F), dim3(256), 0, st, work,
-                       tw, m, ck, V);
+  using Ge = FnoGeo<N>;
+  static size_t fwd_lds(int m) { return sizeof(float2) * ((size_t)Ge::G * N * Ge::S + (size_t)Ge::G * m * (N + 1) + N); }
+  static hipError_t fwd(const float* in, int F, const float2* tw, int m, int ck, float2* P, float2* V,
+                        hipStream_t st) {
+    // groups a block walks: four, so that loads overlap the transforms, but
+    // no fewer than about 1024 blocks (four per CU)
+    const unsigned np = (unsigned)F * N, groups = (np + Ge::G - 1) / Ge::G;
+    const int per = (int)std::min(4u, std::max(1u, groups / 1024));
+    const dim3 g((groups + per - 1) / per);
+    if (m == 8)
+      hipLaunchKernelGGL((k_fno_plane_fwd<N, 8>), g, dim3(256), fwd_lds(m), st, in, np, per, tw, m, P);
+    else
+      hipLaunchKernelGGL((k_fno_plane_fwd<N, 0>), g, dim3(256), fwd_lds(m), st, in, np, per, tw, m, P);
+    hipLaunchKernelGGL(k_fno_x_fwd<N>, dim3((2 * m * m + KC - 1) / KC, F), dim3(256), 0, st, P, tw, m, ck, V);
     return hipGetLastError();
   }
-  static hipError_t inv(const float2* U, int F, const float2* tw, int m, int ck, float2* work,
-                        float* out, int accumulate, hipStream_t st) {
-    const size_t ng = (size_t)N * N * N;
-    hipError_t e = hipMemsetAsync(work, 0, sizeof(float2) * ng * F, st);
-    if (e != hipSuccess) return e;
-    const int ncol = 2 * m * m;
-    hipLaunchKernelGGL(k_fno_x_scatter<N>, dim3((ncol + KC - 1) / KC, F), dim3(256), 0, st, U, tw,
-                       m, ck, work);
-    const size_t sm = sizeof(float2) * (N * fplane_stride<N>() + N);
-    hipLaunchKernelGGL(k_fno_yz_inv<N>, dim3(N, F), dim3(256), sm, st, work, tw, out, accumulate);
+  static hipError_t x_inv(const float2* U, int F, const float2* tw, int m, int ck, float2* P, hipStream_t st) {
+    hipLaunchKernelGGL(k_fno_x_inv<N>, dim3((2 * m * m + KC - 1) / KC, F), dim3(256), 0, st, U, tw, m, ck, P);
     return hipGetLastError();
   }
-  static void configure() {
-    const int sm = (int)(sizeof(float2) * (N * fplane_stride<N>() + N));
-    (void)hipFuncSetAttribute((const void*)k_fno_yz_fwd_t<N>, hipFuncAttributeMaxDynamicSharedMemorySize, sm);
-    (void)hipFuncSetAttribute((const void*)k_fno_yz_inv<N>, hipFuncAttributeMaxDynamicSharedMemorySize, sm);
+  static size_t layer_lds(int T, int m, int nj) {
+    const int ks = m <= 8 ? 4 : (2 * m + 3) / 4;
+    return sizeof(float) * (size_t)Ge::N1 * nj * 16 * T * (4 * ks + 4) + sizeof(float2) * N;
+  }
+  template <int T>
+  static hipError_t layer_t(const FnoLayerArgs& a, hipStream_t st) {
+    // 16 rows a block while three blocks fit on a CU, else fewer (one value
+    // of j2 fits for every allowed width and mode count); fewer too where 16
+    // would leave under four blocks per CU (64^3, batch 3: 68.5 us with 8
+    // rows, 70.7 with 16)
+    int nj = 16 / Ge::N1;
+    while (nj > 1 && (layer_lds(T, a.m, nj) > 52 * 1024 || N * (Ge::N2 / nj) * a.B < 1024)) nj /= 2;
+    const size_t lds = layer_lds(T, a.m, nj);
+    const dim3 g(N * (Ge::N2 / nj), a.B);
+    const void* k = a.m <= 8 ? (const void*)k_fno_layer<N, T, 4> : (const void*)k_fno_layer<N, T, 0>;
+    if (lds > 64 * 1024) {
+      const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+    }
+    if (a.m <= 8)
+      hipLaunchKernelGGL((k_fno_layer<N, T, 4>), g, dim3(256), lds, st, a.in, a.M, a.trans, a.bias, a.W, a.P, a.m, a.tw,
+                         nj, a.act, a.zout, a.zg, a.out);
+    else
+      hipLaunchKernelGGL((k_fno_layer<N, T, 0>), g, dim3(256), lds, st, a.in, a.M, a.trans, a.bias, a.W, a.P, a.m, a.tw,
+                         nj, a.act, a.zout, a.zg, a.out);
+    return hipGetLastError();
+  }
+  static hipError_t layer(const FnoLayerArgs& a, hipStream_t st) {
+    switch ((a.W + 15) / 16) {
+      case 1: return layer_t<1>(a, st);
+      case 2: return layer_t<2>(a, st);
+      case 3: return layer_t<3>(a, st);
+      case 4: return layer_t<4>(a, st);
+      default: return hipErrorInvalidValue;
+    }
   }
 };
 
@@ -756,22 +925,14 @@ bool fno_grid_supported(int n) { return n == 16 || n == 32 || n == 64; }
     default: return hipErrorInvalidValue;     \
   }
 
-hipError_t fno_fft_fwd(int n, const float* in, int F, const float2* tw, int m, int ck, float2* work,
+hipError_t fno_fft_fwd(int n, const float* in, int F, const float2* tw, int m, int ck, float2* P,
                        float2* V, hipStream_t st) {
-  FNO_DISPATCH(n, fwd(in, F, tw, m, ck, work, V, st));
+  FNO_DISPATCH(n, fwd(in, F, tw, m, ck, P, V, st));
 }
-hipError_t fno_fft_inv(int n, const float2* U, int F, const float2* tw, int m, int ck, float2* work,
-                       float* out, int accumulate, hipStream_t st) {
-  FNO_DISPATCH(n, inv(U, F, tw, m, ck, work, out, accumulate, st));
+hipError_t fno_x_inv(int n, const float2* U, int F, const float2* tw, int m, int ck, float2* P, hipStream_t st) {
+  FNO_DISPATCH(n, x_inv(U, F, tw, m, ck, P, st));
 }
-void fno_configure(int n) {
-  switch (n) {
-    case 16: FnoLaunch<16>::configure(); break;
-    case 32: FnoLaunch<32>::configure(); break;
-    case 64: FnoLaunch<64>::configure(); break;
-    default: break;
-  }
-}
+hipError_t fno_layer(int n, const FnoLayerArgs& a, hipStream_t st) { FNO_DISPATCH(n, layer(a, st)); }
 
 static inline unsigned nb(size_t n) { return (unsigned)((n + 255) / 256); }
 
@@ -806,31 +967,15 @@ hipError_t fno_spec_mix_bwd(const float2* V, const float2* GU, const float2* R, 
   return hipGetLastError();
 }
 hipError_t fno_pointwise(const float* in, int Cin, const float* Wm, const float* bias, int Cout,
-                         const float* add, int B, size_t ng, int act, float* zout, float* out,
-                         hipStream_t st) {
+                         int B, size_t ng, float* out, hipStream_t st) {
   if (Cin > PW_MAXC || Cout > PW_MAXC) return hipErrorInvalidValue;
   const dim3 g(nb(ng), B);
   if (Cin == 3 && Cout == 32)
-    hipLaunchKernelGGL((k_pointwise<3, 32>), g, dim3(256), 0, st, in, Cin, Wm, bias, Cout, add, ng, act, zout, out);
-  else if (Cin == 32 && Cout == 32)
-    hipLaunchKernelGGL((k_pointwise<32, 32>), g, dim3(256), 0, st, in, Cin, Wm, bias, Cout, add, ng, act, zout, out);
+    hipLaunchKernelGGL((k_pointwise<3, 32>), g, dim3(256), 0, st, in, Cin, Wm, bias, Cout, ng, out);
   else if (Cin == 32 && Cout == 1)
-    hipLaunchKernelGGL((k_pointwise<32, 1>), g, dim3(256), 0, st, in, Cin, Wm, bias, Cout, add, ng, act, zout, out);
+    hipLaunchKernelGGL((k_pointwise<32, 1>), g, dim3(256), 0, st, in, Cin, Wm, bias, Cout, ng, out);
   else
-    hipLaunchKernelGGL((k_pointwise<0, 0>), g, dim3(256), 0, st, in, Cin, Wm, bias, Cout, add, ng, act, zout, out);
-  return hipGetLastError();
-}
-hipError_t fno_pointwise_bwd(const float* gz, int Cout, const float* Wm, int Cin, int B, size_t ng,
-                             float* gin, hipStream_t st) {
-  if (Cin > PW_MAXC || Cout > PW_MAXC) return hipErrorInvalidValue;
-  if (Cout == 32)
-    hipLaunchKernelGGL((k_pointwise_bwd<32>), dim3(nb(ng), B), dim3(256), 0, st, gz, Cout, Wm, Cin, ng, gin);
-  else
-    hipLaunchKernelGGL((k_pointwise_bwd<0>), dim3(nb(ng), B), dim3(256), 0, st, gz, Cout, Wm, Cin, ng, gin);
-  return hipGetLastError();
-}
-hipError_t fno_gelu_bwd(float* gh, const float* z, size_t n, hipStream_t st) {
-  hipLaunchKernelGGL(k_gelu_bwd, dim3(nb(n)), dim3(256), 0, st, gh, z, n);
+    hipLaunchKernelGGL((k_pointwise<0, 0>), g, dim3(256), 0, st, in, Cin, Wm, bias, Cout, ng, out);
   return hipGetLastError();
 }
 // points per wave: about 2048 waves (two per SIMD), 64 to 1024 points each

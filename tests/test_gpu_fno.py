@@ -229,3 +229,35 @@ def test_outer_products_channel_tiles(n, cin, W, B):
         e = np.linalg.norm(gd[k] - g_o[k]) / np.linalg.norm(g_o[k])
         say(f"outer n={n} cin={cin} W={W} B={B} {k}: {e:.1e}")
         assert e < 2e-5, k
+
+
+@pytest.mark.parametrize("n,W,m,L,B", [(16, 5, 1, 2, 2), (16, 17, 8, 2, 3), (16, 64, 3, 2, 1), (32, 8, 16, 2, 1),
+                                       (32, 33, 9, 1, 2), (64, 32, 8, 2, 1), (64, 3, 32, 2, 1), (64, 49, 5, 1, 1)])
+def test_truncated_transforms_and_layers(n, W, m, L, B):
+    """Forward output, loss and every gradient at widths around the 16-channel
+    tiles and mode counts on both sides of the register path (m <= 8), up to
+    all modes (2 m = n), against the oracle.  FP32: eps 6e-8 times the root of
+    the few hundred terms a value sums; a factor 20 of margin."""
+    import torch
+    from paper_2205_06690_amd import bse
+    cin = 2
+    rng = np.random.default_rng(n + W + m)
+    net = bse.Fno(n, cin=cin, width=W, modes=m, layers=L, max_batch=B, bf16_weights=False, seed=6)
+    p = net.get_params()
+    p = p + (0.3 / W) * rng.standard_normal(p.size).astype(np.float32)
+    net.set_params(p)
+    x = rng.standard_normal((B, cin, n, n, n)).astype(np.float32)
+    t = rng.standard_normal((B, n, n, n)).astype(np.float32)
+    xd, td = torch.from_numpy(x).cuda(), torch.from_numpy(t).cuda()
+    yd = torch.empty((B, n, n, n), dtype=torch.float32, device="cuda")
+    net.forward(B, xd.data_ptr(), yd.data_ptr())
+    loss, g = net.loss_grad(B, xd.data_ptr(), td.data_ptr())
+    d = flat_to_dict(net.get_params(compute=True), cin, W, m, L)
+    y_o, _ = ofno.forward(d, x.astype(np.float64), n, m, L)
+    loss_o, g_o = ofno.loss_and_grad(d, x.astype(np.float64), t.astype(np.float64), n, m, L)
+    ey = np.linalg.norm(yd.cpu().numpy() - y_o) / np.linalg.norm(y_o)
+    gd = flat_to_dict(g, cin, W, m, L)
+    eg = {k: float(np.linalg.norm(gd[k] - g_o[k]) / np.linalg.norm(g_o[k])) for k in g_o}
+    say(f"layers n={n} W={W} m={m}: y {ey:.1e}, loss {abs(loss / loss_o - 1):.1e}, grads {max(eg.values()):.1e}")
+    assert ey < 2e-5 and abs(loss / loss_o - 1) < 2e-5
+    assert max(eg.values()) < 2e-5, eg
