@@ -19,6 +19,7 @@
 #include "prop_kernels.h"
 #include "clean_mfma.h"
 #include "clean_f64.h"
+#include "cheb_f64.h"
 #include "contract_mfma.h"
 #include "host_math.h"
 
@@ -201,6 +202,7 @@ struct bse_system {
   hipStream_t own_stream = nullptr;
   // surrogate descriptors and buffers
   DBuf n0dens, vdev, fx, fy, fscale, fdots, fwpol;
+  DBuf ch_ws, ch_dens;   // Chebyshev spectrum and exciton states
   DBuf mx_f, mx_tf, mx_out, mx_rho, mx_dv, mx_c, mx_part, mx_eps;  // matrix-free A f
   int mx_eps_v0 = -1, mx_eps_n = 0;   // valence window whose eps mx_eps holds
   DBuf bnd_n, bnd_v, bnd_part;   // boundary potential: density, v_H, block sums
@@ -1034,38 +1036,129 @@ void chebyshev_mixed(bse_system* s, int n_mom, double e_min, double e_max, int n
 }
 
 // The Chebyshev interval: the caller's [e_min, e_max] if e_min < e_max,
-// otherwise the Gershgorin interval of the device copy of A
-void cheb_interval(bse_system* s, int n, double* e_min, double* e_max, const char* who) {
+// otherwise the Gershgorin interval of the device copy of A (lohi: 2n, mm: 2
+// doubles of device scratch)
+void cheb_interval(bse_system* s, int n, double* e_min, double* e_max, double* lohi, double* mm, const char* who) {
   if (*e_min < *e_max) return;
   hipStream_t st = s->stream;
-  DBuf lohi;
-  lohi.alloc(sizeof(double) * 2 * (size_t)n);
-  HIPC(launch_gershgorin(s->A_d.as<double>(), n, lohi.as<double>(), st));
-  std::vector<double> h(2 * (size_t)n);
-  HIPC(hipMemcpyAsync(h.data(), lohi.p, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st));
+  double h[2];
+  HIPC(launch_gershgorin(s->A_d.as<double>(), n, lohi, st));
+  HIPC(launch_interval(lohi, n, mm, st));
+  HIPC(hipMemcpyAsync(h, mm, sizeof(h), hipMemcpyDeviceToHost, st));
   HIPC(hipStreamSynchronize(st));
-  *e_min = *std::min_element(h.begin(), h.begin() + n);
-  *e_max = *std::max_element(h.begin() + n, h.end());
+  *e_min = h[0];
+  *e_max = h[1];
   if (!(*e_min < *e_max)) fail(BSE_ERR_ARG, std::string(who) + ": degenerate interval; pass bounds");
 }
 
-// electron-hole dipoles of the last bse_build_A as three start vectors
-// [3][n] on the device (f0_d holds them as [n][3])
-void cheb_start(bse_system* s, int n, double* dst) {
-  hipStream_t st = s->stream;
-  std::vector<double> f0(3 * (size_t)n), f0t(3 * (size_t)n);
-  HIPC(hipMemcpyAsync(f0.data(), s->f0_d.p, sizeof(double) * f0.size(), hipMemcpyDeviceToHost, st));
-  HIPC(hipStreamSynchronize(st));
-  for (int i = 0; i < n; ++i)
-    for (int p = 0; p < 3; ++p) f0t[(size_t)p * n + i] = f0[(size_t)i * 3 + p];
-  HIPC(hipMemcpyAsync(dst, f0t.data(), sizeof(double) * f0t.size(), hipMemcpyHostToDevice, st));
-  HIPC(hipStreamSynchronize(st));
+size_t round32(size_t x) { return (x + 31) / 32 * 32; }
+
+// The recursion with A resident on the chip (cheb_f64.hip) from the vectors
+// fv = f^0 [3][n]: `total` steps in segments, `use` taking each one (fc =
+// f^{k0}, out, k0, steps).  seg holds cheb_seg_doubles(n, total) doubles; err
+// (device) is 0 at the end unless the workgroups never met.
+size_t cheb_seg_doubles(int n, int total) { return 2 * round32((size_t)std::min(total, CHEB_SEG) * 3 * n); }
+void cheb_res_run(bse_system* s, int n, const double* fv, double* seg, int* err, int total, double a, double b,
+                  const std::function<void(const double*, const double*, int, int)>& use) {
+  const size_t half = cheb_seg_doubles(n, total) / 2;
+  HIPC(launch_fill_zero(err, sizeof(int), s->stream));
+  const double *fc = fv, *fp = nullptr;
+  for (int k0 = 0, w = 0; k0 < total; w ^= 1) {
+    const int steps = std::min(CHEB_SEG, total - k0);
+    double* out = seg + w * half;
+    HIPC(launch_cheb_res(s->A_d.as<double>(), n, fc, fp, out, steps, k0, a, b, err, s->stream));
+    use(fc, out, k0, steps);
+    fp = steps > 1 ? out + (size_t)(steps - 2) * 3 * n : fc;
+    fc = out + (size_t)(steps - 1) * 3 * n;
+    k0 += steps;
+  }
+}
+
+// Device buffers of one Chebyshev spectrum, carved from `base` (null: sizes
+// only), each part rounded up to 256 bytes; returns the doubles needed.  res:
+// the resident recursion's, else those of a launch per step.
+struct ChebBufs {
+  double *fv, *seg, *part, *mu, *D, *wd, *sd, *lohi, *mm;
+  int* err;
+};
+size_t cheb_carve(double* base, int n, int n_mom, int n_w, bool res, ChebBufs* o) {
+  const size_t K = (size_t)n_mom / 2;
+  size_t used = 0;
+  auto take = [&](size_t x) {
+    double* p = base ? base + used : nullptr;
+    used += round32(x);
+    return p;
+  };
+  ChebBufs c{};
+  c.fv = take((res ? 3 : 9) * (size_t)n);
+  c.part = take(6 * K * (res ? 1 : (size_t)cheb_blocks(n)));
+  c.seg = res ? take(cheb_seg_doubles(n, (int)K)) : nullptr;
+  c.mu = take(3 * (size_t)n_mom);
+  c.D = take(6 * (size_t)n_mom);
+  c.wd = take((size_t)n_w);
+  c.sd = take((size_t)n_w);
+  c.lohi = take(2 * (size_t)n);
+  c.mm = take(2);
+  c.err = res ? reinterpret_cast<int*>(take(1)) : nullptr;
+  if (o) *o = c;
+  return used;
+}
+size_t cheb_noalloc_doubles(int n, int n_mom, int n_w) { return cheb_carve(nullptr, n, n_mom, n_w, false, nullptr); }
+
+// The resident recursion needs A on the chip (n <= 1024) and enough steps to
+// pay for loading it (16: n = 200 then takes 4 steps' worth of launches), and
+// is taken only where its buffers fit in the fixed scratch, so that the
+// allocating and the allocation-free entry points always compute alike.
+bool cheb_resident(int n, int n_mom, int n_w) {
+  return n <= cheb_res_max() && n_mom / 2 >= 16 &&
+         cheb_carve(nullptr, n, n_mom, n_w, true, nullptr) * sizeof(double) <= NOALLOC_SCRATCH_BYTES;
 }
 
 // Chebyshev absorption (Eqs. 7-8) on the device copy of A: the residues of
 // the three dipole start vectors by the recursion in A~ = (A - b)/a, then the
 // broadened delta through its Chebyshev coefficients (Gauss-Chebyshev
-// quadrature on M = 2 n_mom nodes, summed at the nodes).
+// quadrature on M = 2 n_mom nodes, summed at the nodes).  buffers(res) gives
+// the device buffers.
+void cheb_spectrum(bse_system* s, int n, int n_mom, double e_min, double e_max, int n_w, const double* w_grid,
+                   double sig, double* sigma, double* residues, double* bounds, const char* who,
+                   const std::function<double*(bool)>& buffers) {
+  hipStream_t st = s->stream;
+  const double* A = s->A_d.as<double>();
+  const int K = n_mom / 2, nblk = cheb_blocks(n), M = 2 * n_mom;
+  bool res = cheb_resident(n, n_mom, n_w);
+  for (;; res = false) {
+    ChebBufs c;
+    cheb_carve(buffers(res), n, n_mom, n_w, res, &c);
+    cheb_interval(s, n, &e_min, &e_max, c.lohi, c.mm, who);
+    const double b = 0.5 * (e_max + e_min), a = 0.5 * (e_max - e_min) * 1.01;
+    if (n_w > 0) HIPC(hipMemcpyAsync(c.wd, w_grid, sizeof(double) * n_w, hipMemcpyHostToDevice, st));
+    HIPC(launch_cheb_start(s->f0_d.as<double>(), n, c.fv, st));
+    if (res) {
+      cheb_res_run(s, n, c.fv, c.seg, c.err, K, a, b, [&](const double* fc, const double* out, int k0, int steps) {
+        HIPC(launch_cheb_dots(fc, out, n, k0, steps, c.part, st));
+      });
+    } else {
+      for (int k = 0; k < K; ++k) {
+        const double* fc = c.fv + (size_t)(k % 3) * 3 * n;
+        const double* fp = c.fv + (size_t)((k + 2) % 3) * 3 * n;
+        double* fn = c.fv + (size_t)((k + 1) % 3) * 3 * n;
+        HIPC(launch_cheb_step(A, n, fc, fp, fn, a, b, k == 0 ? 1 : 0, c.part + (size_t)k * nblk * 6, st));
+      }
+    }
+    HIPC(launch_cheb_spectrum(c.part, K, res ? 1 : nblk, c.mu, M, c.D, a, b, c.wd, n_w, sig, c.sd, st));
+    if (n_w > 0) HIPC(hipMemcpyAsync(sigma, c.sd, sizeof(double) * n_w, hipMemcpyDeviceToHost, st));
+    if (residues) HIPC(hipMemcpyAsync(residues, c.mu, sizeof(double) * 3 * (size_t)n_mom, hipMemcpyDeviceToHost, st));
+    int err = 0;
+    if (res) HIPC(hipMemcpyAsync(&err, c.err, sizeof(int), hipMemcpyDeviceToHost, st));
+    HIPC(hipStreamSynchronize(st));
+    if (!err) break;
+  }
+  if (bounds) {
+    bounds[0] = e_min;
+    bounds[1] = e_max;
+  }
+}
+
 void chebyshev_spectrum(bse_system* s, int n_mom, double e_min, double e_max, int n_w,
                         const double* w_grid, double sig, double* sigma, double* residues,
                         double* bounds) {
@@ -1075,54 +1168,15 @@ void chebyshev_spectrum(bse_system* s, int n_mom, double e_min, double e_max, in
   if (n_mom < 2 || n_mom % 2 != 0 || n_w < 0 || (n_w > 0 && (!w_grid || !sigma || !(sig > 0))) ||
       (n_w == 0 && !residues))
     fail(BSE_ERR_ARG, "bse_chebyshev_spectrum: bad arguments");
-  hipStream_t st = s->stream;
-  const double* A = s->A_d.as<double>();
-  cheb_interval(s, n, &e_min, &e_max, "bse_chebyshev_spectrum");
-  const double b = 0.5 * (e_max + e_min), a = 0.5 * (e_max - e_min) * 1.01;
-  const int K = n_mom / 2, nblk = cheb_blocks(n), M = 2 * n_mom;
-  DBuf fv, part, mu, D, wd, sd;
-  fv.alloc(sizeof(double) * 9 * (size_t)n);
-  part.alloc(sizeof(double) * 6 * (size_t)K * nblk);
-  mu.alloc(sizeof(double) * 3 * (size_t)n_mom);
-  D.alloc(sizeof(double) * 3 * (size_t)M);
-  if (n_w > 0) {
-    wd.alloc(sizeof(double) * n_w);
-    sd.alloc(sizeof(double) * n_w);
-    HIPC(hipMemcpyAsync(wd.p, w_grid, sizeof(double) * n_w, hipMemcpyHostToDevice, st));
-  }
-  // f^0 = dipoles, [3][n]
-  double* buf = fv.as<double>();
-  cheb_start(s, n, buf);
-  for (int k = 0; k < K; ++k) {
-    const double* fc = buf + (size_t)(k % 3) * 3 * n;
-    const double* fp = buf + (size_t)((k + 2) % 3) * 3 * n;
-    double* fn = buf + (size_t)((k + 1) % 3) * 3 * n;
-    HIPC(launch_cheb_step(A, n, fc, fp, fn, a, b, k == 0 ? 1 : 0,
-                          part.as<double>() + (size_t)k * nblk * 6, st));
-  }
-  HIPC(launch_cheb_spectrum(part.as<double>(), K, nblk, mu.as<double>(), M, D.as<double>(), a, b,
-                            wd.as<double>(), n_w, sig, sd.as<double>(), st));
-  if (n_w > 0) HIPC(hipMemcpyAsync(sigma, sd.p, sizeof(double) * n_w, hipMemcpyDeviceToHost, st));
-  if (residues)
-    HIPC(hipMemcpyAsync(residues, mu.p, sizeof(double) * 3 * (size_t)n_mom, hipMemcpyDeviceToHost, st));
-  HIPC(hipStreamSynchronize(st));
-  if (bounds) {
-    bounds[0] = e_min;
-    bounds[1] = e_max;
-  }
+  cheb_spectrum(s, n, n_mom, e_min, e_max, n_w, w_grid, sig, sigma, residues, bounds, "bse_chebyshev_spectrum",
+                [&](bool res) {
+                  s->ch_ws.alloc(sizeof(double) * cheb_carve(nullptr, n, n_mom, n_w, res, nullptr));
+                  return s->ch_ws.as<double>();
+                });
 }
 
 // chebyshev_spectrum without allocation: the same launches and arithmetic,
-// with every device buffer carved from this device's `scratch` array and no
-// host staging (start vectors and the Gershgorin interval on the device).
-// Sizes in doubles, each part rounded up to 256 bytes.
-size_t cheb_noalloc_doubles(int n, int n_mom, int n_w) {
-  auto r = [](size_t x) { return (x + 31) / 32 * 32; };
-  const size_t K = (size_t)n_mom / 2, nblk = (size_t)cheb_blocks(n), M = 2 * (size_t)n_mom;
-  return r(9 * (size_t)n) + r(6 * K * nblk) + r(3 * (size_t)n_mom) + r(3 * M) + 2 * r((size_t)n_w) +
-         r(2 * (size_t)n) + r(2);
-}
-
+// with every device buffer carved from this device's `scratch` array.
 void chebyshev_spectrum_noalloc(bse_system* s, int n_mom, double e_min, double e_max, int n_w,
                                 const double* w_grid, double sig, double* sigma, double* residues,
                                 double* bounds) {
@@ -1138,45 +1192,8 @@ void chebyshev_spectrum_noalloc(bse_system* s, int n_mom, double e_min, double e
   double* base = scratch_dev(s->cfg.device);
   if (!base) fail(BSE_ERR_STATE, "bse_chebyshev_spectrum_noalloc: no scratch on this device");
   HIPC(hipSetDevice(s->cfg.device));
-  hipStream_t st = s->stream;
-  auto r = [](size_t x) { return (x + 31) / 32 * 32; };
-  const int K = n_mom / 2, nblk = cheb_blocks(n), M = 2 * n_mom;
-  double* fv = base;
-  double* part = fv + r(9 * (size_t)n);
-  double* mu = part + r(6 * (size_t)K * nblk);
-  double* D = mu + r(3 * (size_t)n_mom);
-  double* wd = D + r(3 * (size_t)M);
-  double* sd = wd + r((size_t)n_w);
-  double* lohi = sd + r((size_t)n_w);
-  double* mm = lohi + r(2 * (size_t)n);
-  const double* A = s->A_d.as<double>();
-  if (!(e_min < e_max)) {
-    double h[2];
-    HIPC(launch_gershgorin(A, n, lohi, st));
-    HIPC(launch_interval(lohi, n, mm, st));
-    HIPC(hipMemcpyAsync(h, mm, sizeof(h), hipMemcpyDeviceToHost, st));
-    HIPC(hipStreamSynchronize(st));
-    e_min = h[0];
-    e_max = h[1];
-    if (!(e_min < e_max)) fail(BSE_ERR_ARG, "bse_chebyshev_spectrum_noalloc: degenerate interval; pass bounds");
-  }
-  const double b = 0.5 * (e_max + e_min), a = 0.5 * (e_max - e_min) * 1.01;
-  if (n_w > 0) HIPC(hipMemcpyAsync(wd, w_grid, sizeof(double) * n_w, hipMemcpyHostToDevice, st));
-  HIPC(launch_cheb_start(s->f0_d.as<double>(), n, fv, st));
-  for (int k = 0; k < K; ++k) {
-    const double* fc = fv + (size_t)(k % 3) * 3 * n;
-    const double* fp = fv + (size_t)((k + 2) % 3) * 3 * n;
-    double* fn = fv + (size_t)((k + 1) % 3) * 3 * n;
-    HIPC(launch_cheb_step(A, n, fc, fp, fn, a, b, k == 0 ? 1 : 0, part + (size_t)k * nblk * 6, st));
-  }
-  HIPC(launch_cheb_spectrum(part, K, nblk, mu, M, D, a, b, wd, n_w, sig, sd, st));
-  if (n_w > 0) HIPC(hipMemcpyAsync(sigma, sd, sizeof(double) * n_w, hipMemcpyDeviceToHost, st));
-  if (residues) HIPC(hipMemcpyAsync(residues, mu, sizeof(double) * 3 * (size_t)n_mom, hipMemcpyDeviceToHost, st));
-  HIPC(hipStreamSynchronize(st));
-  if (bounds) {
-    bounds[0] = e_min;
-    bounds[1] = e_max;
-  }
+  cheb_spectrum(s, n, n_mom, e_min, e_max, n_w, w_grid, sig, sigma, residues, bounds,
+                "bse_chebyshev_spectrum_noalloc", [&](bool) { return base; });
 }
 
 // Frequency-resolved exciton states (Eq. 8) on the device copy of A: the full
@@ -1192,41 +1209,52 @@ void exciton_states(bse_system* s, int n_mom, double e_min, double e_max, int n_
   const int n = s->a_no * s->a_nc;
   hipStream_t st = s->stream;
   const double* A = s->A_d.as<double>();
-  cheb_interval(s, n, &e_min, &e_max, "bse_exciton_states");
-  const double b = 0.5 * (e_max + e_min), a = 0.5 * (e_max - e_min) * 1.01;
-  auto* t = s->timer.begin("exciton_states");
-  DBuf fv, g, F, wd;
-  fv.alloc(sizeof(double) * 9 * (size_t)n);
-  g.alloc(sizeof(double) * (size_t)n_w * n_mom);
-  F.alloc(sizeof(double) * 3 * (size_t)n_w * n);
-  wd.alloc(sizeof(double) * n_w);
-  HIPC(hipMemcpyAsync(wd.p, w_list, sizeof(double) * n_w, hipMemcpyHostToDevice, st));
-  HIPC(launch_cheb_coef(wd.as<double>(), n_w, n_mom, 2 * n_mom, a, b, sig, g.as<double>(), st));
-  double* buf = fv.as<double>();
-  cheb_start(s, n, buf);
-  HIPC(launch_cheb_acc_init(buf, n, g.as<double>(), n_mom, n_w, F.as<double>(), st));
-  // buffer k % 3 holds f^k
-  for (int m = 0; m + 1 < n_mom; ++m) {
-    const double* fc = buf + (size_t)(m % 3) * 3 * n;
-    const double* fp = buf + (size_t)((m + 2) % 3) * 3 * n;
-    double* fn = buf + (size_t)((m + 1) % 3) * 3 * n;
-    HIPC(launch_cheb_step_acc(A, n, fc, fp, fn, a, b, m == 0 ? 1 : 0, g.as<double>(), n_mom, m + 1, n_w,
-                              F.as<double>(), st));
-  }
   const size_t ng = s->ng;
-  DBuf dens;
-  if (dens_out) {
-    const int v0 = s->cfg.n_occ - s->a_no, c0 = s->cfg.n_occ;
-    dens.alloc(sizeof(double) * 3 * (size_t)n_w * ng);
-    HIPC(launch_exciton_density(s->phi64.as<double>(), v0, c0, s->a_no, s->a_nc, ng, F.as<double>(),
-                                3 * n_w, dens.as<double>(), st));
+  bool res = n <= cheb_res_max() && n_mom > 16;
+  for (;; res = false) {
+    const size_t nf = round32((res ? 3 : 9) * (size_t)n), ngm = round32((size_t)n_w * n_mom);
+    const size_t nF = round32(3 * (size_t)n_w * n), nseg = res ? cheb_seg_doubles(n, n_mom - 1) : 0;
+    s->ch_ws.alloc(sizeof(double) * (nf + ngm + nF + nseg + round32(2 * (size_t)n) + 96));
+    double* buf = s->ch_ws.as<double>();
+    double *g = buf + nf, *F = g + ngm, *seg = F + nF, *lohi = seg + nseg;
+    double *mm = lohi + round32(2 * (size_t)n), *wd = mm + 32;
+    int* err = reinterpret_cast<int*>(mm + 64);
+    cheb_interval(s, n, &e_min, &e_max, lohi, mm, "bse_exciton_states");
+    const double b = 0.5 * (e_max + e_min), a = 0.5 * (e_max - e_min) * 1.01;
+    auto* t = s->timer.begin("exciton_states");
+    HIPC(hipMemcpyAsync(wd, w_list, sizeof(double) * n_w, hipMemcpyHostToDevice, st));
+    HIPC(launch_cheb_coef(wd, n_w, n_mom, 2 * n_mom, a, b, sig, g, st));
+    HIPC(launch_cheb_start(s->f0_d.as<double>(), n, buf, st));
+    if (res) {
+      cheb_res_run(s, n, buf, seg, err, n_mom - 1, a, b, [&](const double* fc, const double* out, int k0, int steps) {
+        HIPC(launch_cheb_states(fc, out, n, k0, steps, g, n_mom, n_w, F, st));
+      });
+    } else {
+      HIPC(launch_cheb_acc_init(buf, n, g, n_mom, n_w, F, st));
+      // buffer k % 3 holds f^k
+      for (int m = 0; m + 1 < n_mom; ++m) {
+        const double* fc = buf + (size_t)(m % 3) * 3 * n;
+        const double* fp = buf + (size_t)((m + 2) % 3) * 3 * n;
+        double* fn = buf + (size_t)((m + 1) % 3) * 3 * n;
+        HIPC(launch_cheb_step_acc(A, n, fc, fp, fn, a, b, m == 0 ? 1 : 0, g, n_mom, m + 1, n_w, F, st));
+      }
+    }
+    if (dens_out) {
+      const int v0 = s->cfg.n_occ - s->a_no, c0 = s->cfg.n_occ;
+      s->ch_dens.alloc(sizeof(double) * 3 * (size_t)n_w * ng);
+      HIPC(launch_exciton_density(s->phi64.as<double>(), v0, c0, s->a_no, s->a_nc, ng, F, 3 * n_w,
+                                  s->ch_dens.as<double>(), st));
+    }
+    s->timer.end(t);
+    HIPC(hipMemcpyAsync(f_out, F, sizeof(double) * 3 * (size_t)n_w * n, hipMemcpyDeviceToHost, st));
+    if (dens_out)
+      HIPC(hipMemcpyAsync(dens_out, s->ch_dens.p, sizeof(double) * 3 * (size_t)n_w * ng, hipMemcpyDeviceToHost,
+                          st));
+    int e = 0;
+    if (res) HIPC(hipMemcpyAsync(&e, err, sizeof(int), hipMemcpyDeviceToHost, st));
+    HIPC(hipStreamSynchronize(st));
+    if (!e) break;
   }
-  s->timer.end(t);
-  HIPC(hipMemcpyAsync(f_out, F.p, sizeof(double) * 3 * (size_t)n_w * n, hipMemcpyDeviceToHost, st));
-  if (dens_out)
-    HIPC(hipMemcpyAsync(dens_out, dens.p, sizeof(double) * 3 * (size_t)n_w * ng, hipMemcpyDeviceToHost,
-                        st));
-  HIPC(hipStreamSynchronize(st));
   if (bounds) {
     bounds[0] = e_min;
     bounds[1] = e_max;

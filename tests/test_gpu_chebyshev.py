@@ -1,0 +1,63 @@
+"""The Chebyshev recursion with A on the chip, at sizes around every change
+of its layout (one workgroup per polarisation up to 256 rows, groups of
+workgroups to 1024, a launch per step beyond and for few moments) and step
+counts that end inside, at and past a segment, against the oracle's
+recursion on the same A."""
+import numpy as np
+import pytest
+
+from gpu_util import say
+
+pytestmark = pytest.mark.gpu
+
+
+def _system(n_o, n_c, seed):
+    """A 16^3 system on random orthonormal orbitals: any A will do."""
+    from paper_2205_06690_amd import bse
+    n, h = 16, 0.6
+    rng = np.random.default_rng(seed)
+    q, _ = np.linalg.qr(rng.standard_normal((n ** 3, n_o + n_c)))
+    phi = np.ascontiguousarray(q.T) / np.sqrt(h ** 3)
+    s = bse.System(n, h, np.zeros(n ** 3), n_occ=n_o, n_stoch=2, n_steps=1, clean_every=0, precision=bse.BSE_FP64,
+                   max_batch=600)
+    s.set_orbitals(phi, np.sort(rng.uniform(-1.0, 1.0, n_o + n_c)))
+    A = s.build_a(n_o, n_c)
+    from oracle import bse as obse
+    from oracle.grid import Grid
+    g = phi.reshape(-1, n, n, n)
+    return s, A, obse.dipoles(Grid((n, n, n), h), g[:n_o], g[n_o:]), phi
+
+
+# a residue sums n products of vectors that carry the rounding of the steps
+# before them: eps n_mom^2 / 2 at the worst, 1.3e-10 at 1540 moments; random
+# signs leave far less
+TOL = 1e-10
+
+
+@pytest.mark.parametrize("n_o,n_c,n_mom", [(1, 1, 40), (8, 8, 1026), (5, 13, 32), (8, 16, 30), (3, 43, 1024), (16, 13, 60), (11, 19, 60), (16, 16, 64),
+                                           (1, 257, 1026), (16, 32, 1540), (19, 27, 64), (32, 32, 130), (25, 41, 40)])
+def test_resident_recursion(n_o, n_c, n_mom):
+    from oracle import bse as obse
+    s, A, f0, phi = _system(n_o, n_c, 7 * n_o + n_c)
+    n = n_o * n_c
+    lo, hi = obse.spectral_bounds(A) if n > 1 else (A[0, 0] - 1.0, A[0, 0] + 1.0)
+    a, b = obse.chebyshev_scale(lo, hi)
+    bounds = (lo, hi)
+    wg = np.linspace(lo, hi, 9)[1:-1]
+    sig = 4.0 * (hi - lo) / n_mom
+    R = obse.chebyshev_residues(A, f0, n_mom, a, b).T
+    sg, res, _ = s.chebyshev_spectrum(n_mom, wg, sig, bounds=bounds)
+    e = np.abs(res - R).max() / np.abs(R[:, 0]).max()
+    sg_o = obse.chebyshev_absorption(R.T, wg, a, b, sig)
+    es = np.abs(sg - sg_o).max() / np.abs(sg_o).max()
+    sg_n, res_n, _ = s.chebyshev_spectrum_noalloc(n_mom, wg, sig, bounds=bounds)
+    assert np.array_equal(res_n, res) and np.array_equal(sg_n, sg)
+    F, dn, _ = s.exciton_states(n_mom - 1, wg[:3], sig, bounds=bounds)
+    F_o = obse.chebyshev_states(A, f0, n_mom - 1, a, b, wg[:3], sig)        # [n_w, n, 3]
+    eF = np.abs(F - F_o.transpose(0, 2, 1)).max() / np.abs(F_o).max()
+    dn_o = np.stack([[obse.exciton_density(phi[:n_o].reshape(-1, 16, 16, 16), phi[n_o:].reshape(-1, 16, 16, 16), F_o[q, :, p])
+                      for p in range(3)] for q in range(3)])
+    ed = np.abs(dn - dn_o).max() / np.abs(dn_o).max()
+    say(f"n = {n}, {n_mom} moments: residues {e:.1e}, sigma {es:.1e}, states {eF:.1e}, densities {ed:.1e}")
+    assert max(e, es, eF, ed) < TOL
+    s.close()
