@@ -1214,7 +1214,8 @@ void exciton_states(bse_system* s, int n_mom, double e_min, double e_max, int n_
   for (;; res = false) {
     const size_t nf = round32((res ? 3 : 9) * (size_t)n), ngm = round32((size_t)n_w * n_mom);
     const size_t nF = round32(3 * (size_t)n_w * n), nseg = res ? cheb_seg_doubles(n, n_mom - 1) : 0;
-    s->ch_ws.alloc(sizeof(double) * (nf + ngm + nF + nseg + round32(2 * (size_t)n) + 96));
+    const size_t ncs = cheb_coef_scratch(n_w, 2 * n_mom);
+    s->ch_ws.alloc(sizeof(double) * (nf + ngm + nF + nseg + round32(2 * (size_t)n) + 96 + ncs));
     double* buf = s->ch_ws.as<double>();
     double *g = buf + nf, *F = g + ngm, *seg = F + nF, *lohi = seg + nseg;
     double *mm = lohi + round32(2 * (size_t)n), *wd = mm + 32;
@@ -1223,7 +1224,7 @@ void exciton_states(bse_system* s, int n_mom, double e_min, double e_max, int n_
     const double b = 0.5 * (e_max + e_min), a = 0.5 * (e_max - e_min) * 1.01;
     auto* t = s->timer.begin("exciton_states");
     HIPC(hipMemcpyAsync(wd, w_list, sizeof(double) * n_w, hipMemcpyHostToDevice, st));
-    HIPC(launch_cheb_coef(wd, n_w, n_mom, 2 * n_mom, a, b, sig, g, st));
+    HIPC(launch_cheb_coef(wd, n_w, n_mom, 2 * n_mom, a, b, sig, mm + 96, g, st));
     HIPC(launch_cheb_start(s->f0_d.as<double>(), n, buf, st));
     if (res) {
       cheb_res_run(s, n, buf, seg, err, n_mom - 1, a, b, [&](const double* fc, const double* out, int k0, int steps) {
@@ -1281,7 +1282,7 @@ void exciton_states_mixed(bse_system* s, int n_mom, double e_min, double e_max, 
   hipStream_t st = s->stream;
   const size_t ng = s->ng, len = (size_t)n_o * ng;
   const double b = 0.5 * (e_max + e_min), a = 0.5 * (e_max - e_min) * 1.01;
-  DBuf fv, af, part, g, F, wd, cq, pq, amp, pa, rho;
+  DBuf fv, af, part, g, F, wd, cq, pq, amp, rho, cs;
   fv.alloc(sizeof(double) * 3 * len);               // [3 rotating vectors][n_o][ng]
   af.alloc(sizeof(double) * len);
   part.alloc(sizeof(double) * 6 * (size_t)mixed_cheb_blocks());
@@ -1293,7 +1294,8 @@ void exciton_states_mixed(bse_system* s, int n_mom, double e_min, double e_max, 
   if (n_a > 0) amp.alloc(sizeof(double) * (size_t)n_o * n_a);
   if (dens_out) rho.alloc(sizeof(double) * ng);
   HIPC(hipMemcpyAsync(wd.p, w_list, sizeof(double) * n_w, hipMemcpyHostToDevice, st));
-  HIPC(launch_cheb_coef(wd.as<double>(), n_w, n_mom, 2 * n_mom, a, b, sig, g.as<double>(), st));
+  cs.alloc(sizeof(double) * cheb_coef_scratch(n_w, 2 * n_mom));
+  HIPC(launch_cheb_coef(wd.as<double>(), n_w, n_mom, 2 * n_mom, a, b, sig, cs.as<double>(), g.as<double>(), st));
   double* buf = fv.as<double>();
   auto vec = [&](int k) { return buf + (size_t)(k % 3) * len; };
   const double* phv = s->phi64.as<double>() + (size_t)(S - n_o) * ng;

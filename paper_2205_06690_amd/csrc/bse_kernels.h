@@ -59,7 +59,8 @@ hipError_t launch_mixed_dipole(const double* phv, int n_o, int n, double h, int 
                                hipStream_t st);
 // Chebyshev spectrum (Eqs. 7-8): Gershgorin rows lohi[2][n]; one recursion
 // step on [3][n] vectors with per-block partial residues part[cheb_blocks(n)][6];
-// residues mu[3][2K], node weights D[3][M] and sigma[n_w] from the partials
+// residues mu[3][2K] and sigma[n_w] from the partials (which it sums in
+// place), DE[2 M] taking the node sums and energies
 hipError_t launch_gershgorin(const double* A, int n, double* lohi, hipStream_t st);
 int cheb_blocks(int n);
 // the dipoles f0[n][3] as the three start vectors out[3][n]
@@ -68,15 +69,17 @@ hipError_t launch_cheb_start(const double* f0, int n, double* out, hipStream_t s
 hipError_t launch_interval(const double* lohi, int n, double* mm, hipStream_t st);
 hipError_t launch_cheb_step(const double* A, int n, const double* fc, const double* fp, double* fn,
                             double a, double b, int first, double* part, hipStream_t st);
-hipError_t launch_cheb_spectrum(const double* part, int K, int nblk, double* mu, int M, double* D,
+hipError_t launch_cheb_spectrum(double* part, int K, int nblk, double* mu, int M, double* DE,
                                 double a, double b, const double* w, int n_w, double sig,
                                 double* out, hipStream_t st);
 // frequency-resolved exciton states (Eq. 8): g[n_w][N] Chebyshev coefficients
 // of the broadened delta (Gauss-Chebyshev quadrature on M nodes); F[n_w][3][n]
 // = g[.][0] f0 at the start, then one recursion step per moment adding
 // g[.][m_next] f^{m_next}; exciton densities dens[n_out][ng] of F[n_out][n]
+// (n_w <= 8; scratch holds cheb_coef_scratch(n_w, M) doubles)
+size_t cheb_coef_scratch(int n_w, int M);
 hipError_t launch_cheb_coef(const double* w, int n_w, int N, int M, double a, double b, double sig,
-                            double* g, hipStream_t st);
+                            double* scratch, double* g, hipStream_t st);
 hipError_t launch_cheb_acc_init(const double* f0, int n, const double* g, int N, int n_w, double* F,
                                 hipStream_t st);
 hipError_t launch_cheb_step_acc(const double* A, int n, const double* fc, const double* fp, double* fn,

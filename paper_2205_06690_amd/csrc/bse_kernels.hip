@@ -413,18 +413,25 @@ __global__ void __launch_bounds__(256) k_cheb_step(const double* __restrict__ A,
         red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
 }
 
-// S[k][q] = sum over blocks of part[k][blk][q] (fixed order), then the
-// residues mu[p][m] for m < 2K
+// part[k][0][q] = sum over the blocks of part[k][blk][q]: one wave per (k, q),
+// lanes over the blocks, a fixed shuffle tree
+__global__ void __launch_bounds__(256) k_cheb_part_sum(double* __restrict__ part, int K, int nblk) {
+  const int w = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (w >= 6 * K) return;
+  double* p = part + (size_t)(w / 6) * nblk * 6 + w % 6;
+  double s = 0;
+  for (int i = lane; i < nblk; i += 64) s += p[(size_t)i * 6];
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+  if (lane == 0) p[0] = s;
+}
+
+// the residues mu[p][m], m < 2K, from S[k][q] = part[k][0][q] (rows nblk apart)
 __global__ void k_cheb_moments(const double* __restrict__ part, int K, int nblk,
                                double* __restrict__ mu) {
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
   const int p = blockIdx.y;
   if (m >= 2 * K) return;
-  auto S = [&](int k, int q) {
-    double acc = 0;
-    for (int i = 0; i < nblk; ++i) acc += part[((size_t)k * nblk + i) * 6 + q];
-    return acc;
-  };
+  auto S = [&](int k, int q) { return part[(size_t)k * nblk * 6 + q]; };
   const double mu0 = S(0, p), mu1 = S(0, 3 + p);
   double v;
   if (m == 0) v = mu0;
@@ -434,39 +441,74 @@ __global__ void k_cheb_moments(const double* __restrict__ part, int K, int nblk,
   mu[(size_t)p * 2 * K + m] = v;
 }
 
-// D[p][k] = (1/M) (2 sum_{m<N} mu[p][m] T_m(x_k) - mu[p][0]), x_k = cos(pi (k+1/2)/M),
-// by Clenshaw's recurrence
-__global__ void k_cheb_nodes(const double* __restrict__ mu, int N, int M, double* __restrict__ D) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  const int p = blockIdx.y;
-  if (k >= M) return;
-  const double x = cos(M_PI * (k + 0.5) / M);
-  const double* m = mu + (size_t)p * N;
-  double b1 = 0, b2 = 0;
-  for (int j = N - 1; j >= 1; --j) {
-    const double b0 = m[j] + 2.0 * x * b1 - b2;
-    b2 = b1;
-    b1 = b0;
+// The node sums D_p(k) = (1/M) (2 sum_{m<N} mu[p][m] T_m(x_k) - mu[p][0]), x_k =
+// cos(pi (k+1/2)/M), by Clenshaw's recurrence, the three polarisations' chains
+// side by side: DE[k] = D_0 + D_1 + D_2 and DE[M + k] = a x_k + b, the node's
+// energy.  The residues come from LDS eight at a time: 37 us at N = 976 against
+// 58 us for one chain a thread reading them from global memory.
+constexpr int CN_CH = 512;
+__global__ void __launch_bounds__(64) k_cheb_nodes(const double* __restrict__ mu, int N, int M, double a, double b,
+                                                   double* __restrict__ DE) {
+  __shared__ double sm[3][CN_CH];
+  const int k = blockIdx.x * 64 + threadIdx.x;
+  const double x = cos(M_PI * (k + 0.5) / M), x2 = 2.0 * x;
+  double b1[3] = {0, 0, 0}, b2[3] = {0, 0, 0};
+  for (int hi = N; hi > 0;) {
+    const int lo = (hi - 1) / CN_CH * CN_CH;
+    __syncthreads();
+    for (int e = threadIdx.x; e < 3 * (hi - lo); e += 64) {
+      const int p = e / (hi - lo), j = e % (hi - lo);
+      sm[p][j] = mu[(size_t)p * N + lo + j];
+    }
+    __syncthreads();
+#pragma unroll 8
+    for (int j = hi - 1; j >= max(lo, 1); --j) {
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        const double b0 = x2 * b1[p] + (sm[p][j - lo] - b2[p]);
+        b2[p] = b1[p];
+        b1[p] = b0;
+      }
+    }
+    hi = lo;
   }
-  const double sum = m[0] + x * b1 - b2;   // sum_j mu_j T_j(x)
-  D[(size_t)p * M + k] = (2.0 * sum - m[0]) / M;
+  if (k >= M) return;
+  double d[3];
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    const double m0 = sm[p][0];                       // the last chunk starts at m = 0
+    const double sum = m0 + x * b1[p] - b2[p];        // sum_j mu_j T_j(x)
+    d[p] = (2.0 * sum - m0) / M;
+  }
+  DE[k] = d[0] + d[1] + d[2];
+  DE[M + k] = a * x + b;
 }
 
-// sigma(omega_q) = omega_q sum_p sum_k G(a x_k + b - omega_q) D[p][k]
-__global__ void k_cheb_sigma(const double* __restrict__ D, int M, double a, double b,
-                             const double* __restrict__ w, int n_w, double sig,
-                             double* __restrict__ out) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= n_w) return;
-  const double om = w[q];
-  const double norm = 1.0 / (sig * sqrt(2.0 * M_PI));
+// sum over the 256 threads of a block, in every thread (red: 4 doubles)
+__device__ __forceinline__ double block_sum4(double v, double* red) {
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  const double t = (red[0] + red[1]) + (red[2] + red[3]);
+  __syncthreads();
+  return t;
+}
+
+// sigma(omega_q) = omega_q sum_k G(E_k - omega_q) D(k): a block per frequency
+// (6 us at 600 frequencies and 1952 nodes; one thread per frequency left the
+// chip idle for 693 us)
+__global__ void __launch_bounds__(256) k_cheb_sigma(const double* __restrict__ DE, int M,
+                                                    const double* __restrict__ w, double sig,
+                                                    double* __restrict__ out) {
+  __shared__ double red[4];
+  const double om = w[blockIdx.x];
   double acc = 0;
-  for (int k = 0; k < M; ++k) {
-    const double E = a * cos(M_PI * (k + 0.5) / M) + b;
-    const double z = (E - om) / sig;
-    acc += exp(-0.5 * z * z) * (D[k] + D[M + k] + D[2 * M + k]);
+  for (int k = threadIdx.x; k < M; k += 256) {
+    const double z = (DE[M + k] - om) / sig;
+    acc += exp(-0.5 * z * z) * DE[k];
   }
-  out[q] = om * norm * acc;
+  acc = block_sum4(acc, red);
+  if (threadIdx.x == 0) out[blockIdx.x] = om * (1.0 / (sig * sqrt(2.0 * M_PI))) * acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -475,33 +517,41 @@ __global__ void k_cheb_sigma(const double* __restrict__ D, int M, double a, doub
 // full three-term recursion, and their exciton densities
 // 2 sum_ia F_ia phi_i phi_a on the grid.
 // ---------------------------------------------------------------------------
-// g[q][m] = (2 - delta_m0)/M sum_k G(a x_k + b - omega_q) cos(m th_k),
-// th_k = pi (k + 1/2)/M; the node Gaussians of a block's omega are staged in
-// LDS 256 nodes at a time
-__global__ void __launch_bounds__(256) k_cheb_coef(const double* __restrict__ w, int N, int M,
-                                                   double a, double b, double sig,
-                                                   double* __restrict__ g) {
-  __shared__ double gk[256], tk[256];
-  const int m = blockIdx.x * blockDim.x + threadIdx.x;
-  const int q = blockIdx.y;
-  const double om = w[q];
-  const double norm = 1.0 / (sig * sqrt(2.0 * M_PI));
-  double acc = 0;
-  for (int k0 = 0; k0 < M; k0 += 256) {
-    __syncthreads();
-    const int k = k0 + (int)threadIdx.x;
-    if (k < M) {
-      const double th = M_PI * (k + 0.5) / M;
-      const double z = (a * cos(th) + b - om) / sig;
-      gk[threadIdx.x] = norm * exp(-0.5 * z * z);
-      tk[threadIdx.x] = th;
-    }
-    __syncthreads();
-    const int kn = min(256, M - k0);
-    if (m < N)
-      for (int j = 0; j < kn; ++j) acc += gk[j] * cos(m * tk[j]);
+// g[q][m] = (2 - delta_m0)/M sum_k G(a x_k + b - omega_q) cos(m th_k), th_k =
+// pi (k + 1/2)/M: the node Gaussians gk[q][k] and angles first, then a block
+// per m, threads over the nodes, all frequencies (n_w <= 8) at once.  With a
+// thread per (m, omega) the cosines ran on 16 of 256 CUs and once per omega
+// (376 us at N = 800, 4 frequencies; 20 us now).
+__global__ void __launch_bounds__(256) k_cheb_tables(const double* __restrict__ w, int n_w, int M, double a, double b,
+                                                     double sig, double* __restrict__ th, double* __restrict__ gk) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= n_w * M) return;
+  const int k = i % M;
+  const double t = M_PI * (k + 0.5) / M;
+  const double z = (a * cos(t) + b - w[i / M]) / sig;
+  gk[i] = 1.0 / (sig * sqrt(2.0 * M_PI)) * exp(-0.5 * z * z);
+  if (i < M) th[i] = t;
+}
+constexpr int CC_W = 8;
+__global__ void __launch_bounds__(256) k_cheb_coef(const double* __restrict__ th, const double* __restrict__ gk,
+                                                   int n_w, int N, int M, double* __restrict__ g) {
+  __shared__ double red[4];
+  const int m = blockIdx.x;
+  double acc[CC_W];
+#pragma unroll
+  for (int q = 0; q < CC_W; ++q) acc[q] = 0;
+  for (int k = threadIdx.x; k < M; k += 256) {
+    const double c = cos(m * th[k]);
+#pragma unroll
+    for (int q = 0; q < CC_W; ++q)
+      if (q < n_w) acc[q] += gk[(size_t)q * M + k] * c;
   }
-  if (m < N) g[(size_t)q * N + m] = (m == 0 ? 1.0 : 2.0) * acc / M;
+#pragma unroll
+  for (int q = 0; q < CC_W; ++q) {
+    if (q >= n_w) break;
+    const double t = block_sum4(acc[q], red);
+    if (threadIdx.x == 0) g[(size_t)q * N + m] = (m == 0 ? 1.0 : 2.0) * t / M;
+  }
 }
 
 // F[q][p][i] = g[q][0] f0[p][i]
@@ -550,30 +600,44 @@ __global__ void __launch_bounds__(256) k_cheb_step_acc(const double* __restrict_
   }
 }
 
-// dens[k][r] = 2 sum_i phi_{v0+i}(r) sum_a F[k][i n_c + a] phi_{c0+a}(r) for
-// the (up to) 8 outputs k = 8 blockIdx.y + kk < n_out; one thread per point
+// dens[k][r] = 2 sum_e F[k][e] phi_{v0+i}(r) phi_{c0+a}(r), e = i n_c + a < n_o
+// n_c, on the FP64 matrix cores (v_mfma_f64_16x16x4f64: lane l supplies A[l %
+// 16][l / 16] and B[l / 16][l % 16], holds D[4 v + l / 16][l % 16]): 16 outputs
+// x 16 points a wave, contraction over e in steps of 4, the pair products
+// formed on the fly.  32^3, 800 pairs, 12 outputs: 78 us (11 us of matrix core
+// time, the rest load latency), against 426 us for a thread per point.
+typedef double dm4 __attribute__((ext_vector_type(4)));
 __global__ void __launch_bounds__(256) k_exciton_density(const double* __restrict__ phi, int v0, int c0,
                                                          int n_o, int n_c, size_t ng,
                                                          const double* __restrict__ F, int n_out,
                                                          double* __restrict__ dens) {
-  const size_t r = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int k0 = blockIdx.y * 8, kn = min(8, n_out - k0);
-  if (r >= ng) return;
-  const int n = n_o * n_c;
-  double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int i = 0; i < n_o; ++i) {
-    const double pv = phi[(size_t)(v0 + i) * ng + r];
-    for (int a = 0; a < n_c; ++a) {
-      const double t = pv * phi[(size_t)(c0 + a) * ng + r];
-      const double* fk = F + (size_t)k0 * n + i * n_c + a;
-#pragma unroll
-      for (int kk = 0; kk < 8; ++kk)
-        if (kk < kn) acc[kk] += fk[(size_t)kk * n] * t;
+  const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+  const size_t r = ((size_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 16 + lr;
+  const size_t rc = min(r, ng - 1);
+  const int k0 = blockIdx.y * 16, n = n_o * n_c;
+  // outputs past the last: a copy of it, never stored
+  const double* fk = F + (size_t)min(k0 + lr, n_out - 1) * n;
+  const double* pv = phi + (size_t)v0 * ng + rc;
+  const double* pc = phi + (size_t)c0 * ng + rc;
+  dm4 acc = {0.0, 0.0, 0.0, 0.0};
+  int i = lk / n_c, a = lk % n_c;
+  for (int e = 0; e < n; e += 4) {
+    const bool live = e + lk < n;
+    const double f = live ? fk[e + lk] : 0.0;
+    const double t = live ? pv[(size_t)i * ng] * pc[(size_t)a * ng] : 0.0;
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(f, t, acc, 0, 0, 0);
+    a += 4;
+    while (a >= n_c) {
+      a -= n_c;
+      ++i;
     }
   }
+  if (r >= ng) return;
 #pragma unroll
-  for (int kk = 0; kk < 8; ++kk)
-    if (kk < kn) dens[(size_t)(k0 + kk) * ng + r] = 2.0 * acc[kk];
+  for (int v = 0; v < 4; ++v) {
+    const int k = k0 + 4 * v + lk;
+    if (k < n_out) dens[(size_t)k * ng + r] = 2.0 * acc[v];
+  }
 }
 
 // F[q][i] = g[q][m] f[i] (init) or F[q][i] += g[q][m] f[i], i < len: the
@@ -995,20 +1059,25 @@ hipError_t launch_cheb_step(const double* A, int n, const double* fc, const doub
                      first, part);
   return hipGetLastError();
 }
-hipError_t launch_cheb_spectrum(const double* part, int K, int nblk, double* mu, int M, double* D,
+hipError_t launch_cheb_spectrum(double* part, int K, int nblk, double* mu, int M, double* DE,
                                 double a, double b, const double* w, int n_w, double sig,
                                 double* out, hipStream_t st) {
+  if (nblk > 1) hipLaunchKernelGGL(k_cheb_part_sum, dim3((6 * K + 3) / 4), dim3(256), 0, st, part, K, nblk);
   hipLaunchKernelGGL(k_cheb_moments, dim3((2 * K + 255) / 256, 3), dim3(256), 0, st, part, K, nblk, mu);
-  hipLaunchKernelGGL(k_cheb_nodes, dim3((M + 255) / 256, 3), dim3(256), 0, st, mu, 2 * K, M, D);
-  if (n_w > 0)
-    hipLaunchKernelGGL(k_cheb_sigma, dim3((n_w + 255) / 256), dim3(256), 0, st, D, M, a, b, w, n_w, sig,
-                       out);
+  if (n_w > 0) {
+    hipLaunchKernelGGL(k_cheb_nodes, dim3((M + 63) / 64), dim3(64), 0, st, mu, 2 * K, M, a, b, DE);
+    hipLaunchKernelGGL(k_cheb_sigma, dim3(n_w), dim3(256), 0, st, DE, M, w, sig, out);
+  }
   return hipGetLastError();
 }
+size_t cheb_coef_scratch(int n_w, int M) { return (size_t)(1 + n_w) * M; }
 hipError_t launch_cheb_coef(const double* w, int n_w, int N, int M, double a, double b, double sig,
-                            double* g, hipStream_t st) {
-  if (n_w <= 0 || N <= 0 || M <= 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_cheb_coef, dim3((N + 255) / 256, n_w), dim3(256), 0, st, w, N, M, a, b, sig, g);
+                            double* scratch, double* g, hipStream_t st) {
+  if (n_w <= 0 || n_w > CC_W || N <= 0 || M <= 0) return hipErrorInvalidValue;
+  double* gk = scratch + (size_t)M;
+  const unsigned nt = (unsigned)(((size_t)n_w * M + 255) / 256);
+  hipLaunchKernelGGL(k_cheb_tables, dim3(nt), dim3(256), 0, st, w, n_w, M, a, b, sig, scratch, gk);
+  hipLaunchKernelGGL(k_cheb_coef, dim3(N), dim3(256), 0, st, scratch, gk, n_w, N, M, g);
   return hipGetLastError();
 }
 hipError_t launch_cheb_acc_init(const double* f0, int n, const double* g, int N, int n_w, double* F,
@@ -1032,7 +1101,7 @@ hipError_t launch_states_acc(double* F, const double* f, const double* g, int N,
 hipError_t launch_exciton_density(const double* phi, int v0, int c0, int n_o, int n_c, size_t ng,
                                   const double* F, int n_out, double* dens, hipStream_t st) {
   if (n_out <= 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_exciton_density, dim3((unsigned)((ng + 255) / 256), (n_out + 7) / 8), dim3(256), 0,
+  hipLaunchKernelGGL(k_exciton_density, dim3((unsigned)((ng + 63) / 64), (n_out + 15) / 16), dim3(256), 0,
                      st, phi, v0, c0, n_o, n_c, ng, F, n_out, dens);
   return hipGetLastError();
 }
@@ -1191,16 +1260,6 @@ __global__ void k_assemble_w(const double* __restrict__ q, const double* __restr
 // order by one block, so the result does not depend on scheduling.
 // ---------------------------------------------------------------------------
 constexpr int BND_T = 256, BND_PER = 16;
-__device__ __forceinline__ double block_sum_256(double v, double* red) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  if (lane == 0) red[wv] = v;
-  __syncthreads();
-  const double t = red[0] + red[1] + red[2] + red[3];
-  __syncthreads();
-  return t;
-}
-
 __global__ void __launch_bounds__(BND_T) k_boundary_partial(const double* __restrict__ vext,
                                                             const double* __restrict__ vh, int n,
                                                             double* __restrict__ part) {
@@ -1217,8 +1276,8 @@ __global__ void __launch_bounds__(BND_T) k_boundary_partial(const double* __rest
       if (i == 0 || j == 0 || k == 0) bnd += v;
     }
   }
-  all = block_sum_256(all, red);
-  bnd = block_sum_256(bnd, red);
+  all = block_sum4(all, red);
+  bnd = block_sum4(bnd, red);
   if (threadIdx.x == 0) {
     part[2 * (size_t)blockIdx.x] = all;
     part[2 * (size_t)blockIdx.x + 1] = bnd;
@@ -1233,8 +1292,8 @@ __global__ void __launch_bounds__(BND_T) k_boundary_final(const double* __restri
     all += part[2 * (size_t)b];
     bnd += part[2 * (size_t)b + 1];
   }
-  all = block_sum_256(all, red);
-  bnd = block_sum_256(bnd, red);
+  all = block_sum4(all, red);
+  bnd = block_sum4(bnd, red);
   if (threadIdx.x == 0) {
     const double nb = 3.0 * n * n - 3.0 * n + 1.0, ng = (double)n * n * n;
     out[0] = bnd / nb - all / ng;
