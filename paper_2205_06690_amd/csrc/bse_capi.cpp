@@ -827,7 +827,8 @@ void spectrum(bse_system* s, int n_exc, double* omega, double* dip2, int n_w, co
     if (fused) {
       // every iteration up to the next convergence check in one launch
       if (!check) continue;
-      HIPC(launch_lanczos_steps(s->A_d.as<double>(), n, V, done, mk, al_d, bq_d, st));
+      if (n <= lanczos_res_max()) HIPC(launch_lanczos_res(s->A_d.as<double>(), n, V, done, mk, al_d, bq_d, st));
+      else HIPC(launch_lanczos_steps(s->A_d.as<double>(), n, V, done, mk, al_d, bq_d, st));
     } else {
       HIPC(launch_gemv(s->A_d.as<double>(), n, V + (size_t)k * n, w, st));
       // two passes of classical Gram-Schmidt against the whole basis
@@ -862,12 +863,18 @@ void spectrum(bse_system* s, int n_exc, double* omega, double* dip2, int n_w, co
     }
     if (mm < n_exc) fail(BSE_ERR_NUMERIC, "Lanczos subspace smaller than n_exc");
     // the convergence test takes Ritz values to 1e-9 (the last components of
-    // their vectors barely depend on that); the final ones are resolved fully
-    tridiag_lowest(alpha, beta, mm, std::min(n_exc, mm), theta, svec, 1e-9);
+    // their vectors barely depend on that); the final ones are resolved fully.
+    // The highest of them converges last as a rule: alone it shows most
+    // checks to be too early
     const double b_last = std::sqrt(std::max(bq[mm - 1], 0.0));
-    bool conv = true;
-    for (int j = 0; j < (int)theta.size() && conv; ++j)
-      if (b_last * std::fabs(svec[j][mm - 1]) > 1e-10 * std::max(anorm, 1.0)) conv = false;
+    const double lim = 1e-10 * std::max(anorm, 1.0);
+    const int nt = std::min(n_exc, mm);
+    bool conv = b_last * std::fabs(bse_host::tridiag_last_component(alpha, beta, mm, nt - 1, 1e-9)) <= lim;
+    if (conv) {
+      tridiag_lowest(alpha, beta, mm, nt, theta, svec, 1e-9);
+      for (int j = 0; j < (int)theta.size() && conv; ++j)
+        if (b_last * std::fabs(svec[j][mm - 1]) > lim) conv = false;
+    }
     if (conv || breakdown || mk == n) {
       m = mm;
       tridiag_lowest(alpha, beta, mm, std::min(n_exc, mm), theta, svec);

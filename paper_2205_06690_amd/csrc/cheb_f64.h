@@ -25,4 +25,10 @@ hipError_t launch_cheb_dots(const double* fc, const double* out, int n, int k0, 
 hipError_t launch_cheb_states(const double* fc, const double* out, int n, int k0, int steps, const double* g, int N,
                               int n_w, double* F, hipStream_t st);
 
+// Lanczos iterations k0 .. k1-1 for n <= lanczos_res_max(): basis V[n+1][n]
+// (v_0 .. v_k0 set), alpha[k], bq[k] = |w_k|^2
+int lanczos_res_max();
+hipError_t launch_lanczos_res(const double* A, int n, double* V, int k0, int k1, double* alpha, double* bq,
+                              hipStream_t st);
+
 }  // namespace bse

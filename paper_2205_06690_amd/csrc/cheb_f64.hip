@@ -1,5 +1,6 @@
-// The Chebyshev recursion of the electron-hole spectra (Eqs. 7-8) as one
-// launch per CHEB_SEG steps, with A in registers and LDS.
+// The recursions of the electron-hole spectra with A in registers and LDS: the
+// Chebyshev recursion (Eqs. 7-8) as one launch per CHEB_SEG steps, and the
+// Lanczos steps up to a convergence check.
 //
 // A step is a matrix-vector product whose result the next step needs: as a
 // launch per step it costs a launch and a walk of A through one wave per row
@@ -158,6 +159,146 @@ __global__ void k_cheb_empty(unsigned long long* __restrict__ p, size_t n) {
     p[i] = CHEB_EMPTY;
 }
 
+// sum over the 16 lanes of a row, in every lane
+__device__ __forceinline__ double sum16(double v) {
+  v += xor16<8>(v);
+  v += xor16<4>(v);
+  v += xor16<2>(v);
+  v += xor16<1>(v);
+  return v;
+}
+
+// Lanczos iterations k0 .. k1-1 in one workgroup: w = A v_k, two passes of
+// classical Gram-Schmidt against v_0 .. v_k (alpha_k = the first pass's
+// coefficient on v_k), bq[k] = |w|^2, v_{k+1} = w / |w|.  A step reads A once and
+// V four times, so V is what stays on the CU: group g of 16 lanes owns the
+// vectors g + 32 q, the first 128 in registers, the rest in LDS; a group forms
+// its coefficients and its share of V c without a barrier, and the shares meet
+// in LDS.  A streams from L2 through registers.  n = 200: 11.5 us a step on
+// average over 140 steps (21 us with A and V read from L2 by every step; 14 us
+// with A in registers and V in LDS and L2).
+constexpr int LZ_QR = 4;                    // vectors a group keeps in registers
+template <int NJ>
+__global__ void __launch_bounds__(CR_T) k_lanczos_res(const double* __restrict__ A, int n, double* __restrict__ V,
+                                                      int k0, int k1, double* __restrict__ alpha,
+                                                      double* __restrict__ bq) {
+  constexpr int NP = 16 * NJ, NI = (NP + 31) / 32, NW = CR_T / 64;
+  extern __shared__ double cr_lds[];
+  double* f = cr_lds;                       // [NP] v_k, zero past n
+  double* w = f + NP;                       // [NP]
+  double* part = w + NP;                    // [NW][NP]
+  double* red = part + NW * NP;             // [NW]
+  double* vl = red + NW;                    // [.][NP] vectors 32 LZ_QR ..
+  const int tid = threadIdx.x, c16 = tid & 15, g = tid >> 4, wv = tid >> 6;
+  double vr[LZ_QR][NJ];
+#pragma unroll
+  for (int q = 0; q < LZ_QR; ++q)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int row = g + 32 * q, col = c16 + 16 * j;
+      vr[q][j] = (row <= k0 && col < n) ? V[(size_t)row * n + col] : 0.0;
+    }
+  for (int e = tid; e < (k0 + 1 - 32 * LZ_QR) * NP; e += CR_T) {
+    const int row = 32 * LZ_QR + e / NP, col = e % NP;
+    vl[e] = col < n ? V[(size_t)row * n + col] : 0.0;
+  }
+  if (tid < NP) {
+    f[tid] = tid < n ? V[(size_t)k0 * n + tid] : 0.0;
+    w[tid] = 0.0;
+  }
+  __syncthreads();
+  for (int k = k0; k < k1; ++k) {
+    {
+      // rows g + 32 i; rows and columns past the last: in-range values, dropped.
+      // Four columns at a time: more loads in flight would spill V
+      double s[NI];
+#pragma unroll
+      for (int i = 0; i < NI; ++i) s[i] = 0.0;
+#pragma unroll 4
+      for (int j = 0; j < NJ; ++j) {
+        const int col = min(c16 + 16 * j, n - 1);
+        const double x = f[c16 + 16 * j];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) s[i] += A[(size_t)min(g + 32 * i, n - 1) * n + col] * x;
+      }
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const double t = sum16(s[i]);
+        if (c16 == 0 && g + 32 * i < n) w[g + 32 * i] = t;
+      }
+    }
+    __syncthreads();
+    const int nq = k / 32;                  // vectors g + 32 q, q <= nq, may exist
+    for (int pass = 0; pass < 2; ++pass) {
+      double wr[NJ], u[NJ];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        wr[j] = w[c16 + 16 * j];
+        u[j] = 0.0;
+      }
+#pragma unroll
+      for (int q = 0; q < LZ_QR; ++q)
+        if (q <= nq) {
+          double t = 0.0;
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) t += vr[q][j] * wr[j];
+          t = sum16(t);                     // 0 for a vector that is not there yet
+          if (pass == 0 && g + 32 * q == k && c16 == 0) alpha[k] = t;
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) u[j] += t * vr[q][j];
+        }
+      for (int row = g + 32 * LZ_QR; row <= k; row += 32) {
+        const double* x = vl + (row - 32 * LZ_QR) * NP + c16;
+        double t = 0.0;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) t += x[16 * j] * wr[j];
+        t = sum16(t);
+        if (pass == 0 && row == k && c16 == 0) alpha[k] = t;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) u[j] += t * x[16 * j];
+      }
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        u[j] += __shfl_xor(u[j], 16, 64);
+        u[j] += __shfl_xor(u[j], 32, 64);
+        if ((tid & 63) < 16) part[wv * NP + c16 + 16 * j] = u[j];
+      }
+      __syncthreads();
+      if (tid < n) {
+        double t = 0.0;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) t += part[q * NP + tid];
+        w[tid] -= t;
+      }
+      __syncthreads();
+    }
+    double t = tid < n ? w[tid] * w[tid] : 0.0;
+    for (int off = 32; off > 0; off >>= 1) t += __shfl_down(t, off, 64);
+    if ((tid & 63) == 0) red[wv] = t;
+    __syncthreads();
+    double b2 = 0.0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) b2 += red[q];
+    if (tid == 0) bq[k] = b2;
+    if (k + 1 >= n) break;
+    const int kn = k + 1;
+    if (tid < NP) {
+      const double v = tid < n ? w[tid] * (b2 > 0.0 ? 1.0 / sqrt(b2) : 0.0) : 0.0;
+      if (tid < n) V[(size_t)kn * n + tid] = v;
+      f[tid] = v;
+      if (kn >= 32 * LZ_QR) vl[(kn - 32 * LZ_QR) * NP + tid] = v;
+    }
+    __syncthreads();
+    if (g == kn % 32) {
+#pragma unroll
+      for (int q = 0; q < LZ_QR; ++q)
+        if (q == kn / 32)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) vr[q][j] = f[c16 + 16 * j];
+    }
+  }
+}
+
 // one wave per (m, polarisation)
 __global__ void __launch_bounds__(256) k_cheb_dots(const double* __restrict__ fc, const double* __restrict__ out, int n,
                                                    int steps, double* __restrict__ S) {
@@ -253,6 +394,29 @@ hipError_t launch_cheb_res(const double* A, int n, const double* fc, const doubl
                      reinterpret_cast<unsigned long long*>(out), tot);
   if (n <= 512) return cheb_res_go<4, 32, true>(A, n, fc, fp, out, steps, first, a, b, err, st);
   return cheb_res_go<2, 64, true>(A, n, fc, fp, out, steps, first, a, b, err, st);
+}
+
+template <int NJ>
+static hipError_t lanczos_res_go(const double* A, int n, double* V, int k0, int k1, double* alpha, double* bq,
+                                 hipStream_t st) {
+  constexpr int NP = 16 * NJ, NW = CR_T / 64;
+  const size_t lds = sizeof(double) * ((size_t)(2 + NW) * NP + NW + (size_t)std::max(0, n - 32 * LZ_QR) * NP);
+  if (lds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute((const void*)k_lanczos_res<NJ>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k_lanczos_res<NJ>, dim3(1), dim3(CR_T), lds, st, A, n, V, k0, k1, alpha, bq);
+  return hipGetLastError();
+}
+// n = 208: V past its first 128 vectors takes 133 KB of LDS
+int lanczos_res_max() { return 208; }
+hipError_t launch_lanczos_res(const double* A, int n, double* V, int k0, int k1, double* alpha, double* bq,
+                              hipStream_t st) {
+  if (n < 1 || n > lanczos_res_max() || k0 < 0 || k1 > n || k0 >= k1) return hipErrorInvalidValue;
+  if (n <= 64) return lanczos_res_go<4>(A, n, V, k0, k1, alpha, bq, st);
+  if (n <= 128) return lanczos_res_go<8>(A, n, V, k0, k1, alpha, bq, st);
+  return lanczos_res_go<13>(A, n, V, k0, k1, alpha, bq, st);
 }
 
 hipError_t launch_cheb_dots(const double* fc, const double* out, int n, int k0, int steps, double* S, hipStream_t st) {

@@ -55,8 +55,9 @@ void sturm_counts(const std::vector<double>& a, const std::vector<double>& b2, i
 // The k lowest eigenpairs of the symmetric tridiagonal T (diagonal a,
 // off-diagonal b): bisection on Sturm counts until each bracket is below
 // tol relative to its magnitude, then inverse iteration.
-void tridiag_lowest(const std::vector<double>& a, const std::vector<double>& b, int m, int k,
-                    std::vector<double>& theta, std::vector<std::vector<double>>& vecs, double tol) {
+// eigenpairs j0 .. j0 + k - 1 (ascending)
+static void tridiag_range(const std::vector<double>& a, const std::vector<double>& b, int m, int j0, int k,
+                          std::vector<double>& theta, std::vector<std::vector<double>>& vecs, double tol) {
   double lo = a[0], hi = a[0];
   for (int i = 0; i < m; ++i) {
     const double r = (i > 0 ? std::fabs(b[i - 1]) : 0.0) + (i < m - 1 ? std::fabs(b[i]) : 0.0);
@@ -71,7 +72,7 @@ void tridiag_lowest(const std::vector<double>& a, const std::vector<double>& b, 
   const double piv0 = 2.220446049250313e-16 * tscale;
   std::vector<double> b2(std::max(m - 1, 1));
   for (int i = 0; i + 1 < m; ++i) b2[i] = b[i] * b[i];
-  // bisection of the k lowest eigenvalues, all brackets advanced together
+  // bisection of the k eigenvalues, all brackets advanced together
   std::vector<double> l(k, lo - 1e-12 * span), h(k, hi + 1e-12 * span), mid(k);
   std::vector<int> act(k), cnt(k);
   for (int it = 0; it < 200; ++it) {
@@ -85,7 +86,7 @@ void tridiag_lowest(const std::vector<double>& a, const std::vector<double>& b, 
     sturm_counts(a, b2, m, mid.data(), na, cnt.data());
     for (int q = 0; q < na; ++q) {
       const int j = act[q];
-      if (cnt[q] > j) h[j] = mid[q]; else l[j] = mid[q];
+      if (cnt[q] > j0 + j) h[j] = mid[q]; else l[j] = mid[q];
     }
   }
   theta.assign(k, 0.0);
@@ -146,6 +147,18 @@ void tridiag_lowest(const std::vector<double>& a, const std::vector<double>& b, 
       for (int i = 0; i < m; ++i) y[i] = z[i] / nrm;
     }
   }
+}
+
+void tridiag_lowest(const std::vector<double>& a, const std::vector<double>& b, int m, int k,
+                    std::vector<double>& theta, std::vector<std::vector<double>>& vecs, double tol) {
+  tridiag_range(a, b, m, 0, k, theta, vecs, tol);
+}
+
+double tridiag_last_component(const std::vector<double>& a, const std::vector<double>& b, int m, int j, double tol) {
+  std::vector<double> theta;
+  std::vector<std::vector<double>> vecs;
+  tridiag_range(a, b, m, j, 1, theta, vecs, tol);
+  return vecs[0][m - 1];
 }
 
 // Least squares of omega[b][m] = c_m + e v[b]: with box means removed,

@@ -32,6 +32,10 @@ void sturm_counts(const std::vector<double>& a, const std::vector<double>& b2, i
 void tridiag_lowest(const std::vector<double>& a, const std::vector<double>& b, int m, int k,
                     std::vector<double>& theta, std::vector<std::vector<double>>& vecs, double tol = 1e-15);
 
+// The last component of the normalised eigenvector of T's eigenvalue j (0 the
+// lowest), by the same bisection and inverse iteration for that pair alone.
+double tridiag_last_component(const std::vector<double>& a, const std::vector<double>& b, int m, int j, double tol);
+
 // Least squares of omega[b][m] = c_m + e v[b] over n_box boxes and n_exc
 // excitations; outputs eps_inv = e, c[n_exc] (nullable), w_k0[b] = e v[b].
 // Returns nullptr, or a message for bad arguments (nothing written).

@@ -61,3 +61,25 @@ def test_resident_recursion(n_o, n_c, n_mom):
     say(f"n = {n}, {n_mom} moments: residues {e:.1e}, sigma {es:.1e}, states {eF:.1e}, densities {ed:.1e}")
     assert max(e, es, eF, ed) < TOL
     s.close()
+
+
+@pytest.mark.parametrize("n_o,n_c", [(2, 3), (8, 8), (5, 13), (8, 16), (3, 43), (13, 16), (11, 19)])
+def test_resident_lanczos(n_o, n_c):
+    """The Lanczos steps with A on the chip (up to 208 rows; the path before
+    it takes 209) to the last basis vector, against a dense eigensolve:
+    excitons to the convergence test's 1e-10 residual, dipoles to the
+    residual over the level spacing."""
+    s, A, f0, _ = _system(n_o, n_c, 11 * n_o + n_c)
+    n = n_o * n_c
+    n_exc = min(n, 6)
+    om, d2 = s.spectrum(n_exc)
+    ev, X = np.linalg.eigh(A)
+    gap = np.diff(ev[:n_exc + 1]).min() if n > n_exc else 1e-2
+    e = np.abs(om - ev[:n_exc]).max()
+    ed = np.abs(d2 - (X[:, :n_exc].T @ f0) ** 2).max() / np.abs(f0).max() ** 2
+    om_all, _ = s.spectrum(n)
+    ea = np.abs(om_all - ev).max()
+    say(f"n = {n}: {n_exc} excitons {e:.1e}, dipoles {ed:.1e} (spacing {gap:.1e}), all {n} {ea:.1e}")
+    assert e < 1e-9 and ea < 1e-9
+    assert ed < max(1e-8, 4e-10 / gap)
+    s.close()
