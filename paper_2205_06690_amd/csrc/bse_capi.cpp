@@ -20,6 +20,7 @@
 #include "clean_mfma.h"
 #include "clean_f64.h"
 #include "cheb_f64.h"
+#include "gemm_f64.h"
 #include "contract_mfma.h"
 #include "host_math.h"
 
@@ -203,6 +204,7 @@ struct bse_system {
   // surrogate descriptors and buffers
   DBuf n0dens, vdev, fx, fy, fscale, fdots, fwpol;
   DBuf ch_ws, ch_dens;   // Chebyshev spectrum and exciton states
+  DBuf mx_v, mx_pp;      // recursion vectors and partials of the mixed spectrum
   DBuf mx_f, mx_tf, mx_out, mx_rho, mx_dv, mx_c, mx_part, mx_eps;  // matrix-free A f
   int mx_eps_v0 = -1, mx_eps_n = 0;   // valence window whose eps mx_eps holds
   DBuf bnd_n, bnd_v, bnd_part;   // boundary potential: density, v_H, block sums
@@ -913,28 +915,20 @@ void spectrum(bse_system* s, int n_exc, double* omega, double* dip2, int n_w, co
 // kinetic term by the FFT pipeline with the k^2/2 multiplier, the Hartree
 // term from dn = 2 sum phi_i f_i, the exchange-like term from the cached
 // W_ij, then the occupied-space projection as a GEMM and an update.
-// C[n_o][S] = dv sum_r f_i phi_s: the streaming projection kernel for up to
-// 32 fields, the tiled FP64 GEMM beyond; part holds proj_scratch(n_o, S, ng)
-size_t proj_scratch(int n_o, int S, size_t ng) {
-  return n_o <= 32 ? proj_part_elems(n_o, S) : gemm_part_elems(n_o, S, ng);
-}
-void proj_coef(const double* f, int n_o, const double* phi, int S, size_t ng, double dv, double* part,
-               double* C, hipStream_t st) {
-  if (n_o <= 32) HIPC(launch_proj_coef(f, n_o, phi, S, ng, dv, part, C, st));
-  else HIPC(launch_gemm_f64(f, n_o, phi, S, ng, dv, part, C, st));
-}
-
-void apply_a_mixed_device(bse_system* s, const double* f_dev, double* af_dev) {
-  const int n_o = s->a_no, S = s->cfg.n_occ;
+//
+// A-bar f of n_vec sets [n_vec][n_o][ng] into af and its coefficients on the
+// occupied orbitals into mx_c: everything but the projection itself
+void apply_abar_device(bse_system* s, const double* f_dev, int n_vec, double* af_dev) {
+  const int n_o = s->a_no, S = s->cfg.n_occ, nf = n_o * n_vec;
   const size_t ng = s->ng;
   hipStream_t st = s->stream;
   const double* phv = s->phi64.as<double>() + (size_t)(S - n_o) * ng;
-  s->mx_tf.alloc(sizeof(double) * ng * n_o);
-  s->mx_rho.alloc(sizeof(double) * ng);
-  s->mx_dv.alloc(sizeof(double) * ng);
-  s->mx_c.alloc(sizeof(double) * (size_t)n_o * S);
-  s->mx_part.alloc(sizeof(double) * proj_scratch(n_o, S, ng));
-  s->work64.alloc(sizeof(cplx<double>) * ng * (size_t)((n_o + 1) / 2));
+  s->mx_tf.alloc(sizeof(double) * ng * nf);
+  s->mx_rho.alloc(sizeof(double) * ng * n_vec);
+  s->mx_dv.alloc(sizeof(double) * ng * n_vec);
+  s->mx_c.alloc(sizeof(double) * (size_t)nf * S);
+  s->mx_part.alloc(sizeof(double) * gemm_part_elems(nf, S, ng));
+  s->work64.alloc(sizeof(cplx<double>) * ng * (size_t)((nf + 1) / 2));
   if (!s->vdev.p || s->vdev.bytes < sizeof(double) * ng) {
     s->vdev.alloc(sizeof(double) * ng);
     HIPC(hipMemcpy(s->vdev.p, s->vext.data(), sizeof(double) * ng, hipMemcpyHostToDevice));
@@ -946,10 +940,10 @@ void apply_a_mixed_device(bse_system* s, const double* f_dev, double* af_dev) {
     s->mx_eps_v0 = S - n_o;
     s->mx_eps_n = n_o;
   }
-  // kinetic term: T f_j for the n_o real fields (two per complex transform)
+  // kinetic term: T f_j for the real fields (two per complex transform)
   PoisArgs<double> a{};
   a.rho = f_dev;
-  a.B = n_o;
+  a.B = nf;
   a.work = s->work64.as<cplx<double>>();
   a.tw = s->td.tw.as<cplx<double>>();
   a.k2 = s->td.k2.as<double>();
@@ -958,15 +952,19 @@ void apply_a_mixed_device(bse_system* s, const double* f_dev, double* af_dev) {
   a.out64 = s->mx_tf.as<double>();
   HIPC(launch_poisson<double>(s->n, a, st));
   // Hartree term
-  HIPC(launch_mixed_density(phv, f_dev, n_o, ng, s->mx_rho.as<double>(), st));
-  poisson64(s, s->mx_rho.as<double>(), 1, s->mx_dv.as<double>(), nullptr, 0.0);
+  HIPC(launch_mixed_density(phv, f_dev, n_o, n_vec, ng, s->mx_rho.as<double>(), st));
+  poisson64(s, s->mx_rho.as<double>(), n_vec, s->mx_dv.as<double>(), nullptr, 0.0);
   HIPC(launch_mixed_combine(f_dev, s->mx_tf.as<double>(), s->vdev.as<double>(), s->mx_eps.as<double>(),
-                            s->cfg.scissors, s->mx_dv.as<double>(), phv, s->wij.as<double>(), n_o, ng,
+                            s->cfg.scissors, s->mx_dv.as<double>(), phv, s->wij.as<double>(), n_o, n_vec, ng,
                             af_dev, st));
-  // Q: coefficients on the occupied orbitals, then the update
-  proj_coef(af_dev, n_o, s->phi64.as<double>(), S, ng, s->dv, s->mx_part.as<double>(), s->mx_c.as<double>(),
-            st);
-  HIPC(launch_project_out(af_dev, n_o, s->phi64.as<double>(), S, s->mx_c.as<double>(), ng, st));
+  HIPC(launch_gemm_f64(af_dev, nf, s->phi64.as<double>(), S, ng, s->dv, s->mx_part.as<double>(), s->mx_c.as<double>(),
+                       st));
+}
+void apply_a_mixed_device(bse_system* s, const double* f_dev, double* af_dev) {
+  apply_abar_device(s, f_dev, 1, af_dev);
+  // Q: the update with the coefficients on the occupied orbitals
+  HIPC(launch_project_out(af_dev, s->a_no, s->phi64.as<double>(), s->cfg.n_occ, s->mx_c.as<double>(), s->ng,
+                          s->stream));
 }
 
 void apply_a_mixed(bse_system* s, int n_vec, const double* f, double* af) {
@@ -1003,38 +1001,35 @@ void chebyshev_mixed(bse_system* s, int n_mom, double e_min, double e_max, int n
   const int n_o = s->a_no, S = s->cfg.n_occ;
   const size_t ng = s->ng, len = (size_t)n_o * ng;
   const double b = 0.5 * (e_max + e_min), a = 0.5 * (e_max - e_min) * 1.01;
-  const int K = n_mom / 2, nblk = mixed_cheb_blocks(), M = 2 * n_mom;
-  DBuf fv, af, part, mu, D, wd, sd, cq, pq;
-  fv.alloc(sizeof(double) * 9 * len);               // [pol][3 rotating vectors][n_o][ng]
-  af.alloc(sizeof(double) * len);
-  part.alloc(sizeof(double) * 6 * (size_t)K * nblk);
+  const int K = n_mom / 2, M = 2 * n_mom, nf = 3 * n_o;
+  DBuf &fv = s->mx_v, &af = s->mx_out, &pq = s->mx_pp;
+  DBuf Sk, mu, D, wd, sd;
+  fv.alloc(sizeof(double) * 9 * len);               // [3 rotating][pol][n_o][ng]
+  af.alloc(sizeof(double) * 3 * len);
+  Sk.alloc(sizeof(double) * 6 * (size_t)K);
   mu.alloc(sizeof(double) * 3 * (size_t)n_mom);
   D.alloc(sizeof(double) * 3 * (size_t)M);
-  cq.alloc(sizeof(double) * (size_t)n_o * S);
-  pq.alloc(sizeof(double) * proj_scratch(n_o, S, ng));
+  s->mx_c.alloc(sizeof(double) * (size_t)nf * S);
+  pq.alloc(sizeof(double) * std::max(gemm_part_elems(nf, S, ng), project_part_elems(nf, ng)));
   if (n_w > 0) {
     wd.alloc(sizeof(double) * n_w);
     sd.alloc(sizeof(double) * n_w);
     HIPC(hipMemcpyAsync(wd.p, w_grid, sizeof(double) * n_w, hipMemcpyHostToDevice, st));
   }
   double* buf = fv.as<double>();
-  auto vec = [&](int p, int k) { return buf + ((size_t)p * 3 + (size_t)(k % 3)) * len; };
+  auto vec = [&](int k) { return buf + (size_t)(k % 3) * 3 * len; };
   const double* phv = s->phi64.as<double>() + (size_t)(S - n_o) * ng;
-  for (int p = 0; p < 3; ++p) {
-    double* f0 = vec(p, 0);
-    HIPC(launch_mixed_dipole(phv, n_o, s->n, s->cfg.h, p, f0, st));
-    proj_coef(f0, n_o, s->phi64.as<double>(), S, ng, s->dv, pq.as<double>(), cq.as<double>(), st);
-    HIPC(launch_project_out(f0, n_o, s->phi64.as<double>(), S, cq.as<double>(), ng, st));
+  // the three polarisations together: every pass over phi and W serves all
+  for (int p = 0; p < 3; ++p) HIPC(launch_mixed_dipole(phv, n_o, s->n, s->cfg.h, p, vec(0) + p * len, st));
+  HIPC(launch_gemm_f64(vec(0), nf, s->phi64.as<double>(), S, ng, s->dv, pq.as<double>(), s->mx_c.as<double>(), st));
+  HIPC(launch_project_out(vec(0), nf, s->phi64.as<double>(), S, s->mx_c.as<double>(), ng, st));
+  for (int k = 0; k < K; ++k) {
+    apply_abar_device(s, vec(k), 3, af.as<double>());
+    HIPC(launch_project_cheb(af.as<double>(), n_o, 3, s->phi64.as<double>(), S, s->mx_c.as<double>(), ng, vec(k),
+                             vec(k + 2), vec(k + 1), a, b, k == 0 ? 1 : 0, s->dv, pq.as<double>(),
+                             Sk.as<double>() + (size_t)k * 6, st));
   }
-  for (int k = 0; k < K; ++k)
-    for (int p = 0; p < 3; ++p) {
-      const double* fc = vec(p, k);
-      apply_a_mixed_device(s, fc, af.as<double>());
-      HIPC(launch_mixed_cheb_update(af.as<double>(), fc, vec(p, k + 2), vec(p, k + 1), len, a, b,
-                                    k == 0 ? 1 : 0, s->dv, p, part.as<double>() + (size_t)k * nblk * 6,
-                                    st));
-    }
-  HIPC(launch_cheb_spectrum(part.as<double>(), K, nblk, mu.as<double>(), M, D.as<double>(), a, b,
+  HIPC(launch_cheb_spectrum(Sk.as<double>(), K, 1, mu.as<double>(), M, D.as<double>(), a, b,
                             wd.as<double>(), n_w, sig, sd.as<double>(), st));
   if (n_w > 0) HIPC(hipMemcpyAsync(sigma, sd.p, sizeof(double) * n_w, hipMemcpyDeviceToHost, st));
   if (residues)
@@ -1292,12 +1287,12 @@ void exciton_states_mixed(bse_system* s, int n_mom, double e_min, double e_max, 
   DBuf fv, af, part, g, F, wd, cq, pq, amp, rho, cs;
   fv.alloc(sizeof(double) * 3 * len);               // [3 rotating vectors][n_o][ng]
   af.alloc(sizeof(double) * len);
-  part.alloc(sizeof(double) * 6 * (size_t)mixed_cheb_blocks());
+  part.alloc(sizeof(double) * (project_part_elems(n_o, ng) + 6));
   g.alloc(sizeof(double) * (size_t)n_w * n_mom);
   F.alloc(sizeof(double) * (size_t)n_w * len);
   wd.alloc(sizeof(double) * n_w);
   cq.alloc(sizeof(double) * (size_t)n_o * S);
-  pq.alloc(sizeof(double) * std::max(proj_scratch(n_o, S, ng), proj_scratch(n_o, std::max(n_a, 1), ng)));
+  pq.alloc(sizeof(double) * std::max(gemm_part_elems(n_o, S, ng), gemm_part_elems(n_o, std::max(n_a, 1), ng)));
   if (n_a > 0) amp.alloc(sizeof(double) * (size_t)n_o * n_a);
   if (dens_out) rho.alloc(sizeof(double) * ng);
   HIPC(hipMemcpyAsync(wd.p, w_list, sizeof(double) * n_w, hipMemcpyHostToDevice, st));
@@ -1311,24 +1306,25 @@ void exciton_states_mixed(bse_system* s, int n_mom, double e_min, double e_max, 
   for (int p = 0; p < 3; ++p) {
     double* f0 = vec(0);
     HIPC(launch_mixed_dipole(phv, n_o, s->n, s->cfg.h, p, f0, st));
-    proj_coef(f0, n_o, s->phi64.as<double>(), S, ng, s->dv, pq.as<double>(), cq.as<double>(), st);
+    HIPC(launch_gemm_f64(f0, n_o, s->phi64.as<double>(), S, ng, s->dv, pq.as<double>(), cq.as<double>(), st));
     HIPC(launch_project_out(f0, n_o, s->phi64.as<double>(), S, cq.as<double>(), ng, st));
     HIPC(launch_states_acc(F.as<double>(), f0, g.as<double>(), n_mom, 0, n_w, len, 1, st));
     for (int m = 0; m + 1 < n_mom; ++m) {
-      apply_a_mixed_device(s, vec(m), af.as<double>());
-      HIPC(launch_mixed_cheb_update(af.as<double>(), vec(m), vec(m + 2), vec(m + 1), len, a, b,
-                                    m == 0 ? 1 : 0, s->dv, p, part.as<double>(), st));
+      apply_abar_device(s, vec(m), 1, af.as<double>());
+      HIPC(launch_project_cheb(af.as<double>(), n_o, 1, s->phi64.as<double>(), S, s->mx_c.as<double>(), ng, vec(m),
+                               vec(m + 2), vec(m + 1), a, b, m == 0 ? 1 : 0, s->dv, part.as<double>() + 6,
+                               part.as<double>(), st));
       HIPC(launch_states_acc(F.as<double>(), vec(m + 1), g.as<double>(), n_mom, m + 1, n_w, len, 0, st));
     }
     for (int q = 0; q < n_w; ++q) {
       const double* Fq = F.as<double>() + (size_t)q * len;
       if (n_a > 0) {
-        proj_coef(Fq, n_o, pha, n_a, ng, s->dv, pq.as<double>(), amp.as<double>(), st);
+        HIPC(launch_gemm_f64(Fq, n_o, pha, n_a, ng, s->dv, pq.as<double>(), amp.as<double>(), st));
         HIPC(hipMemcpyAsync(f_out + ((size_t)q * 3 + p) * n_o * n_a, amp.p, sizeof(double) * n_o * n_a,
                             hipMemcpyDeviceToHost, st));
       }
       if (dens_out) {
-        HIPC(launch_mixed_density(phv, Fq, n_o, ng, rho.as<double>(), st));
+        HIPC(launch_mixed_density(phv, Fq, n_o, 1, ng, rho.as<double>(), st));
         HIPC(hipMemcpyAsync(dens_out + ((size_t)q * 3 + p) * ng, rho.p, sizeof(double) * ng,
                             hipMemcpyDeviceToHost, st));
       }

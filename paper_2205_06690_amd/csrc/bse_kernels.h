@@ -10,11 +10,6 @@ hipError_t launch_fill_nan(double* w, size_t n, hipStream_t st);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 template <typename T>
 hipError_t launch_products(const double* phi, const int* pq, int K, size_t ng, T* out, hipStream_t st);
-size_t gemm_chunk(int M, int N, size_t K);
-size_t gemm_part_elems(int M, int N, size_t K);
-// C[m][n] = scale * sum_r A[m][r] B[n][r]
-hipError_t launch_gemm_f64(const double* A, int M, const double* B, int N, size_t K, double scale,
-                           double* part, double* C, hipStream_t st);
 hipError_t launch_assemble_a(const double* X, const double* D, int no, int nc, int nij,
                              const double* eps_v, const double* eps_c, double scissors, double* A,
                              hipStream_t st);
@@ -33,28 +28,16 @@ hipError_t launch_dot(const double* a, const double* b, int n, double* out, hipS
 // out[q] = sum_k S[q][k] V[k], q < nq, k < m
 hipError_t launch_ritz(const double* V, int n, int m, const double* S, int nq, double* out,
                        hipStream_t st);
-// matrix-free A f (Eq. 6), FP64, fields [n_o][ng]: rho = 2 sum phi_i f_i;
-// out_j = Tf_j + (V + Delta - eps_j) f_j + dv phi_j - sum_i f_i W_ij (W stack
-// of pairs i <= j in row order); out_j -= sum_s C[j][s] phi_s (n_o S <= 8192)
-hipError_t launch_mixed_density(const double* phv, const double* f, int n_o, size_t ng, double* rho,
+// matrix-free A f (Eq. 6), FP64, n_vec sets of fields [n_vec][n_o][ng]: rho_v =
+// 2 sum phi_i f_i; out_j = Tf_j + (V + Delta - eps_j) f_j + dv_v phi_j - sum_i f_i
+// W_ij (W stack of pairs i <= j in row order; n_vec 1 or 3)
+hipError_t launch_mixed_density(const double* phv, const double* f, int n_o, int n_vec, size_t ng, double* rho,
                                 hipStream_t st);
 hipError_t launch_mixed_combine(const double* f, const double* tf, const double* vext,
                                 const double* eps_v, double scissors, const double* dv,
-                                const double* phv, const double* wij, int n_o, size_t ng,
+                                const double* phv, const double* wij, int n_o, int n_vec, size_t ng,
                                 double* out, hipStream_t st);
-// C[n_o][S] = dv sum_r f_i(r) phi_s(r) for n_o <= 32 fields (ng a multiple
-// of 32); part holds proj_part_elems(n_o, S) doubles
-size_t proj_part_elems(int n_o, int S);
-hipError_t launch_proj_coef(const double* f, int n_o, const double* phi, int S, size_t ng, double dv,
-                            double* part, double* C, hipStream_t st);
-hipError_t launch_project_out(double* out, int n_o, const double* phi, int S, const double* C,
-                              size_t ng, hipStream_t st);
-// mixed-representation Chebyshev: one step of polarisation p over len values
-// with partials part[mixed_cheb_blocks()][6]; dipole start f_j = (r_axis - c) phi_j
-int mixed_cheb_blocks();
-hipError_t launch_mixed_cheb_update(const double* af, const double* fc, const double* fp, double* fn,
-                                    size_t len, double a, double b, int first, double dv, int p,
-                                    double* part, hipStream_t st);
+// dipole start of the mixed representation: f_j = (r_axis - centre) phi_j
 hipError_t launch_mixed_dipole(const double* phv, int n_o, int n, double h, int axis, double* f,
                                hipStream_t st);
 // Chebyshev spectrum (Eqs. 7-8): Gershgorin rows lohi[2][n]; one recursion

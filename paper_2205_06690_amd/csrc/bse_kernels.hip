@@ -45,60 +45,6 @@ __global__ void k_products(const double* __restrict__ phi, const int* __restrict
   out[(size_t)k * ng + r] = (T)(phi[(size_t)p * ng + r] * phi[(size_t)q * ng + r]);
 }
 
-// FP64 split-K NT GEMM (vector FMA), 64x64 tile, 4x4 per thread
-constexpr int G_BM = 64, G_BN = 64;
-__global__ void __launch_bounds__(256) k_gemm_f64(const double* __restrict__ A, int M,
-                                                  const double* __restrict__ B, int N, size_t K,
-                                                  size_t chunk, double* __restrict__ part) {
-  constexpr int BK = 16;
-  __shared__ double As[BK][G_BM + 1];
-  __shared__ double Bs[BK][G_BN + 1];
-  const int m0 = blockIdx.x * G_BM, n0 = blockIdx.y * G_BN, kc = blockIdx.z;
-  const size_t k0 = (size_t)kc * chunk, k1 = min(K, k0 + chunk);
-  const int tid = threadIdx.x, tm = tid / 16, tn = tid % 16;
-  double acc[4][4] = {};
-  for (size_t kb = k0; kb < k1; kb += BK) {
-    for (int e = tid; e < G_BM * BK; e += 256) {
-      const int row = e / BK, kk = e % BK;
-      const size_t k = kb + kk;
-      As[kk][row] = (m0 + row < M && k < k1) ? A[(size_t)(m0 + row) * K + k] : 0.0;
-      Bs[kk][row] = (n0 + row < N && k < k1) ? B[(size_t)(n0 + row) * K + k] : 0.0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < BK; ++kk) {
-      double a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][tm * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tn * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * b[j];
-    }
-    __syncthreads();
-  }
-  double* out = part + (size_t)kc * M * N;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + tm * 4 + i, n = n0 + tn * 4 + j;
-      if (m < M && n < N) out[(size_t)m * N + n] = acc[i][j];
-    }
-}
-
-template <typename P>
-__global__ void k_part_sum(const P* __restrict__ part, int nchunk, int MN, double scale,
-                           double* __restrict__ C) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= MN) return;
-  double s = 0;
-  for (int k = 0; k < nchunk; ++k) s += (double)part[(size_t)k * MN + i];
-  C[i] = s * scale;
-}
-
 // A[(ia),(jb)] = (e_a - e_i + Delta) d_ij d_ab + 2 X[(ia),(jb)] - D[ab][ij]
 // with D packed over a <= b and i <= j (row-major upper triangles).
 __device__ __forceinline__ int upack(int a, int b, int n) {
@@ -660,232 +606,89 @@ __global__ void __launch_bounds__(256) k_states_acc(double* __restrict__ F, cons
 // and out are [n_o][ng] real fields of the valence window; W_ij comes from
 // the [n_ij][ng] stack of pairs i <= j in row order.
 // ---------------------------------------------------------------------------
-// rho = 2 sum_i phi_i f_i
+// rho_v = 2 sum_i phi_i f_i of set v = blockIdx.y
 __global__ void k_mixed_density(const double* __restrict__ phv, const double* __restrict__ f,
                                 int n_o, size_t ng, double* __restrict__ rho) {
   const size_t r = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= ng) return;
+  f += (size_t)blockIdx.y * n_o * ng;
   double acc = 0;
+#pragma unroll 4
   for (int i = 0; i < n_o; ++i) acc += phv[(size_t)i * ng + r] * f[(size_t)i * ng + r];
-  rho[r] = 2.0 * acc;
+  rho[(size_t)blockIdx.y * ng + r] = 2.0 * acc;
 }
 
-// out_j = Tf_j + (V + Delta - eps_j) f_j + dv phi_j - sum_i f_i W_ij
-__global__ void k_mixed_combine(const double* __restrict__ f, const double* __restrict__ tf,
-                                const double* __restrict__ vext, const double* __restrict__ eps_v,
-                                double scissors, const double* __restrict__ dv,
-                                const double* __restrict__ phv, const double* __restrict__ wij,
-                                int n_o, size_t ng, double* __restrict__ out) {
+// out_j = Tf_j + (V + Delta - eps_j) f_j + dv phi_j - sum_i f_i W_ij for NV sets of
+// NO fields: one thread per point holds every f and every sum, so that each
+// W_ij (i <= j) is read once for all of them.  Bound by reading W, f and Tf and
+// writing out: 64^3, 3 sets of 10, 325 MB in 57 us (5.7 TB/s, W partly from the
+// Infinity Cache), against 3 x 59 us for a thread per point and field.
+template <int NO, int NV>
+__global__ void __launch_bounds__(256) k_mixed_combine_all(const double* __restrict__ f, const double* __restrict__ tf,
+                                                           const double* __restrict__ vext,
+                                                           const double* __restrict__ eps_v, double scissors,
+                                                           const double* __restrict__ dv,
+                                                           const double* __restrict__ phv,
+                                                           const double* __restrict__ wij, size_t ng,
+                                                           double* __restrict__ out) {
+  const size_t r = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (r >= ng) return;
+  double x[NV][NO], s[NV][NO], d[NV];
+  const double v0 = vext[r] + scissors;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) d[v] = dv[(size_t)v * ng + r];
+#pragma unroll
+  for (int j = 0; j < NO; ++j) {
+    const double ph = phv[(size_t)j * ng + r], vj = v0 - eps_v[j];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      const size_t e = ((size_t)v * NO + j) * ng + r;
+      x[v][j] = f[e];
+      s[v][j] = tf[e] + vj * x[v][j] + d[v] * ph;
+    }
+  }
+  size_t p = r;
+#pragma unroll
+  for (int i = 0; i < NO; ++i)
+#pragma unroll
+    for (int j = i; j < NO; ++j, p += ng) {
+      const double w = wij[p];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        s[v][j] -= x[v][i] * w;
+        if (i != j) s[v][i] -= x[v][j] * w;
+      }
+    }
+#pragma unroll
+  for (int j = 0; j < NO; ++j)
+#pragma unroll
+    for (int v = 0; v < NV; ++v) out[((size_t)v * NO + j) * ng + r] = s[v][j];
+}
+
+// the same for any n_o: a thread per point and field, NV sets at once
+template <int NV>
+__global__ void __launch_bounds__(256) k_mixed_combine(const double* __restrict__ f, const double* __restrict__ tf,
+                                                       const double* __restrict__ vext,
+                                                       const double* __restrict__ eps_v, double scissors,
+                                                       const double* __restrict__ dv, const double* __restrict__ phv,
+                                                       const double* __restrict__ wij, int n_o, size_t ng,
+                                                       double* __restrict__ out) {
   const size_t r = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int j = blockIdx.y;
   if (r >= ng) return;
-  const double fj = f[(size_t)j * ng + r];
-  double v = tf[(size_t)j * ng + r] + (vext[r] + scissors - eps_v[j]) * fj + dv[r] * phv[(size_t)j * ng + r];
+  const size_t set = (size_t)n_o * ng, e = (size_t)j * ng + r;
+  const double vj = vext[r] + scissors - eps_v[j], ph = phv[e];
+  double s[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) s[v] = tf[v * set + e] + vj * f[v * set + e] + dv[(size_t)v * ng + r] * ph;
   for (int i = 0; i < n_o; ++i) {
     const int lo = i < j ? i : j, hi = i < j ? j : i;
-    const int p = lo * n_o - lo * (lo - 1) / 2 + (hi - lo);
-    v -= f[(size_t)i * ng + r] * wij[(size_t)p * ng + r];
+    const double w = wij[(size_t)(lo * n_o - lo * (lo - 1) / 2 + (hi - lo)) * ng + r];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) s[v] -= f[v * set + (size_t)i * ng + r] * w;
   }
-  out[(size_t)j * ng + r] = v;
-}
-
-// out_j -= sum_s C[j][s] phi_s (the occupied-space projection), C staged in LDS
-// out_j -= sum_s C[j][s] phi_s: the coefficients of PO_SC orbitals at a time
-// sit in LDS transposed, cs[s][JB], so that each orbital's JB coefficients
-// are read as double2; JB fields per pass over phi (one pass for n_o <= JB)
-constexpr int PO_LDS = 4096;                     // doubles of coefficients in LDS
-template <int JB>
-__global__ void __launch_bounds__(256) k_project_out(double* __restrict__ out, int n_o,
-                                                     const double* __restrict__ phi, int S,
-                                                     const double* __restrict__ C, size_t ng) {
-  constexpr int SC = PO_LDS / JB;                // orbitals per staged chunk
-  __shared__ __attribute__((aligned(16))) double cs[PO_LDS];
-  const size_t r = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool live = r < ng;
-  for (int j0 = 0; j0 < n_o; j0 += JB) {
-    double acc[JB];
 #pragma unroll
-    for (int q = 0; q < JB; ++q) acc[q] = 0;
-    for (int c0 = 0; c0 < S; c0 += SC) {
-      const int cn = min(SC, S - c0);
-      __syncthreads();
-      for (int e = threadIdx.x; e < cn * JB; e += blockDim.x) {
-        const int sI = e / JB, q = e % JB;
-        cs[e] = (j0 + q < n_o) ? C[(size_t)(j0 + q) * S + c0 + sI] : 0.0;
-      }
-      __syncthreads();
-      if (!live) continue;
-#pragma unroll 2
-      for (int sI = 0; sI < cn; ++sI) {
-        const double p = phi[(size_t)(c0 + sI) * ng + r];
-        const double2* c2 = reinterpret_cast<const double2*>(cs + (size_t)sI * JB);
-#pragma unroll
-        for (int q = 0; q < JB / 2; ++q) {
-          const double2 c = c2[q];
-          acc[2 * q] += c.x * p;
-          acc[2 * q + 1] += c.y * p;
-        }
-      }
-    }
-    if (live)
-#pragma unroll
-      for (int q = 0; q < JB; ++q)
-        if (j0 + q < n_o) out[(size_t)(j0 + q) * ng + r] -= acc[q];
-  }
-}
-
-// Coefficients of n_o fields on S orbitals, C[i][s] = dv sum_r f_i(r)
-// phi_s(r): block (x, y) owns the points [x pb, (x+1) pb) and the orbitals
-// [128 y, 128 y + 128); tiles of PJ_T points of phi (rows padded) and of
-// the fields are staged in LDS, the next tile's loads in flight during the
-// current one; thread t keeps the n_o sums of orbital t % 128 over half of
-// each tile's points (t / 128), the halves are added at the end, and
-// part[x][i][s] is reduced over x afterwards.
-constexpr int PJ_T = 32, PJ_S = 128, PJ_BLK = 512;
-template <int NO>
-__global__ void __launch_bounds__(256) k_proj_coef(const double* __restrict__ f, int n_o,
-                                                   const double* __restrict__ phi, int S, size_t ng,
-                                                   size_t pb, double* __restrict__ part) {
-  constexpr int NL = PJ_S * PJ_T / 256;          // phi values per thread and tile
-  constexpr int NF = (NO * PJ_T + 255) / 256;    // field values per thread and tile
-  __shared__ double lp[PJ_S][PJ_T + 1];
-  __shared__ double lf[NO][PJ_T];
-  const int t = threadIdx.x, so = t % PJ_S, h = t / PJ_S;
-  const int s0 = blockIdx.y * PJ_S, s = s0 + so;
-  const size_t r0 = (size_t)blockIdx.x * pb, r1 = min(ng, r0 + pb);
-  double rp[NL], rf[NF];
-  auto load = [&](size_t rb) {
-#pragma unroll
-    for (int k = 0; k < NL; ++k) {
-      const int e = t + 256 * k, row = e / PJ_T, c = e % PJ_T;
-      const int sr = min(s0 + row, S - 1);      // rows past S: in-range data, never used
-      rp[k] = phi[(size_t)sr * ng + rb + c];
-    }
-#pragma unroll
-    for (int k = 0; k < NF; ++k) {
-      const int e = t + 256 * k, i = min(e / PJ_T, n_o - 1), c = e % PJ_T;
-      rf[k] = f[(size_t)i * ng + rb + c];
-    }
-  };
-  double acc[NO];
-#pragma unroll
-  for (int i = 0; i < NO; ++i) acc[i] = 0;
-  if (r0 < r1) load(r0);
-  for (size_t rb = r0; rb < r1; rb += PJ_T) {
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < NL; ++k) {
-      const int e = t + 256 * k;
-      lp[e / PJ_T][e % PJ_T] = rp[k];
-    }
-#pragma unroll
-    for (int k = 0; k < NF; ++k) {
-      const int e = t + 256 * k;
-      if (e < NO * PJ_T) lf[e / PJ_T][e % PJ_T] = (e / PJ_T < n_o) ? rf[k] : 0.0;
-    }
-    __syncthreads();
-    if (rb + PJ_T < r1) load(rb + PJ_T);
-#pragma unroll 4
-    for (int c = h * (PJ_T / 2); c < (h + 1) * (PJ_T / 2); ++c) {
-      const double v = lp[so][c];
-#pragma unroll
-      for (int i = 0; i < NO; ++i) acc[i] += v * lf[i][c];
-    }
-  }
-  // second half's sums into the first's (fixed order), through LDS
-  __syncthreads();
-  double* red = &lp[0][0];                        // PJ_S * NO <= PJ_S * (PJ_T + 1)
-  if (h == 1)
-#pragma unroll
-    for (int i = 0; i < NO; ++i) red[i * PJ_S + so] = acc[i];
-  __syncthreads();
-  if (h == 0 && s < S) {
-    double* out = part + (size_t)blockIdx.x * n_o * S;
-#pragma unroll
-    for (int i = 0; i < NO; ++i)
-      if (i < n_o) out[(size_t)i * S + s] = acc[i] + red[i * PJ_S + so];
-  }
-}
-
-// C[k] = dv sum_x part[x][k]: a block sums 8 outputs in 32 slices of x
-// (slice j: x = j, j + 32, ...) and adds the slices in order
-__global__ void __launch_bounds__(256) k_proj_reduce(const double* __restrict__ part, int nx, int MN,
-                                                     double dv, double* __restrict__ C) {
-  __shared__ double red[32][8];
-  const int o = threadIdx.x & 7, j = threadIdx.x >> 3;
-  const int k = blockIdx.x * 8 + o;
-  double acc = 0;
-  if (k < MN)
-    for (int x = j; x < nx; x += 32) acc += part[(size_t)x * MN + k];
-  red[j][o] = acc;
-  __syncthreads();
-  if (j == 0 && k < MN) {
-    double sum = 0;
-#pragma unroll
-    for (int q = 0; q < 32; ++q) sum += red[q][o];
-    C[k] = sum * dv;
-  }
-}
-
-// mixed-representation Chebyshev step for polarisation p: fn = 2 (af - b fc)/a
-// - fp (first: (af - b fc)/a) over len values, with the block partials
-// dv <fc|fc> and dv <fn|fc> into part[blk][p] and part[blk][3 + p]
-__global__ void __launch_bounds__(256) k_mixed_cheb_update(const double* __restrict__ af,
-                                                           const double* __restrict__ fc,
-                                                           const double* __restrict__ fp,
-                                                           double* __restrict__ fn, size_t len,
-                                                           double ia, double b, int first, double dv,
-                                                           int p, double* __restrict__ part) {
-  double c0 = 0, c1 = 0;
-  // four values per thread and iteration (double2 accesses), scalar tail
-  const size_t len4 = len & ~(size_t)3;
-  for (size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4; i < len4; i += (size_t)gridDim.x * 256 * 4) {
-    const double2 a0 = *reinterpret_cast<const double2*>(af + i);
-    const double2 a1 = *reinterpret_cast<const double2*>(af + i + 2);
-    const double2 u0 = *reinterpret_cast<const double2*>(fc + i);
-    const double2 u1 = *reinterpret_cast<const double2*>(fc + i + 2);
-    double2 p0 = make_double2(0.0, 0.0), p1 = p0;
-    if (!first) {
-      p0 = *reinterpret_cast<const double2*>(fp + i);
-      p1 = *reinterpret_cast<const double2*>(fp + i + 2);
-    }
-    const double cv[4] = {u0.x, u0.y, u1.x, u1.y};
-    const double av[4] = {a0.x, a0.y, a1.x, a1.y};
-    const double pv[4] = {p0.x, p0.y, p1.x, p1.y};
-    double nv[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const double t = (av[q] - b * cv[q]) * ia;
-      nv[q] = first ? t : 2.0 * t - pv[q];
-      c0 += cv[q] * cv[q];
-      c1 += nv[q] * cv[q];
-    }
-    *reinterpret_cast<double2*>(fn + i) = make_double2(nv[0], nv[1]);
-    *reinterpret_cast<double2*>(fn + i + 2) = make_double2(nv[2], nv[3]);
-  }
-  for (size_t i = len4 + (size_t)blockIdx.x * 256 + threadIdx.x; i < len; i += (size_t)gridDim.x * 256) {
-    const double cur = fc[i];
-    const double t = (af[i] - b * cur) * ia;
-    const double nx = first ? t : 2.0 * t - fp[i];
-    fn[i] = nx;
-    c0 += cur * cur;
-    c1 += nx * cur;
-  }
-  __shared__ double r0[256], r1[256];
-  r0[threadIdx.x] = c0;
-  r1[threadIdx.x] = c1;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) {
-      r0[threadIdx.x] += r0[threadIdx.x + s];
-      r1[threadIdx.x] += r1[threadIdx.x + s];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    part[(size_t)blockIdx.x * 6 + p] = r0[0] * dv;
-    part[(size_t)blockIdx.x * 6 + 3 + p] = r1[0] * dv;
-  }
+  for (int v = 0; v < NV; ++v) out[v * set + e] = s[v];
 }
 
 // f0_j(r) = (r_axis - centre) phi_j(r), before the occupied-space projection
@@ -937,29 +740,6 @@ hipError_t launch_products(const double* phi, const int* pq, int K, size_t ng, T
 }
 template hipError_t launch_products<double>(const double*, const int*, int, size_t, double*, hipStream_t);
 
-size_t gemm_chunk(int M, int N, size_t K) {
-  const size_t tiles = (size_t)((M + G_BM - 1) / G_BM) * ((N + G_BN - 1) / G_BN);
-  size_t chunk = 4096;
-  while (tiles * ((K + chunk - 1) / chunk) > 4096 && chunk < K) chunk *= 2;
-  return chunk;
-}
-size_t gemm_part_elems(int M, int N, size_t K) {
-  const size_t chunk = gemm_chunk(M, N, K);
-  return ((K + chunk - 1) / chunk) * (size_t)M * N;
-}
-
-
-hipError_t launch_gemm_f64(const double* A, int M, const double* B, int N, size_t K, double scale,
-                           double* part, double* C, hipStream_t st) {
-  const size_t chunk = gemm_chunk(M, N, K);
-  const int nchunk = (int)((K + chunk - 1) / chunk);
-  dim3 g((M + G_BM - 1) / G_BM, (N + G_BN - 1) / G_BN, nchunk);
-  hipLaunchKernelGGL(k_gemm_f64, g, dim3(256), 0, st, A, M, B, N, K, chunk, part);
-  hipLaunchKernelGGL((k_part_sum<double>), dim3((M * N + 255) / 256), dim3(256), 0, st, part,
-                     nchunk, M * N, scale, C);
-  return hipGetLastError();
-}
-
 hipError_t launch_assemble_a(const double* X, const double* D, int no, int nc, int nij,
                              const double* eps_v, const double* eps_c, double scissors, double* A,
                              hipStream_t st) {
@@ -979,57 +759,41 @@ hipError_t launch_gemv(const double* A, int n, const double* v, double* y, hipSt
   hipLaunchKernelGGL(k_gemv, dim3(n), dim3(256), 0, st, A, n, v, y);
   return hipGetLastError();
 }
-hipError_t launch_mixed_density(const double* phv, const double* f, int n_o, size_t ng, double* rho,
+hipError_t launch_mixed_density(const double* phv, const double* f, int n_o, int n_vec, size_t ng, double* rho,
                                 hipStream_t st) {
-  hipLaunchKernelGGL(k_mixed_density, dim3((unsigned)((ng + 255) / 256)), dim3(256), 0, st, phv, f, n_o,
+  hipLaunchKernelGGL(k_mixed_density, dim3((unsigned)((ng + 255) / 256), n_vec), dim3(256), 0, st, phv, f, n_o,
                      ng, rho);
+  return hipGetLastError();
+}
+template <int NV>
+static hipError_t combine_go(int n_o, hipStream_t st, const double* f, const double* tf, const double* vext,
+                             const double* eps_v, double scissors, const double* dv, const double* phv,
+                             const double* wij, size_t ng, double* out) {
+  const dim3 g((unsigned)((ng + 255) / 256)), b(256);
+#define BSE_COMBINE(NO)                                                                                          \
+  case NO:                                                                                                       \
+    hipLaunchKernelGGL((k_mixed_combine_all<NO, NV>), g, b, 0, st, f, tf, vext, eps_v, scissors, dv, phv, wij,   \
+                       ng, out);                                                                                 \
+    break;
+  // one thread per point up to 12 fields (three sets of 12 are 144 registers
+  // of values), a thread per point and field beyond
+  switch (n_o) {
+    BSE_COMBINE(1) BSE_COMBINE(2) BSE_COMBINE(3) BSE_COMBINE(4) BSE_COMBINE(5) BSE_COMBINE(6)
+    BSE_COMBINE(7) BSE_COMBINE(8) BSE_COMBINE(9) BSE_COMBINE(10) BSE_COMBINE(11) BSE_COMBINE(12)
+    default:
+      hipLaunchKernelGGL(k_mixed_combine<NV>, dim3(g.x, n_o), b, 0, st, f, tf, vext, eps_v, scissors, dv, phv, wij,
+                         n_o, ng, out);
+  }
+#undef BSE_COMBINE
   return hipGetLastError();
 }
 hipError_t launch_mixed_combine(const double* f, const double* tf, const double* vext,
                                 const double* eps_v, double scissors, const double* dv,
-                                const double* phv, const double* wij, int n_o, size_t ng,
+                                const double* phv, const double* wij, int n_o, int n_vec, size_t ng,
                                 double* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_mixed_combine, dim3((unsigned)((ng + 255) / 256), n_o), dim3(256), 0, st, f, tf,
-                     vext, eps_v, scissors, dv, phv, wij, n_o, ng, out);
-  return hipGetLastError();
-}
-hipError_t launch_project_out(double* out, int n_o, const double* phi, int S, const double* C,
-                              size_t ng, hipStream_t st) {
-  if (n_o < 1 || S < 1) return hipErrorInvalidValue;
-  const dim3 g((unsigned)((ng + 255) / 256)), b(256);
-  if (n_o <= 8)
-    hipLaunchKernelGGL(k_project_out<8>, g, b, 0, st, out, n_o, phi, S, C, ng);
-  else if (n_o <= 16)
-    hipLaunchKernelGGL(k_project_out<16>, g, b, 0, st, out, n_o, phi, S, C, ng);
-  else
-    hipLaunchKernelGGL(k_project_out<32>, g, b, 0, st, out, n_o, phi, S, C, ng);
-  return hipGetLastError();
-}
-size_t proj_part_elems(int n_o, int S) { return (size_t)PJ_BLK * n_o * S; }
-hipError_t launch_proj_coef(const double* f, int n_o, const double* phi, int S, size_t ng, double dv,
-                            double* part, double* C, hipStream_t st) {
-  if (n_o < 1 || n_o > 32 || S < 1 || ng % PJ_T) return hipErrorInvalidValue;
-  // PJ_BLK point ranges, each a multiple of the tile
-  const size_t pb = ((ng + PJ_BLK - 1) / PJ_BLK + PJ_T - 1) / PJ_T * PJ_T;
-  const int nx = (int)((ng + pb - 1) / pb);
-  const dim3 g(nx, (S + PJ_S - 1) / PJ_S), b(256);
-  if (n_o <= 8)
-    hipLaunchKernelGGL(k_proj_coef<8>, g, b, 0, st, f, n_o, phi, S, ng, pb, part);
-  else if (n_o <= 16)
-    hipLaunchKernelGGL(k_proj_coef<16>, g, b, 0, st, f, n_o, phi, S, ng, pb, part);
-  else
-    hipLaunchKernelGGL(k_proj_coef<32>, g, b, 0, st, f, n_o, phi, S, ng, pb, part);
-  const int MN = n_o * S;
-  hipLaunchKernelGGL(k_proj_reduce, dim3((MN + 7) / 8), dim3(256), 0, st, part, nx, MN, dv, C);
-  return hipGetLastError();
-}
-int mixed_cheb_blocks() { return 256; }
-hipError_t launch_mixed_cheb_update(const double* af, const double* fc, const double* fp, double* fn,
-                                    size_t len, double a, double b, int first, double dv, int p,
-                                    double* part, hipStream_t st) {
-  hipLaunchKernelGGL(k_mixed_cheb_update, dim3(mixed_cheb_blocks()), dim3(256), 0, st, af, fc, fp, fn,
-                     len, 1.0 / a, b, first, dv, p, part);
-  return hipGetLastError();
+  if (n_vec == 1) return combine_go<1>(n_o, st, f, tf, vext, eps_v, scissors, dv, phv, wij, ng, out);
+  if (n_vec == 3) return combine_go<3>(n_o, st, f, tf, vext, eps_v, scissors, dv, phv, wij, ng, out);
+  return hipErrorInvalidValue;
 }
 hipError_t launch_mixed_dipole(const double* phv, int n_o, int n, double h, int axis, double* f,
                                hipStream_t st) {
