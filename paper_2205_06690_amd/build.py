@@ -21,8 +21,8 @@ OUT_DIR = os.path.join(PKG, "_lib")
 LIB = os.path.join(OUT_DIR, "libbse.so")
 BUILD = os.path.join(ROOT, "_build")
 
-SOURCES = ["prop_kernels.hip", "clean_mfma.hip", "clean_f64.hip", "cheb_f64.hip", "gemm_f64.hip", "contract_mfma.hip", "bse_kernels.hip",
-           "fno_kernels.hip", "bse_capi.cpp", "fno.cpp", "host_math.cpp"]
+SOURCES = ["prop_kernels.hip", "kin_mfma.hip", "clean_mfma.hip", "clean_f64.hip", "cheb_f64.hip", "gemm_f64.hip",
+           "contract_mfma.hip", "bse_kernels.hip", "fno_kernels.hip", "bse_capi.cpp", "fno.cpp", "host_math.cpp"]
 # plain C++ host code (no device code): compiled as C++, not as HIP
 HOST_ONLY = ("host_math.cpp",)
 

@@ -17,6 +17,7 @@
 #include "../../include/bse.h"
 #include "bse_kernels.h"
 #include "prop_kernels.h"
+#include "kin_mfma.h"
 #include "clean_mfma.h"
 #include "clean_f64.h"
 #include "cheb_f64.h"
@@ -118,7 +119,7 @@ struct Timer {
 };
 
 struct Tables {
-  DBuf tw, kph, pf, ph, k2;
+  DBuf tw, kph, kin, pf, ph, k2;
 };
 
 }  // namespace
@@ -244,6 +245,14 @@ void upload_tables(bse_system* s, Tables& tb) {
   tb.tw.alloc(sizeof(C) * n);
   tb.kph.alloc(sizeof(C) * n);
   tb.k2.alloc(sizeof(T) * n);
+  if constexpr (std::is_same<T, double>::value) {
+    if (kin_yz_grid(n)) {
+      std::vector<double> km;
+      kin_table(n, h, dt, km);
+      tb.kin.alloc(sizeof(double) * km.size());
+      HIPC(hipMemcpy(tb.kin.p, km.data(), sizeof(double) * km.size(), hipMemcpyHostToDevice));
+    }
+  }
   tb.pf.alloc(sizeof(C) * s->ng);
   tb.ph.alloc(sizeof(C) * s->ng);
   HIPC(hipMemcpy(tb.tw.p, tw.data(), sizeof(C) * n, hipMemcpyHostToDevice));
@@ -285,7 +294,9 @@ void ensure_batch(bse_system* s, int B) {
   const int S = s->cfg.n_occ;
   s->d.alloc(sizeof(C) * ng * (size_t)B * L);
   s->u.alloc(sizeof(T) * ng * B);
-  s->dens.alloc(sizeof(T) * ng * B);
+  int rows = B;        // densities of any batch up to B, in parts
+  for (int b = 1; b <= B; ++b) rows = std::max(rows, b * prop_yz_parts<T>(s->n, b));
+  s->dens.alloc(sizeof(T) * ng * rows);
   s->wpol.alloc(sizeof(double) * ng * B);
   s->q.alloc(sizeof(double) * ng * B);
   s->rho64.alloc(sizeof(double) * ng * B);
@@ -349,10 +360,11 @@ void clean(bse_system* s, int B, int from_mid, const cplx<T>* H) {
 }
 
 template <typename T>
-void poissonT(bse_system* s, int B, double* acc, double wn) {
+void poissonT(bse_system* s, int B, double* acc, double wn, int parts = 1) {
   Tables& tb = tabs<T>(s);
   PoisArgs<T> a{};
   a.rho = s->dens.as<T>();
+  a.parts = parts;
   a.B = B;
   a.work = s->work.as<cplx<T>>();
   a.tw = tb.tw.as<cplx<T>>();
@@ -381,6 +393,7 @@ struct PropRun {
   const int* pq_dev;
   const cplx<T>* hcur;   // H_n
   bool half;             // the state is an end-of-step state (t = 0 or just cleaned)
+  int parts;             // parts of the density the plane pass leaves
 };
 
 template <typename T>
@@ -451,6 +464,7 @@ void prop_unperturbed_step(PropRun<T>& r, int n, hipStream_t st) {
   pe.ph = tb.ph.as<C>();
   pe.tw = tb.tw.as<C>();
   pe.kph = tb.kph.as<C>();
+  pe.kin = tb.kin.as<C>();
   pe.dt = (T)s->cfg.dt;
   pe.L = s->L;
   pe.mode = PX_ETA0;
@@ -461,6 +475,8 @@ void prop_unperturbed_step(PropRun<T>& r, int n, hipStream_t st) {
   pze.d = hnext;
   pze.tw = tb.tw.as<C>();
   pze.kph = tb.kph.as<C>();
+  pze.kin = tb.kin.as<C>();
+  pze.parts = 1;
   pze.L = s->L;
   pze.density = 0;
   pze.order = y.order;
@@ -482,6 +498,7 @@ PropXArgs<T> prop_pair_x_args(bse_system* s, const cplx<T>* hcur, bool half) {
   px.H = hcur;
   px.tw = tb.tw.as<C>();
   px.kph = tb.kph.as<C>();
+  px.kin = tb.kin.as<C>();
   px.dt = (T)s->cfg.dt;
   px.L = s->L;
   px.mode = half ? PX_HALF : PX_FULL;
@@ -498,7 +515,9 @@ PropYZArgs<T> prop_pair_yz_args(bse_system* s, const cplx<T>* hnext) {
   pz.H = hnext;
   pz.tw = tb.tw.as<C>();
   pz.kph = tb.kph.as<C>();
+  pz.kin = tb.kin.as<C>();
   pz.dens = s->dens.as<T>();
+  pz.parts = 1;
   pz.L = s->L;
   pz.density = 1;
   pz.order = y.order;
@@ -514,7 +533,8 @@ void prop_pair_passes(PropRun<T>& r, int n) {
   auto* t1 = s->timer.slot("prop_x", 1);
   const LaunchEvents e1{t1 ? t1->first : nullptr, t1 ? t1->second : nullptr};
   HIPC(launch_prop_x<T>(s->n, px, r.B, s->stream, s->tune_tc, t1 ? &e1 : nullptr));
-  const PropYZArgs<T> pz = prop_pair_yz_args<T>(s, prop_hbuf<T>(s, n + 1));
+  PropYZArgs<T> pz = prop_pair_yz_args<T>(s, prop_hbuf<T>(s, n + 1));
+  pz.parts = r.parts;
   const YZSched y = yz_sched<T>(s);
   const bool split = !y.fused && prop_yz_split<T>(s->n);
   auto* t2 = s->timer.slot(split ? "prop_z" : "prop_yz", 1);
@@ -535,10 +555,10 @@ void prop_after_passes(PropRun<T>& r, int n) {
   const bool do_clean = M > 0 && ((n + 1) % M == 0);
   const double wn = s->wts[n + 1];
   if (!do_clean) {
-    poissonT<T>(s, B, s->wpol.as<double>(), wn);
+    poissonT<T>(s, B, s->wpol.as<double>(), wn, r.parts);
     r.half = false;
   } else {
-    poissonT<T>(s, B, nullptr, 0.0);
+    poissonT<T>(s, B, nullptr, 0.0, r.parts);
     clean<T>(s, B, 1, hnext);
     // the check point of Eq. 15: the unperturbed set must keep the norms
     // of eta_l(0) under the unitary propagation
@@ -552,7 +572,7 @@ void prop_after_passes(PropRun<T>& r, int n) {
 
 template <typename T>
 void propagate_batch(bse_system* s, int B, const int* pq_dev) {
-  PropRun<T> r{s, B, pq_dev, nullptr, true};
+  PropRun<T> r{s, B, pq_dev, nullptr, true, prop_yz_parts<T>(s->n, B)};
   prop_begin<T>(r);
   for (int n = 0; n < s->cfg.n_steps; ++n) {
     prop_pair_passes<T>(r, n);   // with the unperturbed set's step
@@ -1404,6 +1424,7 @@ void autotune_t(bse_system* s, int B, const char* cache_path) {
   HIPC(launch_fill_zero(s->u.p, sizeof(T) * s->ng * (size_t)B, s->stream));
   PropXArgs<T> px = prop_pair_x_args<T>(s, s->h0.as<C>(), false);
   PropYZArgs<T> pz = prop_pair_yz_args<T>(s, s->h0.as<C>());
+  pz.parts = prop_yz_parts<T>(s->n, B);
   float best_x = 1e30f, best_yz = 1e30f;
   int tc_best = 0, nt_best = 0, ox_best = 0, sched_best = -1, oz_best = 0;
   for (int ox : {0, 1})
@@ -1522,7 +1543,7 @@ void batch_list_run(int n_sys, bse_system* const* sys, const int32_t* n_pairs, v
                     const BatchList& bl, hipStream_t st) {
   std::vector<PropRun<float>> runs(n_sys);
   for (int i = 0; i < n_sys; ++i) {
-    runs[i] = PropRun<float>{sys[i], n_pairs[i], sys[i]->pq_d.as<int>(), nullptr, true};
+    runs[i] = PropRun<float>{sys[i], n_pairs[i], sys[i]->pq_d.as<int>(), nullptr, true, 1};
     prop_begin<float>(runs[i]);
   }
   const int N = sys[0]->cfg.n_steps;
@@ -1662,8 +1683,8 @@ std::vector<const void*> workspace_signature(const bse_system* s) {
                         &s->part, &s->part32, &s->gpart, &s->coef, &s->coefE, &s->E, &s->flags,
                         &s->pscale, &s->normpart, &s->phi64, &s->phi_occ32, &s->phih, &s->phil,
                         &s->phith, &s->phitl, &s->eta0, &s->h0, &s->hbuf, &s->n0,
-                        &s->tf.tw, &s->tf.kph, &s->tf.pf, &s->tf.ph, &s->tf.k2,
-                        &s->td.tw, &s->td.kph, &s->td.pf, &s->td.ph, &s->td.k2};
+                        &s->tf.tw, &s->tf.kph, &s->tf.kin, &s->tf.pf, &s->tf.ph, &s->tf.k2,
+                        &s->td.tw, &s->td.kph, &s->td.kin, &s->td.pf, &s->td.ph, &s->td.k2};
   std::vector<const void*> sig;
   for (const DBuf* b : bufs) sig.push_back(b->p);
   sig.push_back(reinterpret_cast<const void*>((uintptr_t)s->cap_b));

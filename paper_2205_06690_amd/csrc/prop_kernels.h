@@ -6,6 +6,32 @@
 
 namespace bse {
 
+// The (field, tile) of a workgroup.  Order 0: a 2-D grid (fields, tiles),
+// field fastest, so that the fields of one tile run close together.  Order
+// 1: a 1-D grid renumbered so that XCD x (workgroup ids are dealt round-robin
+// to the eight XCDs, x = id mod 8) walks its own contiguous range of
+// (tile, field) with the field fastest: the fields of a tile then share one
+// XCD's L2 for the tile's shared operands (the unperturbed orbitals, the
+// phase tables) instead of each of the eight L2s fetching them.
+__device__ __forceinline__ bool field_tile(int order, int nf, int ntile, int& f, int& tile) {
+  if (order == 0) {
+    f = blockIdx.x;
+    tile = blockIdx.y;
+    return true;
+  }
+  const unsigned id = blockIdx.x, per = gridDim.x >> 3;
+  const unsigned v = (id & 7u) * per + (id >> 3);
+  if (v >= (unsigned)nf * (unsigned)ntile) return false;
+  f = (int)(v % (unsigned)nf);
+  tile = (int)(v / (unsigned)nf);
+  return true;
+}
+inline dim3 field_tile_grid(int order, int nf, int ntile) {
+  if (order == 0) return dim3(nf, ntile);
+  const unsigned n = (unsigned)nf * (unsigned)ntile;
+  return dim3(8 * ((n + 7) / 8));
+}
+
 enum { PX_ETA0 = 0, PX_FULL = 1, PX_HALF = 2 };
 
 template <typename T> struct PropXArgs {
@@ -17,11 +43,13 @@ template <typename T> struct PropXArgs {
   const cplx<T>* H;    // unperturbed mid-step state [L][ng]
   const cplx<T>* tw;   // twiddles exp(-2 pi i m/N)
   const cplx<T>* kph;  // exp(-i k^2 dt/2) / N per frequency index
+  const cplx<T>* kin;  // FP64: the axis' exp(-i k^2 dt/2) as matrices (kin_table)
   T dt;
   int L;
   int mode;
-  int order;           // workgroup order: 0 field fastest on a 2-D grid, 1 XCD-grouped (see launch_order)
+  int order;           // workgroup order: 0 field fastest on a 2-D grid, 1 XCD-grouped (see field_tile)
   int nf;              // fields (or pairs) of the launch; set by the launcher
+  int ls;              // groups of a pair's orbitals, workgroups apart; set by the launcher
 };
 
 template <typename T> struct PropYZArgs {
@@ -29,7 +57,9 @@ template <typename T> struct PropYZArgs {
   const cplx<T>* H;
   const cplx<T>* tw;
   const cplx<T>* kph;
-  T* dens;
+  const cplx<T>* kin;  // as PropXArgs::kin
+  T* dens;             // [parts][B][ng]
+  int parts;           // 1, or prop_yz_parts(n, B): partial sums, unscaled
   int L;
   int density;
   int order;           // workgroup order of the y-line pass, as PropXArgs::order
@@ -38,7 +68,8 @@ template <typename T> struct PropYZArgs {
 };
 
 template <typename T> struct PoisArgs {
-  const T* rho;        // [B][ng] real densities
+  const T* rho;        // [B][ng] real densities; parts > 1: 4 times the sum of [parts][B][ng]
+  int parts;           // partial densities of a plane pass (0 as 1)
   int B;
   cplx<T>* work;       // [(B+1)/2][ng]
   const cplx<T>* tw;
@@ -98,6 +129,8 @@ template <typename T> hipError_t launch_prop_x(int n, const PropXArgs<T>& a, int
 template <typename T> hipError_t launch_prop_yz(int n, const PropYZArgs<T>& a, int nb, hipStream_t st, int nt = 0,
                                                 const LaunchEvents* ev = nullptr,
                                                 const LaunchEvents* ev2 = nullptr);
+// parts of the density the plane pass leaves for B pairs
+template <typename T> int prop_yz_parts(int n, int B);
 // Work lists of uneven batches (FP32): one launch of a propagation pass walks
 // the items of every listed system of one grid size, (pair, x tile) for the
 // x pass and (x plane, pair) for the plane pass, systems in order with

@@ -15,6 +15,7 @@
 #include "prop_kernels.h"
 #include "clean_mfma.h"
 #include "clean_f64.h"
+#include "kin_mfma.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -62,32 +63,6 @@ __device__ __forceinline__ void kinetic_x_tile(cplx<T>* s, const cplx<T>* __rest
 // stage B runs through LDS; stage C reads its N1 slots back and the results
 // go straight to HBM.  The pair variant keeps u_b in registers across the L
 // orbitals and has the next orbital's loads in flight during the transform.
-// The (field, tile) of a workgroup.  Order 0: a 2-D grid (fields, tiles),
-// field fastest, so that the fields of one tile run close together.  Order
-// 1: a 1-D grid renumbered so that XCD x (workgroup ids are dealt round-robin
-// to the eight XCDs, x = id mod 8) walks its own contiguous range of
-// (tile, field) with the field fastest: the fields of a tile then share one
-// XCD's L2 for the tile's shared operands (the unperturbed orbitals, the
-// phase tables) instead of each of the eight L2s fetching them.
-__device__ __forceinline__ bool field_tile(int order, int nf, int ntile, int& f, int& tile) {
-  if (order == 0) {
-    f = blockIdx.x;
-    tile = blockIdx.y;
-    return true;
-  }
-  const unsigned id = blockIdx.x, per = gridDim.x >> 3;
-  const unsigned v = (id & 7u) * per + (id >> 3);
-  if (v >= (unsigned)nf * (unsigned)ntile) return false;
-  f = (int)(v % (unsigned)nf);
-  tile = (int)(v / (unsigned)nf);
-  return true;
-}
-inline dim3 field_tile_grid(int order, int nf, int ntile) {
-  if (order == 0) return dim3(nf, ntile);
-  const unsigned n = (unsigned)nf * (unsigned)ntile;
-  return dim3(8 * ((n + 7) / 8));
-}
-
 // One (field or pair fb, tile of TC columns) of the x pass, by a block of
 // 256 threads on LDS s (x_lds bytes); shared by the per-system kernel and the
 // work-list kernel of uneven batches.
@@ -934,8 +909,19 @@ __global__ void __launch_bounds__(NT) k_poisson_yz_fwd(PoisArgs<T> a) {
   const T i0 = a.pscale ? (T)(1.0 / a.pscale[b0]) : (T)1;
   const T i1 = (a.pscale && r1) ? (T)(1.0 / a.pscale[b1]) : (T)1;
   int bad0 = 0, bad1 = 0;
-  for (int e = tid; e < P; e += NT)
-    s[plane_idx<N>(e)] = load_pair<C>(r0[e] * i0, r1 ? r1[e] * i1 : (T)0, a.flags != nullptr, bad0, bad1);
+  const size_t ps = (size_t)a.B * ng;
+  for (int e = tid; e < P; e += NT) {
+    T v0 = r0[e], v1 = r1 ? r1[e] : (T)0;
+    if (a.parts > 1) {
+      for (int k = 1; k < a.parts; ++k) {
+        v0 += r0[k * ps + e];
+        if (r1) v1 += r1[k * ps + e];
+      }
+      v0 *= (T)4;
+      v1 *= (T)4;
+    }
+    s[plane_idx<N>(e)] = load_pair<C>(v0 * i0, v1 * i1, a.flags != nullptr, bad0, bad1);
+  }
   flag_bad(a.flags, b0, b1, bad0, bad1);
   __syncthreads();
   NoMul nm;
@@ -1460,6 +1446,9 @@ hipError_t launch_prop_yz_list(int n, const YZListSys* list, int nsys, unsigned 
 
 template <int N, typename T>
 struct Launch {
+  // FP64 takes the matrix products (kin_mfma.hip) where they are the faster
+  static constexpr bool KIN_X = std::is_same<T, double>::value && N <= 32;
+  static constexpr bool KIN_YZ = std::is_same<T, double>::value && N <= 64;
   // plain launch, or one that records ev's events in its own dispatch
   template <typename K, typename A>
   static void go(K kern, dim3 grid, dim3 block, size_t sm, hipStream_t st, const LaunchEvents* ev, const A& a) {
@@ -1486,12 +1475,16 @@ struct Launch {
   }
   // F: fields (unperturbed set) or pairs (perturbed set); tc 0 = default
   static hipError_t prop_x(const PropXArgs<T>& a, int F, hipStream_t st, int tc, const LaunchEvents* ev) {
-    if (tc == 0) tc = x_tc<N>();
-    switch (tc) {
-      case 16: return prop_x_tc<16>(a, F, st, ev);
-      case 32: return prop_x_tc<32>(a, F, st, ev);
-      case 64: return prop_x_tc<64>(a, F, st, ev);
-      default: return hipErrorInvalidValue;
+    if constexpr (KIN_X) {
+      return launch_kin_x(N, a, F, st, tc, ev);
+    } else {
+      if (tc == 0) tc = x_tc<N>();
+      switch (tc) {
+        case 16: return prop_x_tc<16>(a, F, st, ev);
+        case 32: return prop_x_tc<32>(a, F, st, ev);
+        case 64: return prop_x_tc<64>(a, F, st, ev);
+        default: return hipErrorInvalidValue;
+      }
     }
   }
   template <int NT>
@@ -1552,12 +1545,17 @@ struct Launch {
   static hipError_t prop_yz(const PropYZArgs<T>& a, int nb, hipStream_t st, int nt, const LaunchEvents* ev,
                             const LaunchEvents* ev2) {
     if (a.fused && yz_reg()) return prop_yz_reg(a, nb, st, ev);   // 1 cross-lane, 2 transposed
-    if constexpr (yz_split()) return prop_zy(a, nb, st, ev, ev2);
-    if (nt == 0) nt = yz_threads<N>();
-    switch (nt) {
-      case 256: return prop_yz_nt<256>(a, nb, st, ev);
-      case 512: return prop_yz_nt<512>(a, nb, st, ev);
-      default: return hipErrorInvalidValue;
+    if constexpr (yz_split()) {
+      return prop_zy(a, nb, st, ev, ev2);
+    } else if constexpr (KIN_YZ) {
+      return launch_kin_yz(N, a, nb, st, nt, ev);
+    } else {
+      if (nt == 0) nt = yz_threads<N>();
+      switch (nt) {
+        case 256: return prop_yz_nt<256>(a, nb, st, ev);
+        case 512: return prop_yz_nt<512>(a, nb, st, ev);
+        default: return hipErrorInvalidValue;
+      }
     }
   }
   static hipError_t poisson(const PoisArgs<T>& a, hipStream_t st) {
@@ -1603,11 +1601,17 @@ struct Launch {
     constexpr int TC = x_tc<N>();
     const int smp = (int)yz_lds<N, T>();
     const int smx = (int)x_lds<N, TC, T>();
-    conf_x<16>();
-    conf_x<32>();
-    conf_x<64>();
-    conf_yz<256>();
-    conf_yz<512>();
+    if constexpr (!KIN_X) {
+      conf_x<16>();
+      conf_x<32>();
+      conf_x<64>();
+    }
+    if constexpr (KIN_YZ) {
+      configure_kin(N);
+    } else {
+      conf_yz<256>();
+      conf_yz<512>();
+    }
     if constexpr (yz_lds<N, T>() <= 160 * 1024) {
       (void)hipFuncSetAttribute((const void*)k_poisson_yz_fwd<N, T, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, smp);
       (void)hipFuncSetAttribute((const void*)k_poisson_yz_inv<N, T, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, smp);
@@ -1663,6 +1667,10 @@ template <typename T>
 hipError_t launch_prop_yz(int n, const PropYZArgs<T>& a, int nb, hipStream_t st, int nt,
                           const LaunchEvents* ev, const LaunchEvents* ev2) {
   BSE_DISPATCH_N(n, T, prop_yz(a, nb, st, nt, ev, ev2));
+}
+template <typename T>
+int prop_yz_parts(int n, int B) {
+  return std::is_same<T, double>::value ? kin_yz_parts(n, B) : 1;
 }
 template <typename T>
 bool prop_yz_split(int n) {
@@ -1821,6 +1829,7 @@ hipError_t launch_to_real(const double* in, size_t n, T* out, hipStream_t st) {
                                        const LaunchEvents*);                                     \
   template hipError_t launch_prop_yz<T>(int, const PropYZArgs<T>&, int, hipStream_t, int,      \
                                         const LaunchEvents*, const LaunchEvents*);               \
+  template int prop_yz_parts<T>(int, int);                                                     \
   template bool prop_yz_split<T>(int);                                                         \
   template bool prop_yz_fused<T>(int);                                                         \
   template hipError_t launch_poisson<T>(int, const PoisArgs<T>&, hipStream_t);                 \
