@@ -295,7 +295,7 @@ void ensure_batch(bse_system* s, int B) {
   s->d.alloc(sizeof(C) * ng * (size_t)B * L);
   s->u.alloc(sizeof(T) * ng * B);
   int rows = B;        // densities of any batch up to B, in parts
-  for (int b = 1; b <= B; ++b) rows = std::max(rows, b * prop_yz_parts<T>(s->n, b));
+  for (int b = 1; b <= B; ++b) rows = std::max(rows, b * prop_yz_parts<T>(s->n, b, L, 2, 0));
   s->dens.alloc(sizeof(T) * ng * rows);
   s->wpol.alloc(sizeof(double) * ng * B);
   s->q.alloc(sizeof(double) * ng * B);
@@ -394,6 +394,7 @@ struct PropRun {
   const cplx<T>* hcur;   // H_n
   bool half;             // the state is an end-of-step state (t = 0 or just cleaned)
   int parts;             // parts of the density the plane pass leaves
+  int busy;              // planes of the systems propagated beside this one
 };
 
 template <typename T>
@@ -529,7 +530,8 @@ template <typename T>
 void prop_pair_passes(PropRun<T>& r, int n) {
   bse_system* s = r.s;
   prop_unperturbed_step<T>(r, n, s->stream);
-  const PropXArgs<T> px = prop_pair_x_args<T>(s, r.hcur, r.half);
+  PropXArgs<T> px = prop_pair_x_args<T>(s, r.hcur, r.half);
+  px.busy = r.busy;
   auto* t1 = s->timer.slot("prop_x", 1);
   const LaunchEvents e1{t1 ? t1->first : nullptr, t1 ? t1->second : nullptr};
   HIPC(launch_prop_x<T>(s->n, px, r.B, s->stream, s->tune_tc, t1 ? &e1 : nullptr));
@@ -571,8 +573,8 @@ void prop_after_passes(PropRun<T>& r, int n) {
 }
 
 template <typename T>
-void propagate_batch(bse_system* s, int B, const int* pq_dev) {
-  PropRun<T> r{s, B, pq_dev, nullptr, true, prop_yz_parts<T>(s->n, B)};
+void propagate_batch(bse_system* s, int B, const int* pq_dev, int busy = 0) {
+  PropRun<T> r{s, B, pq_dev, nullptr, true, prop_yz_parts<T>(s->n, B, s->L, yz_sched<T>(s).fused_kind, busy), busy};
   prop_begin<T>(r);
   for (int n = 0; n < s->cfg.n_steps; ++n) {
     prop_pair_passes<T>(r, n);   // with the unperturbed set's step
@@ -1424,7 +1426,7 @@ void autotune_t(bse_system* s, int B, const char* cache_path) {
   HIPC(launch_fill_zero(s->u.p, sizeof(T) * s->ng * (size_t)B, s->stream));
   PropXArgs<T> px = prop_pair_x_args<T>(s, s->h0.as<C>(), false);
   PropYZArgs<T> pz = prop_pair_yz_args<T>(s, s->h0.as<C>());
-  pz.parts = prop_yz_parts<T>(s->n, B);
+  pz.parts = 1;
   float best_x = 1e30f, best_yz = 1e30f;
   int tc_best = 0, nt_best = 0, ox_best = 0, sched_best = -1, oz_best = 0;
   for (int ox : {0, 1})
@@ -1543,7 +1545,7 @@ void batch_list_run(int n_sys, bse_system* const* sys, const int32_t* n_pairs, v
                     const BatchList& bl, hipStream_t st) {
   std::vector<PropRun<float>> runs(n_sys);
   for (int i = 0; i < n_sys; ++i) {
-    runs[i] = PropRun<float>{sys[i], n_pairs[i], sys[i]->pq_d.as<int>(), nullptr, true, 1};
+    runs[i] = PropRun<float>{sys[i], n_pairs[i], sys[i]->pq_d.as<int>(), nullptr, true, 1, 0};
     prop_begin<float>(runs[i]);
   }
   const int N = sys[0]->cfg.n_steps;
@@ -1561,6 +1563,14 @@ void batch_list_run(int n_sys, bse_system* const* sys, const int32_t* n_pairs, v
     HIPC(launch_finite_check(w, n_pairs[i], s->ng, s->flags.as<int>(), st));
     HIPC(launch_nan_flagged(w, n_pairs[i], s->ng, s->flags.as<int>(), st));
   }
+}
+
+// planes (grid points per axis x pairs) of the systems beside system i
+int other_planes(int n_sys, bse_system* const* sys, const int32_t* n_pairs, int i) {
+  long long k = 0;
+  for (int j = 0; j < n_sys; ++j)
+    if (j != i) k += (long long)sys[j]->n * n_pairs[j];
+  return (int)std::min(k, 1LL << 20);
 }
 
 // ---------------------------------------------------------------------------
@@ -1641,9 +1651,9 @@ void apply_w_batch(int n_sys, bse_system* const* sys, const int32_t* n_pairs,
     for (int i = 0; i < n_sys && !list; ++i) {
       bse_system* s = sys[i];
       HIPC(hipStreamWaitEvent(s->stream, ev[n_sys], 0));
-      const int B = n_pairs[i];
-      if (s->cfg.precision == BSE_FP64) propagate_batch<double>(s, B, s->pq_d.as<int>());
-      else propagate_batch<float>(s, B, s->pq_d.as<int>());
+      const int B = n_pairs[i], busy = other_planes(n_sys, sys, n_pairs, i);
+      if (s->cfg.precision == BSE_FP64) propagate_batch<double>(s, B, s->pq_d.as<int>(), busy);
+      else propagate_batch<float>(s, B, s->pq_d.as<int>(), busy);
       double* w = reinterpret_cast<double*>(w_dev[i]);
       HIPC(launch_add(s->q.as<double>(), s->wpol.as<double>(), (size_t)B * s->ng, w, s->stream));
       HIPC(launch_finite_check(w, B, s->ng, s->flags.as<int>(), s->stream));
@@ -1771,9 +1781,9 @@ void plan_create(int n_sys, bse_system* const* sys, const int32_t* n_pairs, cons
     for (int i = 0; i < n_sys; ++i) {
       bse_system* s = sys[i];
       HIPC(hipStreamWaitEvent(s->stream, ev[n_sys], 0));
-      const int B = n_pairs[i];
-      if (s->cfg.precision == BSE_FP64) propagate_batch<double>(s, B, P->pq[i].as<int>());
-      else propagate_batch<float>(s, B, P->pq[i].as<int>());
+      const int B = n_pairs[i], busy = other_planes(n_sys, sys, n_pairs, i);
+      if (s->cfg.precision == BSE_FP64) propagate_batch<double>(s, B, P->pq[i].as<int>(), busy);
+      else propagate_batch<float>(s, B, P->pq[i].as<int>(), busy);
       double* w = reinterpret_cast<double*>(w_dev[i]);
       HIPC(launch_add(s->q.as<double>(), s->wpol.as<double>(), (size_t)B * s->ng, w, s->stream));
       HIPC(launch_finite_check(w, B, s->ng, s->flags.as<int>(), s->stream));

@@ -26,10 +26,10 @@ inline bool kin_x_grid(int n) { return n == 16 || n == 24 || n == 32; }
 void kin_table(int n, double h, double dt, std::vector<double>& out);
 
 // groups of orbitals whose densities the plane pass sums apart, and the parts
-// it leaves for B pairs (1, or one per group where the planes of the pairs
-// alone are few)
+// it leaves for B pairs beside busy planes of other systems (1, or one per
+// group where the planes are few)
 constexpr int kin_yz_groups(int n) { return n <= 32 ? 5 : 2; }
-int kin_yz_parts(int n, int B);
+int kin_yz_parts(int n, int B, int busy);
 
 void configure_kin(int n);
 // as launch_prop_x, launch_prop_yz

@@ -136,8 +136,7 @@ template <int N> struct KinMat {
 //   PX_ETA0: out = Pf * in                                  (unperturbed set)
 //   PX_FULL: out = Pf * (d - i dt u_b H_l)                  (mid-step state)
 //   PX_HALF: out = Ph * (d - i dt/2 u_b (Ph H_l))           (cleaned end state)
-// A wave takes 16 neighbouring columns (y, z), 128- or 256-byte rows of every
-// x, and orbitals l0, l0 + ls, ... of its pair; u_b stays in registers and the
+// A wave takes 16 neighbouring columns (y, z), a 256-byte row of every x, and orbitals l0, l0 + ls, ... of its pair; u_b stays in registers and the
 // state of the next orbital loads during the products.
 // ---------------------------------------------------------------------------
 template <int N, bool ETA>
@@ -405,7 +404,7 @@ static hipError_t kin_x_tc(const PropXArgs<double>& a, int F, hipStream_t st, co
   b.nf = F;
   // a pair's orbitals go to several waves while those are fewer than eight on
   // a SIMD (24^3, 8 pairs: 20.6 us unsplit, 9 split in ten)
-  b.ls = a.mode == PX_ETA0 ? 1 : std::max(1, std::min(a.L, 8192 / (F * (N * N / 16))));
+  b.ls = a.mode == PX_ETA0 ? 1 : std::max(1, std::min(a.L, 8192 / (F * (N * N / 16) + a.busy)));
   const dim3 grid = field_tile_grid(a.order, F * b.ls, N * N / TC);
   if (a.mode == PX_ETA0) return kin_go(k_kin_x<N, TC, true>, grid, 4 * TC, 0, st, ev, b);
   return kin_go(k_kin_x<N, TC, false>, grid, 4 * TC, 0, st, ev, b);
@@ -464,8 +463,8 @@ hipError_t launch_kin_yz(int n, const PropYZArgs<double>& a, int nb, hipStream_t
 // the chip short: up to 32 points (five groups) below two on a SIMD (32^3, 12
 // pairs: 53 us together, 34 apart), above (two groups) below six (64^3, 11
 // pairs: 329 and 319; 48^3, 12 pairs: 146 and 118).
-int kin_yz_parts(int n, int B) {
-  return kin_yz_grid(n) && (long long)B * n * n / 16 < (n <= 32 ? 2048 : 6144) ? kin_yz_groups(n) : 1;
+int kin_yz_parts(int n, int B, int busy) {
+  return kin_yz_grid(n) && ((long long)B * n + busy) * n / 16 < (n <= 32 ? 2048 : 6144) ? kin_yz_groups(n) : 1;
 }
 
 template <int N, int W> static void kin_conf_w() {

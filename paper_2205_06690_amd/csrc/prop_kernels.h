@@ -50,6 +50,7 @@ template <typename T> struct PropXArgs {
   int order;           // workgroup order: 0 field fastest on a 2-D grid, 1 XCD-grouped (see field_tile)
   int nf;              // fields (or pairs) of the launch; set by the launcher
   int ls;              // groups of a pair's orbitals, workgroups apart; set by the launcher
+  int busy;            // planes (n x pairs) of other systems that share the chip
 };
 
 template <typename T> struct PropYZArgs {
@@ -59,7 +60,7 @@ template <typename T> struct PropYZArgs {
   const cplx<T>* kph;
   const cplx<T>* kin;  // as PropXArgs::kin
   T* dens;             // [parts][B][ng]
-  int parts;           // 1, or prop_yz_parts(n, B): partial sums, unscaled
+  int parts;           // 1, or prop_yz_parts: partial sums, unscaled
   int L;
   int density;
   int order;           // workgroup order of the y-line pass, as PropXArgs::order
@@ -129,8 +130,8 @@ template <typename T> hipError_t launch_prop_x(int n, const PropXArgs<T>& a, int
 template <typename T> hipError_t launch_prop_yz(int n, const PropYZArgs<T>& a, int nb, hipStream_t st, int nt = 0,
                                                 const LaunchEvents* ev = nullptr,
                                                 const LaunchEvents* ev2 = nullptr);
-// parts of the density the plane pass leaves for B pairs
-template <typename T> int prop_yz_parts(int n, int B);
+// parts of the density the plane pass leaves for B pairs of L orbitals; busy as PropXArgs::busy
+template <typename T> int prop_yz_parts(int n, int B, int L, int fused, int busy);
 // Work lists of uneven batches (FP32): one launch of a propagation pass walks
 // the items of every listed system of one grid size, (pair, x tile) for the
 // x pass and (x plane, pair) for the plane pass, systems in order with

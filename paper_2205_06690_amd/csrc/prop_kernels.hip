@@ -67,7 +67,7 @@ __device__ __forceinline__ void kinetic_x_tile(cplx<T>* s, const cplx<T>* __rest
 // 256 threads on LDS s (x_lds bytes); shared by the per-system kernel and the
 // work-list kernel of uneven batches.
 template <int N, int TC, typename T, bool ETA>
-__device__ __forceinline__ void prop_x_item(const PropXArgs<T>& a, int fb, int tile, cplx<T>* s) {
+__device__ __forceinline__ void prop_x_item(const PropXArgs<T>& a, int fb, int tile, int l0, int ls, cplx<T>* s) {
   using C = cplx<T>;
   constexpr int NTH = 256;
   constexpr int N1 = Fac<N>::N1, N2 = Fac<N>::N2;
@@ -144,10 +144,10 @@ __device__ __forceinline__ void prop_x_item(const PropXArgs<T>& a, int fb, int t
     for (int j1 = 0; j1 < N1; ++j1) {
       const size_t g = gidx(it, j1);
       uu[it][j1] = cu * a.u[(size_t)b * ng + g];
-      dn[it][j1] = a.din[(size_t)b * a.L * ng + g];
-      hn[it][j1] = a.H[g];
+      dn[it][j1] = a.din[((size_t)b * a.L + l0) * ng + g];
+      hn[it][j1] = a.H[(size_t)l0 * ng + g];
     }
-  for (int l = 0; l < a.L; ++l) {
+  for (int l = l0; l < a.L; l += ls) {
     const size_t fo = ((size_t)b * a.L + l) * ng;
     C v[IT][N1];
 #pragma unroll
@@ -160,14 +160,14 @@ __device__ __forceinline__ void prop_x_item(const PropXArgs<T>& a, int fb, int t
         const C x = cmk<C>(dn[it][j1].x + uu[it][j1] * h.y, dn[it][j1].y - uu[it][j1] * h.x);
         v[it][j1] = cmul(p, x);
       }
-    if (l + 1 < a.L) {
+    if (l + ls < a.L) {
 #pragma unroll
       for (int it = 0; it < IT; ++it)
 #pragma unroll
         for (int j1 = 0; j1 < N1; ++j1) {
           const size_t g = gidx(it, j1);
-          dn[it][j1] = a.din[fo + ng + g];
-          hn[it][j1] = a.H[(size_t)(l + 1) * ng + g];
+          dn[it][j1] = a.din[fo + (size_t)ls * ng + g];
+          hn[it][j1] = a.H[(size_t)(l + ls) * ng + g];
         }
     }
     __syncthreads();  // the previous orbital's stage C has read its slots
@@ -191,8 +191,8 @@ __global__ void __launch_bounds__(256) k_prop_x(PropXArgs<T> a) {
   // the blocks of one tile run close together and share its H and phase
   // tiles in L2 (field_tile)
   int fb, tile;
-  if (!field_tile(a.order, a.nf, N * N / TC, fb, tile)) return;
-  prop_x_item<N, TC, T, ETA>(a, fb, tile, reinterpret_cast<cplx<T>*>(smem_raw));
+  if (!field_tile(a.order, a.nf * a.ls, N * N / TC, fb, tile)) return;
+  prop_x_item<N, TC, T, ETA>(a, fb / a.ls, tile, fb % a.ls, a.ls, reinterpret_cast<cplx<T>*>(smem_raw));
 }
 
 // ---------------------------------------------------------------------------
@@ -234,7 +234,8 @@ __device__ __forceinline__ void kinetic_yz_plane(cplx<T>* s, const cplx<T>* __re
 // orbitals of the pair with the next one's loads in flight, and the induced
 // density of the pair; a block of NT threads on LDS s (yz_lds bytes).
 // Shared by the per-system kernel and the work-list kernel.
-template <int N, typename T, int NT>
+// PART: orbital blockIdx.z alone, its density to a part of its own.
+template <int N, typename T, int NT, bool PART>
 __device__ __forceinline__ void prop_yz_pair_item(const PropYZArgs<T>& a, int x, int b, cplx<T>* s) {
   using C = cplx<T>;
   constexpr int P = N * N;
@@ -245,15 +246,16 @@ __device__ __forceinline__ void prop_yz_pair_item(const PropYZArgs<T>& a, int x,
   const size_t poff = (size_t)x * P;
   C* tws = s + N * plane_stride<N>();
   stage_tables<N>(tws, a.tw, a.kph, tid, NT);
+  const int l0 = PART ? blockIdx.z : 0, l1 = PART ? l0 + 1 : a.L;
   T acc[PER];
   C dn[PER];
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
     acc[i] = 0;
     const int e = tid + i * NT;
-    if (e < P) dn[i] = a.d[((size_t)b * a.L) * ng + poff + e];
+    if (e < P) dn[i] = a.d[((size_t)b * a.L + l0) * ng + poff + e];
   }
-  for (int l = 0; l < a.L; ++l) {
+  for (int l = l0; l < l1; ++l) {
     C* d = a.d + ((size_t)b * a.L + l) * ng + poff;
     const C* __restrict__ h = a.H + (size_t)l * ng + poff;
     C hc[PREF_H ? PER : 1];
@@ -266,7 +268,7 @@ __device__ __forceinline__ void prop_yz_pair_item(const PropYZArgs<T>& a, int x,
     __syncthreads();
     // loads of the next orbital and of this orbital's unperturbed plane are
     // in flight during the transform
-    if (l + 1 < a.L) {
+    if (l + 1 < l1) {
 #pragma unroll
       for (int i = 0; i < PER; ++i) {
         const int e = tid + i * NT;
@@ -292,15 +294,16 @@ __device__ __forceinline__ void prop_yz_pair_item(const PropYZArgs<T>& a, int x,
       }
     }
   }
-  T* dn_out = a.dens + (size_t)b * ng + poff;
+  // a part stays unscaled: the loader scales the sum
+  T* dn_out = a.dens + (PART ? (size_t)l0 * a.nf + b : (size_t)b) * ng + poff;
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
     const int e = tid + i * NT;
-    if (e < P) dn_out[e] = (T)4 * acc[i];
+    if (e < P) dn_out[e] = PART ? acc[i] : (T)4 * acc[i];
   }
 }
 
-template <int N, typename T, int NT, bool DENS>
+template <int N, typename T, int NT, bool DENS, bool PART>
 __global__ void __launch_bounds__(NT) k_prop_yz(PropYZArgs<T> a) {
   using C = cplx<T>;
   extern __shared__ unsigned char smem_raw[];
@@ -309,7 +312,7 @@ __global__ void __launch_bounds__(NT) k_prop_yz(PropYZArgs<T> a) {
   // together stream consecutive planes of one field (measured faster than
   // sharing the H planes across pairs, which the x pass gains from)
   if (DENS) {
-    prop_yz_pair_item<N, T, NT>(a, blockIdx.x, blockIdx.y, s);
+    prop_yz_pair_item<N, T, NT, PART>(a, blockIdx.x, blockIdx.y, s);
     return;
   }
   constexpr int P = N * N;
@@ -684,7 +687,8 @@ __global__ void __launch_bounds__(YZR_NT) k_prop_yz_reg(PropYZArgs<float> a) {
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int rt_swz(int vi) { return (vi ^ (vi >> 4)) & 15; }
 
-template <int N, bool DENS>
+// PART: orbital blockIdx.z alone, its density to a part of its own.
+template <int N, bool DENS, bool PART>
 __global__ void __launch_bounds__(YZR_NT) k_prop_yz_rt(PropYZArgs<float> a) {
   using C = float2;
   constexpr int R = N / 16, G = YZR_NT / 16, LPG = N / G, S = N + 1;
@@ -713,8 +717,9 @@ __global__ void __launch_bounds__(YZR_NT) k_prop_yz_rt(PropYZArgs<float> a) {
   stage_tables<N>(tws, a.tw, a.kph, tid, YZR_NT);
   const int zb = g * N + j;
   auto zo = [&](int q, int j1) { return zb + G * N * q + 16 * j1; };
-  const int nf = DENS ? a.L : 1;
-  const size_t f0 = DENS ? (size_t)b * a.L : (size_t)b;
+  const int l0 = PART ? blockIdx.z : 0;
+  const int nf = DENS && !PART ? a.L : 1;
+  const size_t f0 = DENS ? (size_t)b * a.L + l0 : (size_t)b;
   C dr[LPG][R];
   {
     const C* src = a.d + f0 * ng + off;
@@ -798,7 +803,7 @@ __global__ void __launch_bounds__(YZR_NT) k_prop_yz_rt(PropYZArgs<float> a) {
   };
   for (int l = 0; l < nf; ++l) {
     C* d = a.d + (f0 + l) * ng + off;
-    const C* h = DENS ? a.H + (size_t)l * ng + off : nullptr;
+    const C* h = DENS ? a.H + (size_t)(l0 + l) * ng + off : nullptr;
     __syncthreads();   // the previous field's scratch is done with the plane
     // point (y = g + G q, z = 16 j1 + j) to row z, column y
 #pragma unroll
@@ -864,11 +869,13 @@ __global__ void __launch_bounds__(YZR_NT) k_prop_yz_rt(PropYZArgs<float> a) {
     }
   }
   if (DENS) {
-    float* dn = a.dens + (size_t)b * ng + off;
+    // a part stays unscaled: the loader scales the sum
+    float* dn = a.dens + ((size_t)l0 * a.nf + b) * ng + off;
+    const float sc = PART ? 1.f : 4.f;
 #pragma unroll
     for (int q = 0; q < LPG; ++q)
 #pragma unroll
-      for (int j1 = 0; j1 < R; ++j1) dn[zo(q, j1)] = 4.f * accl[(q * R + j1) * YZR_NT + tid];
+      for (int j1 = 0; j1 < R; ++j1) dn[zo(q, j1)] = sc * accl[(q * R + j1) * YZR_NT + tid];
   }
 }
 
@@ -886,6 +893,14 @@ __device__ __forceinline__ C load_pair(T v0, T v1, bool check, int& bad0, int& b
     if (!isfinite(v1)) { v1 = (T)0; bad1 = 1; }
   }
   return cmk<C>(v0, v1);
+}
+// 4 times the sum of a density's parts in order
+template <typename T>
+__device__ __forceinline__ T sum_parts(const T* __restrict__ r, size_t stride, int parts) {
+  T v = r[0];
+#pragma unroll 4
+  for (int k = 1; k < parts; ++k) v += r[k * stride];
+  return (T)4 * v;
 }
 __device__ __forceinline__ void flag_bad(int* flags, int b0, int b1, int bad0, int bad1) {
   if (bad0) atomicOr(&flags[b0], 1);
@@ -909,18 +924,15 @@ __global__ void __launch_bounds__(NT) k_poisson_yz_fwd(PoisArgs<T> a) {
   const T i0 = a.pscale ? (T)(1.0 / a.pscale[b0]) : (T)1;
   const T i1 = (a.pscale && r1) ? (T)(1.0 / a.pscale[b1]) : (T)1;
   int bad0 = 0, bad1 = 0;
-  const size_t ps = (size_t)a.B * ng;
-  for (int e = tid; e < P; e += NT) {
-    T v0 = r0[e], v1 = r1 ? r1[e] : (T)0;
-    if (a.parts > 1) {
-      for (int k = 1; k < a.parts; ++k) {
-        v0 += r0[k * ps + e];
-        if (r1) v1 += r1[k * ps + e];
-      }
-      v0 *= (T)4;
-      v1 *= (T)4;
+  if (a.parts > 1) {
+    const size_t ps = (size_t)a.B * ng;
+    for (int e = tid; e < P; e += NT) {
+      const T v0 = sum_parts(r0 + e, ps, a.parts), v1 = r1 ? sum_parts(r1 + e, ps, a.parts) : (T)0;
+      s[plane_idx<N>(e)] = load_pair<C>(v0 * i0, v1 * i1, a.flags != nullptr, bad0, bad1);
     }
-    s[plane_idx<N>(e)] = load_pair<C>(v0 * i0, v1 * i1, a.flags != nullptr, bad0, bad1);
+  } else {
+    for (int e = tid; e < P; e += NT)
+      s[plane_idx<N>(e)] = load_pair<C>(r0[e] * i0, r1 ? r1[e] * i1 : (T)0, a.flags != nullptr, bad0, bad1);
   }
   flag_bad(a.flags, b0, b1, bad0, bad1);
   __syncthreads();
@@ -1052,8 +1064,16 @@ __global__ void __launch_bounds__(256) k_poisson_z(PoisArgs<T> a, int dir) {
     const T i0 = a.pscale ? (T)(1.0 / a.pscale[b0]) : (T)1;
     const T i1 = (a.pscale && has1) ? (T)(1.0 / a.pscale[b1]) : (T)1;
     int bad0 = 0, bad1 = 0;
-    for (int e = tid; e < E; e += 256)
-      s[(e / N) * S + e % N] = load_pair<C>(r0[e] * i0, r1 ? r1[e] * i1 : (T)0, a.flags != nullptr, bad0, bad1);
+    if (a.parts > 1) {
+      const size_t ps = (size_t)a.B * ng;
+      for (int e = tid; e < E; e += 256) {
+        const T v0 = sum_parts(r0 + e, ps, a.parts), v1 = r1 ? sum_parts(r1 + e, ps, a.parts) : (T)0;
+        s[(e / N) * S + e % N] = load_pair<C>(v0 * i0, v1 * i1, a.flags != nullptr, bad0, bad1);
+      }
+    } else {
+      for (int e = tid; e < E; e += 256)
+        s[(e / N) * S + e % N] = load_pair<C>(r0[e] * i0, r1 ? r1[e] * i1 : (T)0, a.flags != nullptr, bad0, bad1);
+    }
     flag_bad(a.flags, b0, b1, bad0, bad1);
     __syncthreads();
     stageA_fwd<N>(s, TL, S, 1, tw, tid, 256, true);
@@ -1359,7 +1379,7 @@ __global__ void __launch_bounds__(256) k_prop_x_list(const XListSys* __restrict_
     k = list_advance(list, nsys, k, w.it);
     const XListSys e = list[k];
     const unsigned loc = w.it - e.first;
-    prop_x_item<N, x_tc<N>(), float, false>(e.a, (int)(loc % (unsigned)e.a.nf), (int)(loc / (unsigned)e.a.nf), s);
+    prop_x_item<N, x_tc<N>(), float, false>(e.a, (int)(loc % (unsigned)e.a.nf), (int)(loc / (unsigned)e.a.nf), 0, 1, s);
     __syncthreads();   // the next item restages the tables and the tile
   }
 }
@@ -1374,7 +1394,7 @@ __global__ void __launch_bounds__(yz_threads<N>()) k_prop_yz_list(const YZListSy
     k = list_advance(list, nsys, k, w.it);
     const YZListSys e = list[k];
     const unsigned loc = w.it - e.first;
-    prop_yz_pair_item<N, float, yz_threads<N>()>(e.a, (int)(loc % (unsigned)N), (int)(loc / (unsigned)N), s);
+    prop_yz_pair_item<N, float, yz_threads<N>(), false>(e.a, (int)(loc % (unsigned)N), (int)(loc / (unsigned)N), s);
     __syncthreads();
   }
 }
@@ -1457,6 +1477,15 @@ struct Launch {
     else
       hipLaunchKernelGGL(kern, grid, block, sm, st, a);
   }
+  // A pair's orbitals go to several workgroups while those are fewer than the
+  // chip runs at once (FP32, 10 orbitals, unsplit -> split: 16^3 2 pairs 7.7 ->
+  // 3.6 us, 32^3 8 pairs 21.7 -> 10.9, 64^3 1 pair 33 -> 13, 8 pairs 64 -> 56).
+  // In FP64 and at 112 points, where the state soon exceeds the last-level
+  // cache, only well below that (64^3 FP64 1 pair 38 -> 25, but 11 pairs 214 ->
+  // 244; 112^3 FP32 5 pairs 305 -> 326).
+  static int x_groups(int blocks, int L) {
+    return std::max(1, std::min(L, (std::is_same<T, float>::value && N <= 64 ? 4096 : 1024) / blocks));
+  }
   template <int TC>
   static hipError_t prop_x_tc(const PropXArgs<T>& a, int F, hipStream_t st, const LaunchEvents* ev) {
     if constexpr (!x_valid<N, TC>()) {
@@ -1464,7 +1493,8 @@ struct Launch {
     } else {
       PropXArgs<T> b = a;
       b.nf = F;
-      const dim3 grid = field_tile_grid(a.order, F, N * N / TC);
+      b.ls = a.mode == PX_ETA0 ? 1 : x_groups(F * (N * N / TC) + a.busy, a.L);
+      const dim3 grid = field_tile_grid(a.order, F * b.ls, N * N / TC);
       size_t sm = x_lds<N, TC, T>();
       if (a.mode == PX_ETA0)
         go(k_prop_x<N, TC, T, true>, grid, dim3(256), sm, st, ev, b);
@@ -1490,10 +1520,15 @@ struct Launch {
   template <int NT>
   static hipError_t prop_yz_nt(const PropYZArgs<T>& a, int nb, hipStream_t st, const LaunchEvents* ev) {
     size_t sm = yz_lds<N, T>();
-    if (a.density)
-      go(k_prop_yz<N, T, NT, true>, dim3(N, nb), dim3(NT), sm, st, ev, a);
+    PropYZArgs<T> b = a;
+    b.nf = nb;
+    if (a.density && a.parts != 1 && a.parts != a.L) return hipErrorInvalidValue;
+    if (a.density && a.parts > 1)
+      go(k_prop_yz<N, T, NT, true, true>, dim3(N, nb, a.parts), dim3(NT), sm, st, ev, b);
+    else if (a.density)
+      go(k_prop_yz<N, T, NT, true, false>, dim3(N, nb), dim3(NT), sm, st, ev, b);
     else
-      go(k_prop_yz<N, T, NT, false>, dim3(N, nb), dim3(NT), sm, st, ev, a);
+      go(k_prop_yz<N, T, NT, false, false>, dim3(N, nb), dim3(NT), sm, st, ev, b);
     return hipGetLastError();
   }
   static constexpr bool yz_split() { return yz_lds<N, T>() > 80 * 1024; }
@@ -1507,12 +1542,16 @@ struct Launch {
     if constexpr (yz_reg()) {
       PropYZArgs<T> ar = a;
       ar.nf = nb;
-      const dim3 gr = a.order ? field_tile_grid(1, nb, N) : dim3(N, nb);
+      dim3 gr = a.order ? field_tile_grid(1, nb, N) : dim3(N, nb);
       if (a.fused == 2) {
-        if (a.density)
-          go(k_prop_yz_rt<N, true>, gr, dim3(YZR_NT), yz_reg_lds(), st, ev, ar);
+        if (a.density && a.parts != 1 && a.parts != a.L) return hipErrorInvalidValue;
+        if (a.density && a.parts > 1) {
+          gr.z = a.parts;
+          go(k_prop_yz_rt<N, true, true>, gr, dim3(YZR_NT), yz_reg_lds(), st, ev, ar);
+        } else if (a.density)
+          go(k_prop_yz_rt<N, true, false>, gr, dim3(YZR_NT), yz_reg_lds(), st, ev, ar);
         else
-          go(k_prop_yz_rt<N, false>, gr, dim3(YZR_NT), yz_reg_lds(), st, ev, ar);
+          go(k_prop_yz_rt<N, false, false>, gr, dim3(YZR_NT), yz_reg_lds(), st, ev, ar);
       } else if (a.density)
         go(k_prop_yz_reg<N, true>, gr, dim3(YZR_NT), yz_reg_lds(), st, ev, ar);
       else
@@ -1593,8 +1632,9 @@ struct Launch {
   template <int NT> static void conf_yz() {
     if constexpr (yz_lds<N, T>() > 160 * 1024) return;   // the plane kernels never run
     const int smp = (int)yz_lds<N, T>();
-    (void)hipFuncSetAttribute((const void*)k_prop_yz<N, T, NT, true>, hipFuncAttributeMaxDynamicSharedMemorySize, smp);
-    (void)hipFuncSetAttribute((const void*)k_prop_yz<N, T, NT, false>, hipFuncAttributeMaxDynamicSharedMemorySize, smp);
+    (void)hipFuncSetAttribute((const void*)k_prop_yz<N, T, NT, true, true>, hipFuncAttributeMaxDynamicSharedMemorySize, smp);
+    (void)hipFuncSetAttribute((const void*)k_prop_yz<N, T, NT, true, false>, hipFuncAttributeMaxDynamicSharedMemorySize, smp);
+    (void)hipFuncSetAttribute((const void*)k_prop_yz<N, T, NT, false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, smp);
   }
   static void configure() {
     constexpr int NT = yz_threads<N>();
@@ -1622,9 +1662,11 @@ struct Launch {
                                 (int)yz_reg_lds());
       (void)hipFuncSetAttribute((const void*)k_prop_yz_reg<N, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)yz_reg_lds());
-      (void)hipFuncSetAttribute((const void*)k_prop_yz_rt<N, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+      (void)hipFuncSetAttribute((const void*)k_prop_yz_rt<N, true, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)yz_reg_lds());
-      (void)hipFuncSetAttribute((const void*)k_prop_yz_rt<N, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+      (void)hipFuncSetAttribute((const void*)k_prop_yz_rt<N, true, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)yz_reg_lds());
+      (void)hipFuncSetAttribute((const void*)k_prop_yz_rt<N, false, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)yz_reg_lds());
     }
   }
@@ -1668,9 +1710,18 @@ hipError_t launch_prop_yz(int n, const PropYZArgs<T>& a, int nb, hipStream_t st,
                           const LaunchEvents* ev, const LaunchEvents* ev2) {
   BSE_DISPATCH_N(n, T, prop_yz(a, nb, st, nt, ev, ev2));
 }
+// The orbitals of a pair run apart where the planes of the pairs alone leave
+// the chip idle; above the line the extra densities, written here and read by
+// the Poisson solve, cost more than they give (FP32, 10 orbitals, together ->
+// apart: 16^3 2 pairs 8.0 -> 3.5 us, 24^3 8 pairs 31 -> 10, 32^3 21 pairs 41 ->
+// 31 but 48 pairs 71 -> 60 plus 12 in the solve; 48^3 12 pairs 92 -> 76; 64^3 1
+// pair 55 -> 18, 4 pairs 61 -> 46, 8 pairs 86 -> 90).
 template <typename T>
-int prop_yz_parts(int n, int B) {
-  return std::is_same<T, double>::value ? kin_yz_parts(n, B) : 1;
+int prop_yz_parts(int n, int B, int L, int fused, int busy) {
+  if (std::is_same<T, double>::value) return kin_yz_parts(n, B, busy);
+  if (n == 112 && fused != 2) return 1;
+  const int most = n <= 32 ? 800 : n == 48 ? 640 : 320;
+  return n * B + busy < most ? L : 1;
 }
 template <typename T>
 bool prop_yz_split(int n) {
@@ -1829,7 +1880,7 @@ hipError_t launch_to_real(const double* in, size_t n, T* out, hipStream_t st) {
                                        const LaunchEvents*);                                     \
   template hipError_t launch_prop_yz<T>(int, const PropYZArgs<T>&, int, hipStream_t, int,      \
                                         const LaunchEvents*, const LaunchEvents*);               \
-  template int prop_yz_parts<T>(int, int);                                                     \
+  template int prop_yz_parts<T>(int, int, int, int, int);                                                     \
   template bool prop_yz_split<T>(int);                                                         \
   template bool prop_yz_fused<T>(int);                                                         \
   template hipError_t launch_poisson<T>(int, const PoisArgs<T>&, hipStream_t);                 \
