@@ -261,3 +261,31 @@ def test_truncated_transforms_and_layers(n, W, m, L, B):
     say(f"layers n={n} W={W} m={m}: y {ey:.1e}, loss {abs(loss / loss_o - 1):.1e}, grads {max(eg.values()):.1e}")
     assert ey < 2e-5 and abs(loss / loss_o - 1) < 2e-5
     assert max(eg.values()) < 2e-5, eg
+
+
+@pytest.mark.parametrize("W,L", [(15, 1), (16, 1), (17, 3), (31, 2)])
+def test_gradient_to_host_in_chunks(W, L):
+    """Gradients just below and above the size from which they reach the host
+    in 1 MB chunks over pinned slots (3.7 and 4.2 MB; 14 MB over more chunks
+    than slots, a region of half a chunk at the end of each layer), twice into
+    new memory: the same as after one plain copy, which a training step from
+    the same weights reads on the device (its first Adam step moves every
+    weight by lr g / (|g| + 1e-8), so the signs show)."""
+    import torch
+    from paper_2205_06690_amd import bse
+    n, m, B, lr = 16, 8, 1, 1e-3
+    rng = np.random.default_rng(W)
+    net = bse.Fno(n, cin=2, width=W, modes=m, layers=L, max_batch=B, bf16_weights=False, seed=2)
+    p = net.get_params()
+    net.set_params(p)
+    x = torch.from_numpy(rng.standard_normal((B, 2, n, n, n)).astype(np.float32)).cuda()
+    t = torch.from_numpy(rng.standard_normal((B, n, n, n)).astype(np.float32)).cuda()
+    _, g0 = net.loss_grad(B, x.data_ptr(), t.data_ptr())
+    _, g1 = net.loss_grad(B, x.data_ptr(), t.data_ptr())
+    assert np.array_equal(g0, g1)
+    net.train_step(B, x.data_ptr(), t.data_ptr(), lr)
+    step = (net.get_params().astype(np.float64) - p) / lr
+    want = -g0.astype(np.float64) / (np.abs(g0) + 1e-8)
+    # the step is a difference of FP32 weights below 1: eps 6e-8 / lr
+    say(f"chunks W {W} L {L}: {g0.nbytes / 2 ** 20:.2f} MB, max|d step| {np.abs(step - want).max():.1e}")
+    assert np.abs(step - want).max() < 1e-3
