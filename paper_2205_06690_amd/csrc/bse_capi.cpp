@@ -188,6 +188,7 @@ struct bse_system {
   DBuf d, u, dens, wpol, q, rho64, work, work64, part, part32, gpart, coef, coefE, E, pq_d, flags;
   DBuf pscale;    // [B][3] row sums of q, then [B] per-pair scales of the packed Poisson solves
   DBuf normpart;  // partial norms of the unperturbed set (check at the cleaning steps)
+  DBuf rowpart;   // partial row sums (launch_row_dots)
   // A / spectrum state
   int a_no = 0, a_nc = 0;
   DBuf wij;       // [n_ij][ng] FP64 W_ij of the valence pairs
@@ -315,6 +316,7 @@ void ensure_batch(bse_system* s, int B) {
   s->flags.alloc(sizeof(int) * B);
   s->work64.alloc(sizeof(cplx<double>) * ng * (size_t)((B + 1) / 2));
   s->pscale.alloc(sizeof(double) * 4 * (size_t)B);
+  s->rowpart.alloc(sizeof(double) * row_dots_part_elems(B));
   s->normpart.alloc(sizeof(double) * norm_drift_part_elems(L));
   s->cap_b = B;
 }
@@ -423,7 +425,8 @@ void prop_begin(PropRun<T>& r) {
   // the RMS of q_b (the response is linear in it), so that a pair whose
   // source is orders of magnitude weaker than its partner's is not buried
   // in the partner's rounding
-  HIPC(launch_row_dots(s->q.as<double>(), nullptr, nullptr, B, ng, s->pscale.as<double>(), st));
+  HIPC(launch_row_dots(s->q.as<double>(), nullptr, nullptr, B, ng, s->rowpart.as<double>(),
+                       s->pscale.as<double>(), st));
   HIPC(launch_rms_scales(s->pscale.as<double>(), B, ng, s->pscale.as<double>() + 3 * (size_t)B, st));
   HIPC(launch_fill_zero(s->wpol.p, sizeof(double) * ng * B, st));
   HIPC(launch_fill_zero(s->u.p, sizeof(T) * ng * B, st));
@@ -1691,7 +1694,7 @@ void apply_w_batch(int n_sys, bse_system* const* sys, const int32_t* n_pairs,
 std::vector<const void*> workspace_signature(const bse_system* s) {
   const DBuf* bufs[] = {&s->d, &s->u, &s->dens, &s->wpol, &s->q, &s->rho64, &s->work, &s->work64,
                         &s->part, &s->part32, &s->gpart, &s->coef, &s->coefE, &s->E, &s->flags,
-                        &s->pscale, &s->normpart, &s->phi64, &s->phi_occ32, &s->phih, &s->phil,
+                        &s->pscale, &s->normpart, &s->rowpart, &s->phi64, &s->phi_occ32, &s->phih, &s->phil,
                         &s->phith, &s->phitl, &s->eta0, &s->h0, &s->hbuf, &s->n0,
                         &s->tf.tw, &s->tf.kph, &s->tf.kin, &s->tf.pf, &s->tf.ph, &s->tf.k2,
                         &s->td.tw, &s->td.kph, &s->td.kin, &s->td.pf, &s->td.ph, &s->td.k2};
@@ -1881,7 +1884,9 @@ std::vector<double> source_and_scale(bse_system* s, int B) {
   HIPC(launch_pair_density(s->phi64.as<double>(), s->pq_d.as<int>(), B, s->ng, s->rho64.as<double>(), s->stream));
   poisson64(s, s->rho64.as<double>(), B, s->q.as<double>(), nullptr, 0.0);
   s->fdots.alloc(sizeof(double) * 3 * B);
-  HIPC(launch_row_dots(s->q.as<double>(), nullptr, nullptr, B, s->ng, s->fdots.as<double>(), s->stream));
+  s->rowpart.alloc(sizeof(double) * row_dots_part_elems(B));
+  HIPC(launch_row_dots(s->q.as<double>(), nullptr, nullptr, B, s->ng, s->rowpart.as<double>(), s->fdots.as<double>(),
+                       s->stream));
   std::vector<double> dots(3 * (size_t)B), sc(B);
   HIPC(hipMemcpyAsync(dots.data(), s->fdots.p, sizeof(double) * 3 * B, hipMemcpyDeviceToHost, s->stream));
   HIPC(hipStreamSynchronize(s->stream));
@@ -1960,7 +1965,7 @@ void apply_w_surrogate(bse_system* s, bse_fno* net, int n_pairs, const int32_t* 
     HIPC(launch_assemble_w(s->q.as<double>(), s->fscale.as<double>(), s->fy.as<float>(), B, ng,
                            s->fwpol.as<double>(), w_dev + (size_t)k0 * ng, s->stream));
     HIPC(launch_row_dots(s->rho64.as<double>(), s->q.as<double>(), s->fwpol.as<double>(), B, ng,
-                         s->fdots.as<double>(), s->stream));
+                         s->rowpart.as<double>(), s->fdots.as<double>(), s->stream));
     std::vector<double> dots(3 * (size_t)B);
     HIPC(hipMemcpyAsync(dots.data(), s->fdots.p, sizeof(double) * 3 * B, hipMemcpyDeviceToHost, s->stream));
     HIPC(hipStreamSynchronize(s->stream));

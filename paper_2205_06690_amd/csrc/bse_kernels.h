@@ -86,8 +86,10 @@ hipError_t launch_boundary_average(const double* vext, const double* vh, int n, 
                                    hipStream_t st);
 // scale[b] = RMS of row b from launch_row_dots' sums (1 for a zero row)
 hipError_t launch_rms_scales(const double* dots, int B, size_t ng, double* scale, hipStream_t st);
+// part holds row_dots_part_elems(B) doubles
+size_t row_dots_part_elems(int B);
 hipError_t launch_row_dots(const double* a, const double* c, const double* d, int B, size_t ng,
-                           double* out, hipStream_t st);
+                           double* part, double* out, hipStream_t st);
 hipError_t launch_features(const double* q, const double* scale, const double* n0, double n0s,
                            const double* v, double vs, int B, size_t ng, float* x, hipStream_t st);
 hipError_t launch_targets(const double* wpol, const double* scale, int B, size_t ng, float* t,
