@@ -40,9 +40,14 @@ hipError_t launch_coef_x3(const float2* d, int F, const PhiSplit& ps, size_t ng,
                           float* part, double dv, double2* coef, hipStream_t st, const MidArgs& mid,
                           const float2* E, int L, double2* gpart);
 // d_f -= sum_s C[f][s] phi_s + c_f E_l (after the end of the step when mid.on);
-// scratch holds the split coefficient rows (clean_scratch_floats)
+// scratch holds the split coefficient rows (clean_scratch_floats); dens
+// (nullable, update_dens_fits(L)): the density of the result, [F / L][ng]
 hipError_t launch_update_x3(float2* d, int F, const PhiSplit& ps, const float2* E, int L, size_t ng,
-                            const double2* coef, float* scratch, hipStream_t st, const MidArgs& mid);
+                            const double2* coef, float* scratch, hipStream_t st, const MidArgs& mid,
+                            float* dens);
+// whether whole pairs of L orbitals fill at least seven eighths of the update's
+// 32-field half tiles: else the density is the cheaper pass of its own
+inline bool update_dens_fits(int L) { return L >= 1 && L <= 32 && 32 / L * L >= 28; }
 // for batches of up to F = B L fields
 size_t clean_scratch_floats(int F, int L, int S, size_t ng);
 // for batches of up to F = B L fields

@@ -68,11 +68,10 @@ __global__ void k_phi_split(const float* __restrict__ phi, int S, int Sp, size_t
 }
 
 // part[kc][row][s] (row < 2F, s < S) = sum over chunk kc of D[row][r] phi_s(r),
-// D = d, finished on the fly when MID.  With EDOT the column-tile-0 blocks
-// also accumulate <E_l, d_f> over their chunk into gpart[f][kc] (E = Ph H_l
+// D = d, finished on the fly when MID.  The column-tile-0 blocks also accumulate <E_l, d_f> over their chunk into gpart[f][kc] (E = Ph H_l
 // computed in registers when MID, read from E otherwise).  Global loads of
 // stage k+1 are in flight during the matrix-core work of stage k.
-template <bool MID, bool EDOT>
+template <bool MID>
 __global__ void __launch_bounds__(256) k_coef_x3(const float2* __restrict__ d, int F, PhiSplit ps,
                                                  size_t ng, int chunk, int nrt, int nct, int nchunk,
                                                  unsigned ntile, MidArgs mid,
@@ -94,7 +93,7 @@ __global__ void __launch_bounds__(256) k_coef_x3(const float2* __restrict__ d, i
   const size_t k1 = min(ng, k0 + (size_t)chunk);
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wm = w >> 1, wn = w & 1;
-  const bool do_e = EDOT && ct == 0;
+  const bool do_e = ct == 0;
   // loader: fields f0 + qa + 16i at points pa, pa+1; state s0 + sb at points hb..hb+15
   const int qa = tid >> 4, pa = (tid & 15) * 2;
   const int sb = tid >> 1, hb = (tid & 1) * 16;
@@ -214,6 +213,94 @@ __global__ void __launch_bounds__(256) k_coef_x3(const float2* __restrict__ d, i
   }
 }
 
+// The same partial sums, bit for bit, for few fields (the unperturbed set): a
+// wave takes 16 MI rows and 64 states of a chunk, both operands straight from
+// memory into registers in the instruction's own layout (lane l: row or state
+// l % 16, points 8 (l / 16) ..), PF stages in flight.  The 128-row tile of
+// k_coef_x3 left these launches with one block per chunk and a barrier per 32
+// points: 10 orbitals, 64^3, 120 states 62 -> 56 us; 112^3, 260 states 511 ->
+// 406; 4 orbitals, 16^3 37 -> 18.  Bound by latency on small grids, by reading
+// phi on large ones (1.46 GB at 112^3, 300 us).
+template <int MI, int PF>
+__global__ void __launch_bounds__(256) k_coef_rows(const float2* __restrict__ d, int F, PhiSplit ps, size_t ng,
+                                                   int chunk, int nrt, int nct, unsigned ntile,
+                                                   float* __restrict__ part) {
+  const unsigned t = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (t >= ntile) return;
+  const int lane = threadIdx.x & 63, m = lane & 15, k8 = 8 * (lane >> 4);
+  const int rt = (int)(t % nrt), ct = (int)((t / nrt) % nct), kc = (int)(t / ((unsigned)nrt * nct));
+  const int R = 2 * F, S = ps.S;
+  const size_t k0 = (size_t)kc * chunk, k1 = min(ng, k0 + (size_t)chunk);
+  // rows past R and states past S load the last one: never stored
+  const float2* pa[MI];
+#pragma unroll
+  for (int i = 0; i < MI; ++i) pa[i] = d + (size_t)(min(R - 1, (rt * MI + i) * 16 + m) / 2) * ng + k8;
+  const bool im = m & 1;
+  size_t pb[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) pb[j] = (size_t)min(S - 1, ct * 64 + j * 16 + m) * ng + k8;
+  f4 acc[MI][4];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+  float4 a[PF][MI][4];
+  bf8 bh[PF][4], bl[PF][4];
+  auto load = [&](int q, size_t kb) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) a[q][i][c] = reinterpret_cast<const float4*>(pa[i] + kb)[c];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      bh[q][j] = *reinterpret_cast<const bf8*>(ps.h + pb[j] + kb);
+      bl[q][j] = *reinterpret_cast<const bf8*>(ps.l + pb[j] + kb);
+    }
+  };
+#pragma unroll
+  for (int q = 0; q < PF; ++q)
+    if (k0 + q * XK < k1) load(q, k0 + q * XK);
+  for (size_t kb = k0; kb < k1; kb += PF * XK) {
+#pragma unroll
+    for (int q = 0; q < PF; ++q) {
+      if (kb + q * XK >= k1) break;
+      bf8 ah[MI], al[MI];
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const float4 w = a[q][i][c];
+          unsigned short h0, l0, h1, l1;
+          split_hl(im ? w.y : w.x, h0, l0);
+          split_hl(im ? w.w : w.z, h1, l1);
+          ah[i][2 * c] = __builtin_bit_cast(__bf16, h0);
+          al[i][2 * c] = __builtin_bit_cast(__bf16, l0);
+          ah[i][2 * c + 1] = __builtin_bit_cast(__bf16, h1);
+          al[i][2 * c + 1] = __builtin_bit_cast(__bf16, l1);
+        }
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[i], bh[q][j], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bl[q][j], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bh[q][j], acc[i][j], 0, 0, 0);
+        }
+      if (kb + (PF + q) * XK < k1) load(q, kb + (PF + q) * XK);
+    }
+  }
+  float* out = part + (size_t)kc * R * S;
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int row = (rt * MI + i) * 16 + 4 * (lane >> 4) + v, col = ct * 64 + j * 16 + m;
+        if (row < R && col < S) out[(size_t)row * S + col] = acc[i][j][v];
+      }
+}
+
 // coef[f][s] = dv * (sum_kc part[kc][2f][s] + i sum_kc part[kc][2f+1][s]),
 // stored with row stride S+1 (slot S holds the E dot).  A block sums 32
 // outputs in RED_SL slices of the chunks (slice j: kc = j, j + RED_SL, ...),
@@ -282,16 +369,20 @@ __global__ void k_coef_split(const double2* __restrict__ coef, int F, int S, int
 }
 
 // d_f(r) = fin(d_f(r)) - sum_s C[f][s] phi_s(r) - c_f E_l(r), fin the end of
-// the step when MID.  Block: 128 rows (64 fields) x 128 points, K = states
-// in stages of 32; row tile fastest so that the row tiles of one point tile
-// (sharing its phi^T tile) run together on one XCD.
-template <bool MID>
+// the step when MID.  Block: 128 rows, two halves of fh <= 32 fields, x 128
+// points, K = states in stages of 32; row tile fastest so that the row tiles
+// of one point tile (sharing its phi^T tile) run together on one XCD.
+// DENS: fh is a multiple of L, and the density of the new state, 4 sum_l
+// Re(conj(E_l) d_{b,l}) in the order of l, leaves with it: a pass of its own
+// over d (64^3, 550 fields: 265 us beside 752 here) is saved.
+template <bool MID, bool DENS>
 __global__ void __launch_bounds__(256, 3) k_update_x3(float2* __restrict__ d, int F, PhiSplit ps,
                                                    const float2* __restrict__ E, int L, size_t ng,
                                                    const unsigned short* __restrict__ cth,
                                                    const unsigned short* __restrict__ ctl,
                                                    const double2* __restrict__ coef, int nrt,
-                                                   unsigned ntile, MidArgs mid) {
+                                                   unsigned ntile, MidArgs mid, int fh,
+                                                   float* __restrict__ dens) {
   // operand tiles during the K loop; afterwards the same LDS holds half of
   // the result tile (64 rows x 128 points, rows padded) at a time
   constexpr int TP = XT + 4;
@@ -306,7 +397,7 @@ __global__ void __launch_bounds__(256, 3) k_update_x3(float2* __restrict__ d, in
   if (t >= ntile) return;
   const int rt = (int)(t % nrt);
   const size_t p0 = (size_t)(t / nrt) * XT;
-  const int r0 = rt * XT;
+  const int f0 = rt * 2 * fh;          // first field; the second half starts at f0 + fh
   const int R = 2 * F, S = ps.S, Sp = ps.Sp;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wm = w >> 1, wn = w & 1;
@@ -321,7 +412,8 @@ __global__ void __launch_bounds__(256, 3) k_update_x3(float2* __restrict__ d, in
   for (int c = 0; c < 4; ++c) {
     const int r = rw + 64 * (c & 1);
     if (c < 2) {
-      go[c] = (unsigned)min(R - 1, r0 + r) * (unsigned)Sp + 8 * qp;
+      // tile row r: row rw of half c
+      go[c] = (unsigned)min(R - 1, 2 * (f0 + c * fh) + rw) * (unsigned)Sp + 8 * qp;
       lo[c] = r * XKP + 8 * qp;
     } else {
       go[c] = (unsigned)min(ng - 1, p0 + r) * (unsigned)Sp + 8 * qp;
@@ -377,23 +469,23 @@ __global__ void __launch_bounds__(256, 3) k_update_x3(float2* __restrict__ d, in
             T[(i * 16 + 4 * (lane >> 4) + v) * TP + wn * 64 + j * 16 + (lane & 15)] = acc[i][j][v];
     }
     __syncthreads();
-    if (pr >= ng) continue;
     float4 p01 = make_float4(0.f, 0.f, 0.f, 0.f), p23 = p01;
-    if (MID) {
+    if (MID && pr < ng) {
       p01 = *reinterpret_cast<const float4*>(mid.ph + pr);
       p23 = *reinterpret_cast<const float4*>(mid.ph + pr + 2);
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int fl = fs + 8 * q;                 // field within the half
-      const int f = r0 / 2 + half * 32 + fl;
-      if (2 * f >= R) continue;
+      const int f = f0 + half * fh + fl;
+      if (fl >= fh || f >= F || pr >= ng) continue;
       const int l = f % L;
       const float cr = (float)coef[(size_t)f * (S + 1) + S].x;
       float2* dp = d + (size_t)f * ng + pr;
       float4 d01 = reinterpret_cast<const float4*>(dp)[0];
       float4 d23 = reinterpret_cast<const float4*>(dp)[1];
       float4 e01, e23;
+      float ei[4];
       if (MID) {
         const float2* hp = mid.H + (size_t)l * ng + pr;
         const float4 h01 = reinterpret_cast<const float4*>(hp)[0];
@@ -410,7 +502,11 @@ __global__ void __launch_bounds__(256, 3) k_update_x3(float2* __restrict__ d, in
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           dv[k] = finish1(dv[k], hv[k], uv[k], pv[k], mid.half_dt);
-          ev[k] = cm(pv[k], hv[k]);
+          // E = Ph H; its imaginary part in the two roundings that the update and
+          // the density have always had
+          ev[k] = make_float2(fmaf(hv[k].x, pv[k].x, -(hv[k].y * pv[k].y)),
+                              fmaf(hv[k].y, pv[k].x, hv[k].x * pv[k].y));
+          if (DENS) ei[k] = fmaf(pv[k].y, hv[k].x, pv[k].x * hv[k].y);
         }
         d01 = make_float4(dv[0].x, dv[0].y, dv[1].x, dv[1].y);
         d23 = make_float4(dv[2].x, dv[2].y, dv[3].x, dv[3].y);
@@ -433,6 +529,35 @@ __global__ void __launch_bounds__(256, 3) k_update_x3(float2* __restrict__ d, in
       d23.w -= aim.w + cr * e23.w;
       reinterpret_cast<float4*>(dp)[0] = d01;
       reinterpret_cast<float4*>(dp)[1] = d23;
+      // the field's term of the density, in its (read) row of the result, with
+      // E rounded as k_clean_e rounds it
+      if (DENS && MID) {
+        e01.y = ei[0];
+        e01.w = ei[1];
+        e23.y = ei[2];
+        e23.w = ei[3];
+      }
+      if (DENS)
+        *reinterpret_cast<float4*>(&T[(2 * fl) * TP + 4 * pg]) =
+            make_float4(e01.x * d01.x + e01.y * d01.y, e01.z * d01.z + e01.w * d01.w, e23.x * d23.x + e23.y * d23.y,
+                        e23.z * d23.z + e23.w * d23.w);
+    }
+    if (DENS) {
+      __syncthreads();
+      const int b0 = (f0 + half * fh) / L;
+      if (pr < ng)
+        for (int k = fs; k < fh / L && (b0 + k) * L < F; k += 8) {
+          float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+          for (int l = 0; l < L; ++l) {
+            const float4 q = *reinterpret_cast<const float4*>(&T[2 * (k * L + l) * TP + 4 * pg]);
+            sum.x += q.x;
+            sum.y += q.y;
+            sum.z += q.z;
+            sum.w += q.w;
+          }
+          *reinterpret_cast<float4*>(dens + (size_t)(b0 + k) * ng + pr) =
+              make_float4(4.f * sum.x, 4.f * sum.y, 4.f * sum.z, 4.f * sum.w);
+        }
     }
   }
 }
@@ -452,29 +577,39 @@ hipError_t launch_coef_x3(const float2* d, int F, const PhiSplit& ps, size_t ng,
                           const float2* E, int L, double2* gpart) {
   if (F <= 0 || ps.S <= 0 || ng % XK || chunk % XK || chunk <= 0) return hipErrorInvalidValue;
   if (mid.on && !gpart) return hipErrorInvalidValue;
-  const int nrt = (2 * F + XT - 1) / XT, nct = (ps.S + XT - 1) / XT;
   const int nchunk = (int)((ng + chunk - 1) / chunk);
-  const unsigned ntile = (unsigned)nrt * nct * nchunk;
-  const dim3 g(round8(ntile)), b(256);
-  if (mid.on)
-    hipLaunchKernelGGL((k_coef_x3<true, true>), g, b, 0, st, d, F, ps, ng, chunk, nrt, nct, nchunk,
-                       ntile, mid, E, L, part, gpart);
-  else if (gpart)
-    hipLaunchKernelGGL((k_coef_x3<false, true>), g, b, 0, st, d, F, ps, ng, chunk, nrt, nct, nchunk,
-                       ntile, mid, E, L, part, gpart);
-  else
-    hipLaunchKernelGGL((k_coef_x3<false, false>), g, b, 0, st, d, F, ps, ng, chunk, nrt, nct, nchunk,
-                       ntile, mid, E, L, part, gpart);
-  if (gpart)
+  if (gpart) {
+    const int nrt = (2 * F + XT - 1) / XT, nct = (ps.S + XT - 1) / XT;
+    const unsigned ntile = (unsigned)nrt * nct * nchunk;
+    const dim3 g(round8(ntile)), b(256);
+    if (mid.on)
+      hipLaunchKernelGGL(k_coef_x3<true>, g, b, 0, st, d, F, ps, ng, chunk, nrt, nct, nchunk, ntile, mid, E, L, part,
+                         gpart);
+    else
+      hipLaunchKernelGGL(k_coef_x3<false>, g, b, 0, st, d, F, ps, ng, chunk, nrt, nct, nchunk, ntile, mid, E, L, part,
+                         gpart);
     hipLaunchKernelGGL(k_edot_reduce, dim3((F + 3) / 4), dim3(256), 0, st, gpart, nchunk, F, ps.S, dv,
                        coef);
+  } else {
+    const int nct = (ps.S + 63) / 64;
+    if (2 * F <= 16) {
+      const unsigned ntile = (unsigned)nct * nchunk;
+      hipLaunchKernelGGL((k_coef_rows<1, 4>), dim3((ntile + 3) / 4), dim3(256), 0, st, d, F, ps, ng, chunk, 1, nct,
+                         ntile, part);
+    } else {
+      const int nrt = (2 * F + 31) / 32;
+      const unsigned ntile = (unsigned)nrt * nct * nchunk;
+      hipLaunchKernelGGL((k_coef_rows<2, 2>), dim3((ntile + 3) / 4), dim3(256), 0, st, d, F, ps, ng, chunk, nrt, nct,
+                         ntile, part);
+    }
+  }
   hipLaunchKernelGGL(k_coef_reduce, dim3((F * ps.S + 31) / 32), dim3(256), 0, st, part, nchunk, F, ps.S,
                      dv, coef);
   return hipGetLastError();
 }
 
 hipError_t launch_update_x3(float2* d, int F, const PhiSplit& ps, const float2* E, int L, size_t ng,
-                            const double2* coef, float* scratch, hipStream_t st, const MidArgs& mid) {
+                            const double2* coef, float* scratch, hipStream_t st, const MidArgs& mid, float* dens) {
   if (F <= 0 || ps.S <= 0 || ps.Sp != clean_sp(ps.S)) return hipErrorInvalidValue;
   // the loader's 32-bit element offsets into phi^T and the coefficient rows
   if (ng * (size_t)ps.Sp > 0xFFFFFFFFull || (size_t)2 * F * ps.Sp > 0xFFFFFFFFull) return hipErrorInvalidValue;
@@ -483,16 +618,15 @@ hipError_t launch_update_x3(float2* d, int F, const PhiSplit& ps, const float2* 
   unsigned short* ctl = cth + (size_t)2 * F * Sp;
   hipLaunchKernelGGL(k_coef_split, dim3((2 * F * Sp + 255) / 256), dim3(256), 0, st, coef, F, ps.S, Sp,
                      cth, ctl);
-  const int nrt = (2 * F + XT - 1) / XT;
+  const int fh = dens ? 32 / L * L : 32;
+  if (fh <= 0 || (dens && F % L)) return hipErrorInvalidValue;
+  const int nrt = (F + 2 * fh - 1) / (2 * fh);
   const size_t npt = (ng + XT - 1) / XT;
   const unsigned ntile = (unsigned)(nrt * npt);
   const dim3 g(round8(ntile)), b(256);
-  if (mid.on)
-    hipLaunchKernelGGL(k_update_x3<true>, g, b, 0, st, d, F, ps, E, L, ng, cth, ctl, coef, nrt, ntile,
-                       mid);
-  else
-    hipLaunchKernelGGL(k_update_x3<false>, g, b, 0, st, d, F, ps, E, L, ng, cth, ctl, coef, nrt, ntile,
-                       mid);
+  auto k = dens ? (mid.on ? k_update_x3<true, true> : k_update_x3<false, true>)
+                : (mid.on ? k_update_x3<true, false> : k_update_x3<false, false>);
+  hipLaunchKernelGGL(k, g, b, 0, st, d, F, ps, E, L, ng, cth, ctl, coef, nrt, ntile, mid, fh, dens);
   return hipGetLastError();
 }
 

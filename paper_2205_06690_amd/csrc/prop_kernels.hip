@@ -1323,7 +1323,9 @@ __global__ void k_to_real(const double* __restrict__ in, size_t n, T* __restrict
 // ---------------------------------------------------------------------------
 // host launchers
 // ---------------------------------------------------------------------------
-template <int N> constexpr int yz_threads() { return N >= 64 ? 512 : 256; }
+// at 24 points the z and y items of a plane fill 192 threads exactly (96 pairs,
+// 10 orbitals: 74 us with 256, 59)
+template <int N> constexpr int yz_threads() { return N >= 64 ? 512 : N == 24 ? 192 : 256; }
 template <int N> constexpr int x_tc() { return N <= 16 ? 64 : 32; }
 
 // tile width of the x pass and block size of the plane passes are tunable;
@@ -1591,6 +1593,7 @@ struct Launch {
     } else {
       if (nt == 0) nt = yz_threads<N>();
       switch (nt) {
+        case 192: return prop_yz_nt<192>(a, nb, st, ev);
         case 256: return prop_yz_nt<256>(a, nb, st, ev);
         case 512: return prop_yz_nt<512>(a, nb, st, ev);
         default: return hipErrorInvalidValue;
@@ -1818,8 +1821,9 @@ hipError_t launch_clean(const CleanArgs<T>& a, hipStream_t st) {
     hipLaunchKernelGGL(k_clean_renorm, dim3((a.F + 3) / 4), dim3(256), 0, st, a.coef, a.F, S,
                        a.coefE, a.n0, a.L, a.renorm);
     // 3. update on the matrix cores
-    e = launch_update_x3(a.d, a.F, ps, a.E, a.L, a.ng, a.coef, a.part32, st, mid);
-    if (e != hipSuccess) return e;
+    const bool fused = update_dens_fits(a.L);
+    e = launch_update_x3(a.d, a.F, ps, a.E, a.L, a.ng, a.coef, a.part32, st, mid, fused ? a.dens : nullptr);
+    if (e != hipSuccess || fused) return e;
   } else {
     // the same steps in FP64 (clean_f64.hip); the unperturbed set's
     // coefficients are the last L rows of coef
