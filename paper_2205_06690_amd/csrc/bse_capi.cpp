@@ -386,8 +386,8 @@ void poissonT(bse_system* s, int B, double* acc, double wn, int parts = 1) {
 // phases, so that the time steps of several systems can be interleaved:
 // results W^pol (FP64) in s->wpol, q in s->q.  Only kernel launches and
 // device-to-device work are issued, so the sequence can be captured into a
-// HIP graph.  The unperturbed set is propagated alongside, double-buffered:
-// H_0 in s->h0, H_n in hbuf[n & 1] for n >= 1.
+// HIP graph.  The unperturbed set is propagated alongside: H_0 in s->h0, H_n
+// in hbuf[n mod nbuf()] for n >= 1.
 template <typename T>
 struct PropRun {
   bse_system* s;
@@ -397,11 +397,15 @@ struct PropRun {
   bool half;             // the state is an end-of-step state (t = 0 or just cleaned)
   int parts;             // parts of the density the plane pass leaves
   int busy;              // planes of the systems propagated beside this one
+  // the unperturbed set's step n + 1 runs inside the pair passes of step n (two
+  // launches fewer a step: W of 2 pairs at 16^3 over 40 steps 1445 -> 1190 us), H_n in hbuf[n mod 3]
+  bool ahead;
+  int nbuf() const { return ahead ? 3 : 2; }
 };
 
 template <typename T>
-cplx<T>* prop_hbuf(bse_system* s, int n) {
-  return s->hbuf.as<cplx<T>>() + (size_t)(n & 1) * (size_t)s->L * s->ng;
+cplx<T>* prop_hbuf(bse_system* s, int n, int nbuf = 2) {
+  return s->hbuf.as<cplx<T>>() + (size_t)(n % nbuf) * (size_t)s->L * s->ng;
 }
 
 template <typename T>
@@ -460,7 +464,7 @@ void prop_unperturbed_step(PropRun<T>& r, int n, hipStream_t st) {
   using C = cplx<T>;
   bse_system* s = r.s;
   Tables& tb = tabs<T>(s);
-  C* hnext = prop_hbuf<T>(s, n + 1);
+  C* hnext = prop_hbuf<T>(s, n + 1, r.nbuf());
   PropXArgs<T> pe{};
   pe.din = r.hcur;
   pe.dout = hnext;
@@ -528,18 +532,25 @@ PropYZArgs<T> prop_pair_yz_args(bse_system* s, const cplx<T>* hnext) {
   pz.fused = y.fused_kind;
   return pz;
 }
-// the unperturbed set's step n, then the perturbed set's two passes of step n
+// the perturbed set's two passes of step n, after the unperturbed set's step n
+// or beside its step n + 1
 template <typename T>
 void prop_pair_passes(PropRun<T>& r, int n) {
   bse_system* s = r.s;
-  prop_unperturbed_step<T>(r, n, s->stream);
+  if (!r.ahead || n == 0) prop_unperturbed_step<T>(r, n, s->stream);
+  const int ne = r.ahead && n + 1 < s->cfg.n_steps ? s->L : 0;
   PropXArgs<T> px = prop_pair_x_args<T>(s, r.hcur, r.half);
   px.busy = r.busy;
+  px.ne = ne;
+  px.ein = prop_hbuf<T>(s, n + 1, r.nbuf());
+  px.eout = prop_hbuf<T>(s, n + 2, r.nbuf());
   auto* t1 = s->timer.slot("prop_x", 1);
   const LaunchEvents e1{t1 ? t1->first : nullptr, t1 ? t1->second : nullptr};
   HIPC(launch_prop_x<T>(s->n, px, r.B, s->stream, s->tune_tc, t1 ? &e1 : nullptr));
-  PropYZArgs<T> pz = prop_pair_yz_args<T>(s, prop_hbuf<T>(s, n + 1));
+  PropYZArgs<T> pz = prop_pair_yz_args<T>(s, prop_hbuf<T>(s, n + 1, r.nbuf()));
   pz.parts = r.parts;
+  pz.ne = ne;
+  pz.ed = px.eout;
   const YZSched y = yz_sched<T>(s);
   const bool split = !y.fused && prop_yz_split<T>(s->n);
   auto* t2 = s->timer.slot(split ? "prop_z" : "prop_yz", 1);
@@ -556,7 +567,7 @@ void prop_after_passes(PropRun<T>& r, int n) {
   bse_system* s = r.s;
   const int B = r.B;
   const int M = s->cfg.clean_every;
-  cplx<T>* hnext = prop_hbuf<T>(s, n + 1);
+  cplx<T>* hnext = prop_hbuf<T>(s, n + 1, r.nbuf());
   const bool do_clean = M > 0 && ((n + 1) % M == 0);
   const double wn = s->wts[n + 1];
   if (!do_clean) {
@@ -577,7 +588,9 @@ void prop_after_passes(PropRun<T>& r, int n) {
 
 template <typename T>
 void propagate_batch(bse_system* s, int B, const int* pq_dev, int busy = 0) {
-  PropRun<T> r{s, B, pq_dev, nullptr, true, prop_yz_parts<T>(s->n, B, s->L, yz_sched<T>(s).fused_kind, busy), busy};
+  PropRun<T> r{s, B, pq_dev, nullptr, true, prop_yz_parts<T>(s->n, B, s->L, yz_sched<T>(s).fused_kind, busy), busy, false};
+  // small batches, where the orbitals run apart (not the 112^3 plane pass)
+  r.ahead = r.parts > 1 && s->n <= 64;
   prop_begin<T>(r);
   for (int n = 0; n < s->cfg.n_steps; ++n) {
     prop_pair_passes<T>(r, n);   // with the unperturbed set's step
@@ -594,7 +607,7 @@ void prepare_unperturbed(bse_system* s) {
   const int L = s->L;
   const size_t hstride = (size_t)L * ng;
   s->h0.alloc(sizeof(C) * hstride);
-  s->hbuf.alloc(sizeof(C) * hstride * 2);
+  s->hbuf.alloc(sizeof(C) * hstride * 3);
   s->eta0.alloc(sizeof(double) * hstride);
   s->n0.alloc(sizeof(double) * L);
   if (!s->deterministic) {
@@ -1548,7 +1561,7 @@ void batch_list_run(int n_sys, bse_system* const* sys, const int32_t* n_pairs, v
                     const BatchList& bl, hipStream_t st) {
   std::vector<PropRun<float>> runs(n_sys);
   for (int i = 0; i < n_sys; ++i) {
-    runs[i] = PropRun<float>{sys[i], n_pairs[i], sys[i]->pq_d.as<int>(), nullptr, true, 1, 0};
+    runs[i] = PropRun<float>{sys[i], n_pairs[i], sys[i]->pq_d.as<int>(), nullptr, true, 1, 0, false};
     prop_begin<float>(runs[i]);
   }
   const int N = sys[0]->cfg.n_steps;

@@ -226,6 +226,26 @@ __global__ void __launch_bounds__(4 * TC, 3) k_kin_x(PropXArgs<double> a) {
   kin_x_item<N, ETA>(a, f / a.ls, tile * TC, f % a.ls, a.ls, KinMat<N>(tab, threadIdx.x & 63));
 }
 
+// the pairs and the ne fields of the unperturbed set, one step ahead, in one
+// launch
+template <int N, int TC>
+__global__ void __launch_bounds__(4 * TC, 3) k_kin_x_both(PropXArgs<double> a) {
+  __shared__ double2 tab[KinMat<N>::E];
+  int f, tile;
+  if (!field_tile(a.order, a.nf * a.ls + a.ne, N * N / TC, f, tile)) return;
+  KinMat<N>::stage(tab, a.kin, 4 * TC);
+  __syncthreads();
+  const KinMat<N> mat(tab, threadIdx.x & 63);
+  if (f < a.nf * a.ls) {
+    kin_x_item<N, false>(a, f / a.ls, tile * TC, f % a.ls, a.ls, mat);
+  } else {
+    PropXArgs<double> e = a;
+    e.din = a.ein;
+    e.dout = a.eout;
+    kin_x_item<N, true>(e, f - a.nf * a.ls, tile * TC, 0, 1, mat);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // plane pass: the y and z factors on P whole y-z planes, and the induced
 // density dn_b = 4 sum_l Re(conj(H_l) d_{b,l}) of the post-kinetic state
@@ -380,8 +400,17 @@ __global__ void __launch_bounds__(KinYZ<N>::template threads<W>(), 2) k_kin_yz(P
   double2* tab = lds + Y::P * W * N * Y::S;
   KinMat<N>::stage(tab, a.kin, Y::template threads<W>());
   __syncthreads();
-  kin_yz_item<N, W, DENS>(a, blockIdx.x * Y::P * W, blockIdx.y, a.parts > 1, blockIdx.z, lds,
-                          KinMat<N>(tab, threadIdx.x & 63));
+  const KinMat<N> mat(tab, threadIdx.x & 63);
+  if (DENS && (int)blockIdx.y >= a.nf) {
+    // a field of the unperturbed set, one step ahead, beside the pairs
+    const int fe = ((int)blockIdx.y - a.nf) * a.parts + (int)blockIdx.z;
+    if (fe >= a.ne) return;
+    PropYZArgs<double> e = a;
+    e.d = a.ed;
+    kin_yz_item<N, W, false>(e, blockIdx.x * Y::P * W, fe, false, 0, lds, mat);
+    return;
+  }
+  kin_yz_item<N, W, DENS>(a, blockIdx.x * Y::P * W, blockIdx.y, a.parts > 1, blockIdx.z, lds, mat);
 }
 
 // ---------------------------------------------------------------------------
@@ -405,8 +434,9 @@ static hipError_t kin_x_tc(const PropXArgs<double>& a, int F, hipStream_t st, co
   // a pair's orbitals go to several waves while those are fewer than eight on
   // a SIMD (24^3, 8 pairs: 20.6 us unsplit, 9 split in ten)
   b.ls = a.mode == PX_ETA0 ? 1 : std::max(1, std::min(a.L, 8192 / (F * (N * N / 16) + a.busy)));
-  const dim3 grid = field_tile_grid(a.order, F * b.ls, N * N / TC);
+  const dim3 grid = field_tile_grid(a.order, F * b.ls + a.ne, N * N / TC);
   if (a.mode == PX_ETA0) return kin_go(k_kin_x<N, TC, true>, grid, 4 * TC, 0, st, ev, b);
+  if (a.ne > 0) return kin_go(k_kin_x_both<N, TC>, grid, 4 * TC, 0, st, ev, b);
   return kin_go(k_kin_x<N, TC, false>, grid, 4 * TC, 0, st, ev, b);
 }
 template <int N>
@@ -435,7 +465,8 @@ static hipError_t kin_yz_w(const PropYZArgs<double>& a, int nb, hipStream_t st, 
   b.nf = nb;
   if (!a.density) b.parts = 1;
   if (b.parts != 1 && b.parts != Y::G) return hipErrorInvalidValue;
-  const dim3 grid(N / (Y::P * W), nb, b.parts);
+  if (a.ne > 0 && (b.parts < 2 || !a.ed)) return hipErrorInvalidValue;
+  const dim3 grid(N / (Y::P * W), nb + (a.ne + b.parts - 1) / b.parts, b.parts);
   const int nt = Y::template threads<W>();
   const size_t lds = Y::template lds<W>();
   if (a.density) return kin_go(k_kin_yz<N, W, true>, grid, nt, lds, st, ev, b);

@@ -51,6 +51,10 @@ template <typename T> struct PropXArgs {
   int nf;              // fields (or pairs) of the launch; set by the launcher
   int ls;              // groups of a pair's orbitals, workgroups apart; set by the launcher
   int busy;            // planes (n x pairs) of other systems that share the chip
+  // the unperturbed set one step ahead in the same launch (ne = 0: not)
+  const cplx<T>* ein;
+  cplx<T>* eout;
+  int ne;              // its fields
 };
 
 template <typename T> struct PropYZArgs {
@@ -61,6 +65,8 @@ template <typename T> struct PropYZArgs {
   const cplx<T>* kin;  // as PropXArgs::kin
   T* dens;             // [parts][B][ng]
   int parts;           // 1, or prop_yz_parts: partial sums, unscaled
+  cplx<T>* ed;         // with parts > 1, nullable: the unperturbed set one step ahead
+  int ne;              // its fields (0: none)
   int L;
   int density;
   int order;           // workgroup order of the y-line pass, as PropXArgs::order

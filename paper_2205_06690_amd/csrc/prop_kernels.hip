@@ -195,6 +195,24 @@ __global__ void __launch_bounds__(256) k_prop_x(PropXArgs<T> a) {
   prop_x_item<N, TC, T, ETA>(a, fb / a.ls, tile, fb % a.ls, a.ls, reinterpret_cast<cplx<T>*>(smem_raw));
 }
 
+// the pairs and the ne fields of the unperturbed set, one step ahead, in one
+// launch: on small batches either alone is mostly launch and latency
+template <int N, int TC, typename T>
+__global__ void __launch_bounds__(256) k_prop_x_both(PropXArgs<T> a) {
+  extern __shared__ unsigned char smem_raw[];
+  cplx<T>* s = reinterpret_cast<cplx<T>*>(smem_raw);
+  int f, tile;
+  if (!field_tile(a.order, a.nf * a.ls + a.ne, N * N / TC, f, tile)) return;
+  if (f < a.nf * a.ls) {
+    prop_x_item<N, TC, T, false>(a, f / a.ls, tile, f % a.ls, a.ls, s);
+  } else {
+    PropXArgs<T> e = a;
+    e.din = a.ein;
+    e.dout = a.eout;
+    prop_x_item<N, TC, T, true>(e, f - a.nf * a.ls, tile, 0, 1, s);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // prop_yz: y and z factors of exp(-iT dt) on a whole y-z plane, plus the
 // induced density dn_b = 4 sum_l Re(conj(H_l) d_{b,l}) of the post-kinetic
@@ -311,10 +329,14 @@ __global__ void __launch_bounds__(NT) k_prop_yz(PropYZArgs<T> a) {
   // grid: (x planes, fields or pairs) with the plane fastest: blocks running
   // together stream consecutive planes of one field (measured faster than
   // sharing the H planes across pairs, which the x pass gains from)
-  if (DENS) {
+  if (DENS && !(PART && (int)blockIdx.y >= a.nf)) {
     prop_yz_pair_item<N, T, NT, PART>(a, blockIdx.x, blockIdx.y, s);
     return;
   }
+  // a field of the unperturbed set: of this launch, or one step ahead beside
+  // the pairs
+  const int fe = PART ? ((int)blockIdx.y - a.nf) * a.parts + (int)blockIdx.z : (int)blockIdx.y;
+  if (PART && fe >= a.ne) return;
   constexpr int P = N * N;
   const int ng = N * N * N;
   const int x = blockIdx.x;
@@ -322,7 +344,7 @@ __global__ void __launch_bounds__(NT) k_prop_yz(PropYZArgs<T> a) {
   const size_t poff = (size_t)x * P;
   C* tws = s + N * plane_stride<N>();
   stage_tables<N>(tws, a.tw, a.kph, tid, NT);
-  C* d = a.d + (size_t)blockIdx.y * ng + poff;
+  C* d = (PART ? a.ed : a.d) + (size_t)fe * ng + poff;
   for (int e = tid; e < P; e += NT) s[plane_idx<N>(e)] = d[e];
   __syncthreads();
   kinetic_yz_plane<N, T, NT>(s, tws, tws + N, tid);
@@ -1496,10 +1518,12 @@ struct Launch {
       PropXArgs<T> b = a;
       b.nf = F;
       b.ls = a.mode == PX_ETA0 ? 1 : x_groups(F * (N * N / TC) + a.busy, a.L);
-      const dim3 grid = field_tile_grid(a.order, F * b.ls, N * N / TC);
+      const dim3 grid = field_tile_grid(a.order, F * b.ls + a.ne, N * N / TC);
       size_t sm = x_lds<N, TC, T>();
       if (a.mode == PX_ETA0)
         go(k_prop_x<N, TC, T, true>, grid, dim3(256), sm, st, ev, b);
+      else if (a.ne > 0)
+        go(k_prop_x_both<N, TC, T>, grid, dim3(256), sm, st, ev, b);
       else
         go(k_prop_x<N, TC, T, false>, grid, dim3(256), sm, st, ev, b);
       return hipGetLastError();
@@ -1525,8 +1549,9 @@ struct Launch {
     PropYZArgs<T> b = a;
     b.nf = nb;
     if (a.density && a.parts != 1 && a.parts != a.L) return hipErrorInvalidValue;
+    if (a.ne > 0 && (a.parts < 2 || !a.ed)) return hipErrorInvalidValue;
     if (a.density && a.parts > 1)
-      go(k_prop_yz<N, T, NT, true, true>, dim3(N, nb, a.parts), dim3(NT), sm, st, ev, b);
+      go(k_prop_yz<N, T, NT, true, true>, dim3(N, nb + (a.ne + a.parts - 1) / a.parts, a.parts), dim3(NT), sm, st, ev, b);
     else if (a.density)
       go(k_prop_yz<N, T, NT, true, false>, dim3(N, nb), dim3(NT), sm, st, ev, b);
     else
@@ -1630,6 +1655,7 @@ struct Launch {
       const int smx = (int)x_lds<N, TC, T>();
       (void)hipFuncSetAttribute((const void*)k_prop_x<N, TC, T, true>, hipFuncAttributeMaxDynamicSharedMemorySize, smx);
       (void)hipFuncSetAttribute((const void*)k_prop_x<N, TC, T, false>, hipFuncAttributeMaxDynamicSharedMemorySize, smx);
+      (void)hipFuncSetAttribute((const void*)k_prop_x_both<N, TC, T>, hipFuncAttributeMaxDynamicSharedMemorySize, smx);
     }
   }
   template <int NT> static void conf_yz() {
