@@ -813,7 +813,10 @@ void build_a(bse_system* s, int n_o, int n_c, double* A_host) {
   // dipoles of the transitions for the spectrum
   HIPC(hipMemcpyAsync(pq.p, pia.data(), sizeof(int) * 2 * n_ia, hipMemcpyHostToDevice, st));
   s->f0_d.alloc(sizeof(double) * 3 * n_ia);
-  HIPC(launch_dipoles(s->phi64.as<double>(), pq.as<int>(), n_ia, s->n, s->cfg.h, s->f0_d.as<double>(), st));
+  DBuf dpart;
+  dpart.alloc(sizeof(double) * dipoles_part_elems(n_ia));
+  HIPC(launch_dipoles(s->phi64.as<double>(), pq.as<int>(), n_ia, s->n, s->cfg.h, dpart.as<double>(),
+                      s->f0_d.as<double>(), st));
   HIPC(hipMemcpyAsync(A_host, s->A_d.p, sizeof(double) * (size_t)n_ia * n_ia, hipMemcpyDeviceToHost, st));
   HIPC(hipStreamSynchronize(st));
   for (size_t k = 0; k < (size_t)n_ia * n_ia; ++k)

@@ -13,7 +13,9 @@ hipError_t launch_products(const double* phi, const int* pq, int K, size_t ng, T
 hipError_t launch_assemble_a(const double* X, const double* D, int no, int nc, int nij,
                              const double* eps_v, const double* eps_c, double scissors, double* A,
                              hipStream_t st);
-hipError_t launch_dipoles(const double* phi, const int* pq, int K, int n, double h, double* f0,
+// part holds dipoles_part_elems(K) doubles
+size_t dipoles_part_elems(int K);
+hipError_t launch_dipoles(const double* phi, const int* pq, int K, int n, double h, double* part, double* f0,
                           hipStream_t st);
 hipError_t launch_gemv(const double* A, int n, const double* v, double* y, hipStream_t st);
 // w -= V^T-projection onto the first m basis vectors (c = V w); c[m-1] also to *last

@@ -68,17 +68,22 @@ __global__ void k_assemble_a(const double* __restrict__ X, const double* __restr
 }
 
 // f0[k][ax] = h^3 sum_r phi_p phi_q (r_ax - centre) for (p, q) = pq[k]
+// A product's DIP_NB blocks leave part[k][block][3], k_dipole_sums adds them in
+// order (64^3, 200 products: one block each 436 us).
+constexpr int DIP_NB = 16;
 __global__ void __launch_bounds__(256) k_dipoles(const double* __restrict__ phi,
                                                  const int* __restrict__ pq, int n, double h,
-                                                 double* __restrict__ f0) {
+                                                 double* __restrict__ part) {
   const int k = blockIdx.x;
   const int p = pq[2 * k], q = pq[2 * k + 1];
   const size_t ng = (size_t)n * n * n;
+  const size_t per = (ng + DIP_NB - 1) / DIP_NB, r0 = blockIdx.y * per, r1 = min(ng, r0 + per);
   const double c = 0.5 * n * h;
   double sx = 0, sy = 0, sz = 0;
-  for (size_t r = threadIdx.x; r < ng; r += 256) {
+#pragma unroll 4
+  for (size_t r = r0 + threadIdx.x; r < r1; r += 256) {
     const double v = phi[(size_t)p * ng + r] * phi[(size_t)q * ng + r];
-    const int x = (int)(r / ((size_t)n * n)), y = (int)((r / n) % n), z = (int)(r % n);
+    const unsigned xy = (unsigned)(r / n), x = xy / n, y = xy % n, z = (unsigned)(r % n);
     sx += v * (x * h - c);
     sy += v * (y * h - c);
     sz += v * (z * h - c);
@@ -93,8 +98,17 @@ __global__ void __launch_bounds__(256) k_dipoles(const double* __restrict__ phi,
       for (int a = 0; a < 3; ++a) red[a][threadIdx.x] += red[a][threadIdx.x + s];
     __syncthreads();
   }
-  if (threadIdx.x == 0)
-    for (int a = 0; a < 3; ++a) f0[(size_t)k * 3 + a] = red[a][0] * h * h * h;
+  if (threadIdx.x < 3) part[((size_t)k * DIP_NB + blockIdx.y) * 3 + threadIdx.x] = red[threadIdx.x][0];
+}
+__global__ void __launch_bounds__(64) k_dipole_sums(const double* __restrict__ part, int n, double h3,
+                                                    double* __restrict__ f0) {
+  const int i = blockIdx.x * 64 + threadIdx.x;   // product, axis
+  if (i >= n) return;
+  const double* p = part + (size_t)(i / 3) * DIP_NB * 3 + i % 3;
+  double s = 0;
+#pragma unroll
+  for (int k = 0; k < DIP_NB; ++k) s += p[3 * k];
+  f0[i] = s * h3;
 }
 
 // ---------------------------------------------------------------------------
@@ -749,9 +763,11 @@ hipError_t launch_assemble_a(const double* X, const double* D, int no, int nc, i
   return hipGetLastError();
 }
 
-hipError_t launch_dipoles(const double* phi, const int* pq, int K, int n, double h, double* f0,
+size_t dipoles_part_elems(int K) { return (size_t)K * DIP_NB * 3; }
+hipError_t launch_dipoles(const double* phi, const int* pq, int K, int n, double h, double* part, double* f0,
                           hipStream_t st) {
-  hipLaunchKernelGGL(k_dipoles, dim3(K), dim3(256), 0, st, phi, pq, n, h, f0);
+  hipLaunchKernelGGL(k_dipoles, dim3(K, DIP_NB), dim3(256), 0, st, phi, pq, n, h, part);
+  hipLaunchKernelGGL(k_dipole_sums, dim3((3 * K + 63) / 64), dim3(64), 0, st, part, 3 * K, h * h * h, f0);
   return hipGetLastError();
 }
 
