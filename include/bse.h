@@ -353,7 +353,8 @@ void bse_batch_plan_destroy(bse_batch_plan* plan);
  * system's grid, precision and a batch of n_pairs pairs and keeps the
  * fastest for later calls: the x pass's tile width (16, 32, 64) and
  * workgroup order (bse_set_launch_order bit 0); the plane pass's block size
- * (256, 512; in FP64 up to 64^3 its default workgroup or twice the planes),
+ * (256, 512; at 24^3 in mixed precision 256 is the default block of 192; in
+ * FP64 up to 64^3 256 is its default workgroup, 512 twice the planes),
  * or where the y and z factors run as one register-line pass
  * (112^3 in mixed precision, unless bse_set_yz_schedule chose the line
  * passes) its 16-point DFT schedule (2 or 0) and workgroup order (bit 2).

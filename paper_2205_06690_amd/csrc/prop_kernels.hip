@@ -1622,9 +1622,12 @@ struct Launch {
     } else if constexpr (KIN_YZ) {
       return launch_kin_yz(N, a, nb, st, nt, ev);
     } else {
-      if (nt == 0) nt = yz_threads<N>();
+      // the shapes on offer are the default (0), 256 and 512 threads; where the
+      // default is below 256 it stands for 256 (24 points: never the slower)
+      constexpr int DEF = yz_threads<N>();
+      if (nt == 0 || (DEF < 256 && nt == 256)) nt = DEF;
+      if (nt == DEF) return prop_yz_nt<DEF>(a, nb, st, ev);
       switch (nt) {
-        case 192: return prop_yz_nt<192>(a, nb, st, ev);
         case 256: return prop_yz_nt<256>(a, nb, st, ev);
         case 512: return prop_yz_nt<512>(a, nb, st, ev);
         default: return hipErrorInvalidValue;
@@ -1684,6 +1687,7 @@ struct Launch {
     if constexpr (KIN_YZ) {
       configure_kin(N);
     } else {
+      conf_yz<NT>();
       conf_yz<256>();
       conf_yz<512>();
     }
