@@ -532,25 +532,30 @@ PropYZArgs<T> prop_pair_yz_args(bse_system* s, const cplx<T>* hnext) {
   pz.fused = y.fused_kind;
   return pz;
 }
+// the shape of the perturbed set's two passes: their parts, the systems beside
+// them and, where the unperturbed set runs along, its step from ein to eout
+template <typename T>
+void prop_beside(const PropRun<T>& r, bool along, const cplx<T>* ein, cplx<T>* eout, PropXArgs<T>& px,
+                 PropYZArgs<T>& pz) {
+  px.busy = r.busy;
+  px.ne = pz.ne = along ? r.s->L : 0;
+  px.ein = ein;
+  px.eout = pz.ed = eout;
+  pz.parts = r.parts;
+}
 // the perturbed set's two passes of step n, after the unperturbed set's step n
 // or beside its step n + 1
 template <typename T>
 void prop_pair_passes(PropRun<T>& r, int n) {
   bse_system* s = r.s;
   if (!r.ahead || n == 0) prop_unperturbed_step<T>(r, n, s->stream);
-  const int ne = r.ahead && n + 1 < s->cfg.n_steps ? s->L : 0;
   PropXArgs<T> px = prop_pair_x_args<T>(s, r.hcur, r.half);
-  px.busy = r.busy;
-  px.ne = ne;
-  px.ein = prop_hbuf<T>(s, n + 1, r.nbuf());
-  px.eout = prop_hbuf<T>(s, n + 2, r.nbuf());
+  PropYZArgs<T> pz = prop_pair_yz_args<T>(s, prop_hbuf<T>(s, n + 1, r.nbuf()));
+  prop_beside<T>(r, r.ahead && n + 1 < s->cfg.n_steps, prop_hbuf<T>(s, n + 1, r.nbuf()),
+                 prop_hbuf<T>(s, n + 2, r.nbuf()), px, pz);
   auto* t1 = s->timer.slot("prop_x", 1);
   const LaunchEvents e1{t1 ? t1->first : nullptr, t1 ? t1->second : nullptr};
   HIPC(launch_prop_x<T>(s->n, px, r.B, s->stream, s->tune_tc, t1 ? &e1 : nullptr));
-  PropYZArgs<T> pz = prop_pair_yz_args<T>(s, prop_hbuf<T>(s, n + 1, r.nbuf()));
-  pz.parts = r.parts;
-  pz.ne = ne;
-  pz.ed = px.eout;
   const YZSched y = yz_sched<T>(s);
   const bool split = !y.fused && prop_yz_split<T>(s->n);
   auto* t2 = s->timer.slot(split ? "prop_z" : "prop_yz", 1);
@@ -587,10 +592,15 @@ void prop_after_passes(PropRun<T>& r, int n) {
 }
 
 template <typename T>
-void propagate_batch(bse_system* s, int B, const int* pq_dev, int busy = 0) {
-  PropRun<T> r{s, B, pq_dev, nullptr, true, prop_yz_parts<T>(s->n, B, s->L, yz_sched<T>(s).fused_kind, busy), busy, false};
+PropRun<T> prop_run(bse_system* s, int B, const int* pq_dev, int busy, int fused_kind) {
+  PropRun<T> r{s, B, pq_dev, nullptr, true, prop_yz_parts<T>(s->n, B, s->L, fused_kind, busy), busy, false};
   // small batches, where the orbitals run apart (not the 112^3 plane pass)
   r.ahead = r.parts > 1 && s->n <= 64;
+  return r;
+}
+template <typename T>
+void propagate_batch(bse_system* s, int B, const int* pq_dev, int busy = 0) {
+  PropRun<T> r = prop_run<T>(s, B, pq_dev, busy, yz_sched<T>(s).fused_kind);
   prop_begin<T>(r);
   for (int n = 0; n < s->cfg.n_steps; ++n) {
     prop_pair_passes<T>(r, n);   // with the unperturbed set's step
@@ -1445,7 +1455,14 @@ void autotune_t(bse_system* s, int B, const char* cache_path) {
   HIPC(launch_fill_zero(s->u.p, sizeof(T) * s->ng * (size_t)B, s->stream));
   PropXArgs<T> px = prop_pair_x_args<T>(s, s->h0.as<C>(), false);
   PropYZArgs<T> pz = prop_pair_yz_args<T>(s, s->h0.as<C>());
-  pz.parts = 1;
+  // the launches that a batch of B pairs makes: in parts and with the
+  // unperturbed set beside the pairs where it runs so (64^3, 1 pair of 10
+  // orbitals: 26 us with both, where the whole pass of the pair alone took 53)
+  const auto issued = [&](int fused_kind) {
+    const PropRun<T> r = prop_run<T>(s, B, nullptr, 0, fused_kind);
+    prop_beside<T>(r, r.ahead, s->h0.as<C>(), prop_hbuf<T>(s, 0), px, pz);
+  };
+  issued(pz.fused);
   float best_x = 1e30f, best_yz = 1e30f;
   int tc_best = 0, nt_best = 0, ox_best = 0, sched_best = -1, oz_best = 0;
   for (int ox : {0, 1})
@@ -1458,6 +1475,7 @@ void autotune_t(bse_system* s, int B, const char* cache_path) {
     for (int sched : {2, 0})
       for (int oz : {0, 1}) {
         pz.fused = sched == 2 ? 2 : 1;
+        issued(pz.fused);
         pz.order = oz;
         const float ms = time_launches<T>(s, 5, [&]() { return launch_prop_yz<T>(s->n, pz, B, s->stream, 0); });
         if (ms > 0 && ms < best_yz) { best_yz = ms; sched_best = sched; oz_best = oz; }

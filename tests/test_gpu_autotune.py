@@ -46,3 +46,22 @@ def test_default_plane_shape_is_kept_at_24():
     assert nt in (256, 512)
     assert after < 1.1 * before
     s.close()
+
+
+@pytest.mark.parametrize("n,L,B,fp64", [(64, 10, 1, False), (32, 6, 2, False), (48, 8, 1, True), (64, 10, 12, False)])
+def test_timed_launches_are_those_that_run(n, L, B, fp64, tmp_path):
+    """The times behind a choice (written to the cache file) are those of the
+    passes of a batch of this size: where a small batch runs its orbitals in
+    parts and the unperturbed set beside the pairs, the passes timed do so
+    too.  Whole, the plane pass of one 64^3 pair takes three times as long; a
+    factor of 1.5 is left for the gaps between launches."""
+    s = _system(n, L, B, fp64)
+    cache = str(tmp_path / "tune.txt")
+    s.autotune(B, cache)
+    x, yz = _pass_times(s, B)
+    f = open(cache).read().split()
+    say(f"{n}^3 {'FP64' if fp64 else 'mixed'} {B} pairs: x pass {x * 1e3:.1f} us, timed {float(f[3]) * 1e3:.1f}; "
+        f"plane pass {yz * 1e3:.1f} us, timed {float(f[4]) * 1e3:.1f}")
+    for ran, timed in ((x, float(f[3])), (yz, float(f[4]))):
+        assert timed < 1.5 * ran + 2e-3 and ran < 1.5 * timed + 2e-3
+    s.close()
