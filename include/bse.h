@@ -362,6 +362,8 @@ void bse_batch_plan_destroy(bse_batch_plan* plan);
  * agree to FP32 rounding.  cache_path (nullable) is a text
  * file of "key tc nt ms_x ms_yz ox sched oz" lines (sched -1 where not
  * tuned): a matching key is used without timing, a new result is appended.
+ * The key names the kernels that the numbers select, so lines that other
+ * kernels wrote are not applied.
  * Overwrites the system's pair workspace. */
 bse_status bse_autotune(bse_system* sys, int32_t n_pairs, const char* cache_path);
 /* The tuned x-tile width and plane-pass block size (0 = built-in default,

@@ -1418,7 +1418,9 @@ template <typename T>
 void autotune_t(bse_system* s, int B, const char* cache_path) {
   using C = cplx<T>;
   char key[128];
-  std::snprintf(key, sizeof(key), "n%d_%s_B%d_L%d", s->n, sizeof(T) == 4 ? "f32" : "f64", B, s->L);
+  // v2: the kernels that a stored tile and block select (a line of former
+  // kernels is left alone and timed anew; raise it when they change)
+  std::snprintf(key, sizeof(key), "v2_n%d_%s_B%d_L%d", s->n, sizeof(T) == 4 ? "f32" : "f64", B, s->L);
   // the choices a result sets: the x tile, the plane block size (0 where
   // the y-z factors run as one register-line pass), the x pass's workgroup
   // order, and for the one-pass y-z kernel its 16-point DFT schedule and order
@@ -1442,7 +1444,7 @@ void autotune_t(bse_system* s, int B, const char* cache_path) {
       int tc = 0, nt = 0, ox = s->launch_order & 1, sched = -1, oz = 0;
       float mx = 0, myz = 0;
       if (is >> k >> tc >> nt && k == key) {
-        // lines written before the orders were tuned end after the times
+        // a line may end after the times
         if (is >> mx >> myz >> ox) is >> sched >> oz;
         apply(tc, nt, ox, sched, oz);
         return;

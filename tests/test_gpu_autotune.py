@@ -65,3 +65,19 @@ def test_timed_launches_are_those_that_run(n, L, B, fp64, tmp_path):
     for ran, timed in ((x, float(f[3])), (yz, float(f[4]))):
         assert timed < 1.5 * ran + 2e-3 and ran < 1.5 * timed + 2e-3
     s.close()
+
+
+def test_lines_of_former_kernels_are_not_applied(tmp_path):
+    """A cache line written for other kernels (its key without their version)
+    is timed anew and stays in the file; the new line is then read."""
+    cache = tmp_path / "tune.txt"
+    old = "n24_f64_B3_L4 16 512 0.001 0.001 0 -1 0\n"
+    cache.write_text(old)
+    s = _system(24, 4, 3, fp64=True)
+    shape = s.autotune(3, str(cache))
+    lines = cache.read_text().splitlines(keepends=True)
+    say(f"24^3 FP64: {lines}")
+    assert lines[0] == old and len(lines) == 2
+    assert s.autotune(3, str(cache)) == shape
+    assert cache.read_text() == "".join(lines)
+    s.close()
