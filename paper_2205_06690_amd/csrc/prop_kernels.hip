@@ -1754,13 +1754,24 @@ hipError_t launch_prop_yz(int n, const PropYZArgs<T>& a, int nb, hipStream_t st,
 // the Poisson solve, cost more than they give (FP32, 10 orbitals, together ->
 // apart: 16^3 2 pairs 8.0 -> 3.5 us, 24^3 8 pairs 31 -> 10, 32^3 21 pairs 41 ->
 // 31 but 48 pairs 71 -> 60 plus 12 in the solve; 48^3 12 pairs 92 -> 76; 64^3 1
-// pair 55 -> 18, 4 pairs 61 -> 46, 8 pairs 86 -> 90).
+// pair 55 -> 18, 4 pairs 61 -> 46, 8 pairs 86 -> 90).  A part is half of its
+// orbital's state, so with many orbitals the line also lies where state and
+// parts stop fitting the 256 MB last-level cache beside what else a step
+// touches; beyond it parts pay only for half as many planes (calls of 10 steps,
+// together -> apart: 32^3 24 pairs, 20 orbitals 1.71 -> 1.59 ms, 30 2.30 -> 2.72;
+// 12 pairs, 120 6.4 -> 5.9; 48^3 13 pairs, 11 2.39 -> 2.25, 20 3.92 -> 4.44; 6
+// pairs, 240 30.6 -> 24.9; 64^3 4 pairs, 10 1.64 -> 1.54, 12 1.81 -> 1.93; 2
+// pairs, 240 23.6 -> 21.8; 112^3 10 orbitals, 1 pair 4.65 -> 4.15, 2 5.55 -> 5.73).
 template <typename T>
 int prop_yz_parts(int n, int B, int L, int fused, int busy) {
   if (std::is_same<T, double>::value) return kin_yz_parts(n, B, busy);
   if (n == 112 && fused != 2) return 1;
-  const int most = n <= 32 ? 800 : n == 48 ? 640 : 320;
-  return n * B + busy < most ? L : 1;
+  // bytes a step touches in parts: the state and its parts (12 a point, orbital
+  // and pair), both buffers of the unperturbed set, potentials, phases
+  const double bytes = (double)n * n * n * (12.0 * B * L + 16.0 * L + 16.0 * B + 16.0);
+  const int most = n <= 32 ? 800 : n == 48 ? 640 : 320;   // planes
+  const bool fits = bytes < (n < 64 ? 240e6 : 210e6);
+  return n * B + busy < (n < 112 && fits ? most : most / 2) ? L : 1;
 }
 template <typename T>
 bool prop_yz_split(int n) {

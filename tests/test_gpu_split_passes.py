@@ -35,3 +35,32 @@ def test_split_and_unsplit_passes_agree(n, fp64, n_stoch, small, large):
     assert np.isfinite(res[0]).all()
     print(f"{n}^3 L {n_stoch}, {small} and {large} pairs: max|dW| {np.abs(res[0] - res[1]).max():.1e}", flush=True)
     assert np.array_equal(res[0], res[1])
+
+
+def test_parts_of_many_orbitals_are_not_slower():
+    """With many orbitals the partial densities outgrow the last-level cache and
+    the pairs run whole: 24 pairs of 30 orbitals at 32^3 (768 planes, in parts
+    with fewer orbitals) must not take longer than 25, which always run whole
+    (5 % for the clock; 13 % slower in parts)."""
+    import time
+    import torch
+    from paper_2205_06690_amd import bse
+    n, h, n_occ, L = 32, 0.5, 6, 30
+    rng = np.random.default_rng(2)
+    s = bse.System(n, h, np.zeros(n ** 3), n_occ=n_occ, n_stoch=L, seed=3, dt=0.05, n_steps=20, gamma=0.5,
+                   clean_every=0, precision=bse.BSE_MIXED, max_batch=25)
+    s.set_orbitals(rng.standard_normal((n_occ, n ** 3)) / (n * h) ** 1.5, np.zeros(n_occ))
+    pq = torch.from_numpy(rng.integers(0, n_occ, (25, 2)).astype(np.int32)).cuda()
+    w = torch.empty((25, n ** 3), dtype=torch.float64, device="cuda")
+    t = {24: [], 25: []}
+    for k in range(8):
+        for B in t:
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            s.apply_w_device(pq[:B], w[:B])
+            torch.cuda.synchronize()
+            t[B].append(time.perf_counter() - t0)
+    a, b = min(t[24][1:]), min(t[25][1:])
+    print(f"32^3, 30 orbitals: 24 pairs {a * 1e3:.2f} ms, 25 pairs {b * 1e3:.2f} ms", flush=True)
+    assert a < 1.05 * b
+    s.close()
