@@ -207,7 +207,9 @@ struct bse_system {
   DBuf n0dens, vdev, fx, fy, fscale, fdots, fwpol;
   DBuf ch_ws, ch_dens;   // Chebyshev spectrum and exciton states
   DBuf mx_v, mx_pp;      // recursion vectors and partials of the mixed spectrum
-  DBuf mx_f, mx_tf, mx_out, mx_rho, mx_dv, mx_c, mx_part, mx_eps;  // matrix-free A f
+  // matrix-free A f; transforms of its own (mx_work): the batch workspace is
+  // sized by batches alone, so that these calls never move it under a plan
+  DBuf mx_f, mx_tf, mx_out, mx_rho, mx_dv, mx_c, mx_part, mx_eps, mx_work;
   int mx_eps_v0 = -1, mx_eps_n = 0;   // valence window whose eps mx_eps holds
   DBuf bnd_n, bnd_v, bnd_part;   // boundary potential: density, v_H, block sums
   double n0_scale = 0, v_scale = 0;
@@ -267,16 +269,18 @@ template <typename T> Tables& tabs(bse_system* s);
 template <> Tables& tabs<float>(bse_system* s) { return s->tf; }
 template <> Tables& tabs<double>(bse_system* s) { return s->td; }
 
-// Coulomb potential of B real FP64 densities (rho64) into q (FP64)
+// Coulomb potential of B real FP64 densities (rho64) into q (FP64), its
+// transforms in `work` (the batch workspace unless given)
 void poisson64(bse_system* s, const double* rho, int B, double* out, double* acc, double wn,
-               int* flags = nullptr) {
+               int* flags = nullptr, DBuf* work = nullptr) {
   const size_t need = sizeof(cplx<double>) * s->ng * (size_t)((B + 1) / 2);
-  s->work64.alloc(need);
+  if (!work) work = &s->work64;
+  work->alloc(need);
   PoisArgs<double> a{};
   a.flags = flags;
   a.rho = rho;
   a.B = B;
-  a.work = s->work64.as<cplx<double>>();
+  a.work = work->as<cplx<double>>();
   a.tw = s->td.tw.as<cplx<double>>();
   a.k2 = s->td.k2.as<double>();
   a.vscale = 4.0 * M_PI / (double)s->ng;
@@ -979,7 +983,7 @@ void apply_abar_device(bse_system* s, const double* f_dev, int n_vec, double* af
   s->mx_dv.alloc(sizeof(double) * ng * n_vec);
   s->mx_c.alloc(sizeof(double) * (size_t)nf * S);
   s->mx_part.alloc(sizeof(double) * gemm_part_elems(nf, S, ng));
-  s->work64.alloc(sizeof(cplx<double>) * ng * (size_t)((nf + 1) / 2));
+  s->mx_work.alloc(sizeof(cplx<double>) * ng * (size_t)((nf + 1) / 2));
   if (!s->vdev.p || s->vdev.bytes < sizeof(double) * ng) {
     s->vdev.alloc(sizeof(double) * ng);
     HIPC(hipMemcpy(s->vdev.p, s->vext.data(), sizeof(double) * ng, hipMemcpyHostToDevice));
@@ -995,7 +999,7 @@ void apply_abar_device(bse_system* s, const double* f_dev, int n_vec, double* af
   PoisArgs<double> a{};
   a.rho = f_dev;
   a.B = nf;
-  a.work = s->work64.as<cplx<double>>();
+  a.work = s->mx_work.as<cplx<double>>();
   a.tw = s->td.tw.as<cplx<double>>();
   a.k2 = s->td.k2.as<double>();
   a.vscale = 1.0 / (double)ng;
@@ -1004,7 +1008,7 @@ void apply_abar_device(bse_system* s, const double* f_dev, int n_vec, double* af
   HIPC(launch_poisson<double>(s->n, a, st));
   // Hartree term
   HIPC(launch_mixed_density(phv, f_dev, n_o, n_vec, ng, s->mx_rho.as<double>(), st));
-  poisson64(s, s->mx_rho.as<double>(), n_vec, s->mx_dv.as<double>(), nullptr, 0.0);
+  poisson64(s, s->mx_rho.as<double>(), n_vec, s->mx_dv.as<double>(), nullptr, 0.0, nullptr, &s->mx_work);
   HIPC(launch_mixed_combine(f_dev, s->mx_tf.as<double>(), s->vdev.as<double>(), s->mx_eps.as<double>(),
                             s->cfg.scissors, s->mx_dv.as<double>(), phv, s->wij.as<double>(), n_o, n_vec, ng,
                             af_dev, st));
