@@ -1039,6 +1039,21 @@ void apply_a_mixed(bse_system* s, int n_vec, const double* f, double* af) {
   HIPC(hipStreamSynchronize(s->stream));
 }
 
+// Scratch of one call, kept for the next one while it is small: beyond
+// KEEP_BYTES in all it is given back when the call ends, also by an error
+// (64^3: up to 13 valence orbitals are kept; five allocations are well under a
+// millisecond of a recursion on more)
+constexpr size_t KEEP_BYTES = (size_t)512 << 20;
+struct CallScratch {
+  std::vector<DBuf*> bufs;
+  ~CallScratch() {
+    size_t held = 0;
+    for (const DBuf* b : bufs) held += b->bytes;
+    if (held > KEEP_BYTES)
+      for (DBuf* b : bufs) b->release();
+  }
+};
+
 // The paper's spectrum algorithm (Eqs. 6-8): the Chebyshev recursion with A
 // applied matrix-free in the mixed representation, from the dipole states
 // f0_j = Q (r_axis - centre) phi_j of each axis; residues by the doubling
@@ -1058,6 +1073,7 @@ void chebyshev_mixed(bse_system* s, int n_mom, double e_min, double e_max, int n
   const double b = 0.5 * (e_max + e_min), a = 0.5 * (e_max - e_min) * 1.01;
   const int K = n_mom / 2, M = 2 * n_mom, nf = 3 * n_o;
   DBuf &fv = s->mx_v, &af = s->mx_out, &pq = s->mx_pp;
+  const CallScratch scratch{{&s->mx_v, &s->mx_out, &s->mx_pp, &s->mx_tf, &s->mx_work}};
   DBuf Sk, mu, D, wd, sd;
   fv.alloc(sizeof(double) * 9 * len);               // [3 rotating][pol][n_o][ng]
   af.alloc(sizeof(double) * 3 * len);
@@ -1225,6 +1241,7 @@ void chebyshev_spectrum(bse_system* s, int n_mom, double e_min, double e_max, in
   if (n_mom < 2 || n_mom % 2 != 0 || n_w < 0 || (n_w > 0 && (!w_grid || !sigma || !(sig > 0))) ||
       (n_w == 0 && !residues))
     fail(BSE_ERR_ARG, "bse_chebyshev_spectrum: bad arguments");
+  const CallScratch scratch{{&s->ch_ws}};
   cheb_spectrum(s, n, n_mom, e_min, e_max, n_w, w_grid, sig, sigma, residues, bounds, "bse_chebyshev_spectrum",
                 [&](bool res) {
                   s->ch_ws.alloc(sizeof(double) * cheb_carve(nullptr, n, n_mom, n_w, res, nullptr));
@@ -1267,6 +1284,7 @@ void exciton_states(bse_system* s, int n_mom, double e_min, double e_max, int n_
   hipStream_t st = s->stream;
   const double* A = s->A_d.as<double>();
   const size_t ng = s->ng;
+  const CallScratch scratch{{&s->ch_ws, &s->ch_dens}};
   bool res = n <= cheb_res_max() && n_mom > 16;
   for (;; res = false) {
     const size_t nf = round32((res ? 3 : 9) * (size_t)n), ngm = round32((size_t)n_w * n_mom);
