@@ -180,7 +180,7 @@ struct bse_system {
   DBuf xi_d;
   DBuf eta0;      // [L][ng] FP64
   DBuf h0;        // [L][ng] complex T: unperturbed set at t = 0 (mid-step form)
-  DBuf hbuf;      // [2][L][ng] complex T: unperturbed set, current and next step
+  DBuf hbuf;      // [2, 3 where it may run ahead][L][ng] complex T: unperturbed set, current and next steps
   DBuf n0;        // [L]
   bool ready = false;
   // batch workspace
@@ -595,11 +595,13 @@ void prop_after_passes(PropRun<T>& r, int n) {
   r.hcur = hnext;
 }
 
+// whether small batches take the unperturbed set along one step ahead (not the
+// 112^3 plane pass), which a third buffer of it is for
+bool prop_may_run_ahead(const bse_system* s) { return s->n <= 64; }
 template <typename T>
 PropRun<T> prop_run(bse_system* s, int B, const int* pq_dev, int busy, int fused_kind) {
   PropRun<T> r{s, B, pq_dev, nullptr, true, prop_yz_parts<T>(s->n, B, s->L, fused_kind, busy), busy, false};
-  // small batches, where the orbitals run apart (not the 112^3 plane pass)
-  r.ahead = r.parts > 1 && s->n <= 64;
+  r.ahead = r.parts > 1 && prop_may_run_ahead(s);
   return r;
 }
 template <typename T>
@@ -621,7 +623,7 @@ void prepare_unperturbed(bse_system* s) {
   const int L = s->L;
   const size_t hstride = (size_t)L * ng;
   s->h0.alloc(sizeof(C) * hstride);
-  s->hbuf.alloc(sizeof(C) * hstride * 3);
+  s->hbuf.alloc(sizeof(C) * hstride * (prop_may_run_ahead(s) ? 3 : 2));
   s->eta0.alloc(sizeof(double) * hstride);
   s->n0.alloc(sizeof(double) * L);
   if (!s->deterministic) {

@@ -34,3 +34,22 @@ def test_large_recursion_scratch_is_given_back():
     assert held < 128 << 20
     assert np.array_equal(r1, r2)
     s.close()
+
+
+def test_no_third_unperturbed_buffer_where_it_is_not_used():
+    """set_orbitals at 112^3 holds, for each stochastic orbital and point, its
+    t = 0 forms (8 + 8 bytes) and two steps of the unperturbed set (8 each in
+    mixed precision); the third step's buffer is for grids up to 64^3."""
+    from paper_2205_06690_amd import bse
+    n, h, n_occ = 112, 0.5, 2
+    phi = np.random.default_rng(5).standard_normal((n_occ, n ** 3)) / (n * h) ** 1.5
+    used = {}
+    for L in (4, 24):
+        s = bse.System(n, h, np.zeros(n ** 3), n_occ=n_occ, n_stoch=L, n_steps=1, precision=bse.BSE_MIXED, max_batch=1)
+        before = _free()
+        s.set_orbitals(phi, np.zeros(n_occ))
+        used[L] = before - _free()
+        s.close()
+    per = (used[24] - used[4]) / 20 / n ** 3
+    say(f"112^3 mixed: {per:.1f} bytes a point and stochastic orbital")
+    assert per < 36
