@@ -1359,10 +1359,9 @@ void exciton_states_mixed(bse_system* s, int n_mom, double e_min, double e_max, 
   hipStream_t st = s->stream;
   const size_t ng = s->ng, len = (size_t)n_o * ng;
   const double b = 0.5 * (e_max + e_min), a = 0.5 * (e_max - e_min) * 1.01;
-  DBuf fv, af, part, g, F, wd, cq, pq, amp, rho, cs;
+  DBuf fv, af, g, F, wd, cq, pq, amp, rho, cs;
   fv.alloc(sizeof(double) * 3 * len);               // [3 rotating vectors][n_o][ng]
   af.alloc(sizeof(double) * len);
-  part.alloc(sizeof(double) * (project_part_elems(n_o, ng) + 6));
   g.alloc(sizeof(double) * (size_t)n_w * n_mom);
   F.alloc(sizeof(double) * (size_t)n_w * len);
   wd.alloc(sizeof(double) * n_w);
@@ -1387,8 +1386,7 @@ void exciton_states_mixed(bse_system* s, int n_mom, double e_min, double e_max, 
     for (int m = 0; m + 1 < n_mom; ++m) {
       apply_abar_device(s, vec(m), 1, af.as<double>());
       HIPC(launch_project_cheb(af.as<double>(), n_o, 1, s->phi64.as<double>(), S, s->mx_c.as<double>(), ng, vec(m),
-                               vec(m + 2), vec(m + 1), a, b, m == 0 ? 1 : 0, s->dv, part.as<double>() + 6,
-                               part.as<double>(), st));
+                               vec(m + 2), vec(m + 1), a, b, m == 0 ? 1 : 0, s->dv, nullptr, nullptr, st));
       HIPC(launch_states_acc(F.as<double>(), vec(m + 1), g.as<double>(), n_mom, m + 1, n_w, len, 0, st));
     }
     for (int q = 0; q < n_w; ++q) {

@@ -20,7 +20,8 @@ hipError_t launch_project_out(double* out, int nf, const double* phi, int S, con
 // The same on af without storing it, then the Chebyshev step of n_pol sets of
 // n_o fields: fn = 2 (x - b fc)/a - fp (first: (x - b fc)/a) with x = af - sum_s
 // C phi_s, and S[p] = dv <fc|fc>, S[3 + p] = dv <fn|fc> of set p (n_pol <= 3;
-// entries of absent sets are 0).  part holds project_part_elems(n_pol n_o, ng).
+// entries of absent sets are 0).  part holds project_part_elems(n_pol n_o, ng);
+// part and S both null: the step without the sums.
 size_t project_part_elems(int nf, size_t ng);
 hipError_t launch_project_cheb(const double* af, int n_o, int n_pol, const double* phi, int S, const double* C,
                                size_t ng, const double* fc, const double* fp, double* fn, double a, double b,

@@ -17,8 +17,10 @@ typedef double g4v __attribute__((ext_vector_type(4)));
 // row's loads take whole 128-byte lines; with eight values, half a line at a
 // time, 124 us).  Bound by reading the operands: 30 fields on 120 orbitals at
 // 64^3, 315 MB in 99 us, against 3 x 77 us for one set of 10 at a time on
-// vector FMA and LDS tiles.
-constexpr int GM_MT = 2, GM_NT = 4;
+// vector FMA and LDS tiles.  MT and NT are what M and N fill: a product of a
+// padded tile takes as long as any other (1 field on 5 orbitals at 16^3: 8.0 us
+// with MT 2 and NT 4, 3.2; 6 on 30 at 48^3: 14 and 8).
+template <int GM_MT, int GM_NT>
 __global__ void __launch_bounds__(256, 2) k_gemm_f64(const double* __restrict__ A, int M, const double* __restrict__ B,
                                                      int N, size_t K, size_t chunk, int nmt, int nnt, unsigned nwave,
                                                      double* __restrict__ part) {
@@ -39,28 +41,38 @@ __global__ void __launch_bounds__(256, 2) k_gemm_f64(const double* __restrict__ 
   for (int i = 0; i < GM_MT; ++i)
 #pragma unroll
     for (int j = 0; j < GM_NT; ++j) acc[i][j] = g4v{0.0, 0.0, 0.0, 0.0};
-  g4v na[GM_MT], nb[GM_NT];
-  auto load = [&](size_t r) {
+  // stages in flight: with one row tile the registers hold two (8 fields on 120
+  // orbitals at 64^3: 83 -> 77 us; four no more, nor 1024 or 4096 waves)
+  constexpr int PF = GM_MT == 1 ? 2 : 1;
+  g4v na[PF][GM_MT], nb[PF][GM_NT];
+  auto load = [&](int q, size_t r) {
 #pragma unroll
-    for (int i = 0; i < GM_MT; ++i) na[i] = *reinterpret_cast<const g4v*>(pa[i] + r);
+    for (int i = 0; i < GM_MT; ++i) na[q][i] = *reinterpret_cast<const g4v*>(pa[i] + r);
 #pragma unroll
-    for (int j = 0; j < GM_NT; ++j) nb[j] = *reinterpret_cast<const g4v*>(pb[j] + r);
+    for (int j = 0; j < GM_NT; ++j) nb[q][j] = *reinterpret_cast<const g4v*>(pb[j] + r);
   };
-  if (k0 < k1) load(k0);
-  for (size_t r = k0; r < k1; r += 16) {
-    g4v a[GM_MT], b[GM_NT];
 #pragma unroll
-    for (int i = 0; i < GM_MT; ++i) a[i] = na[i];
+  for (int q = 0; q < PF; ++q)
+    if (k0 + 16 * q < k1) load(q, k0 + 16 * q);
+  for (size_t rb = k0; rb < k1; rb += 16 * PF) {
 #pragma unroll
-    for (int j = 0; j < GM_NT; ++j) b[j] = nb[j];
-    if (r + 16 < k1) load(r + 16);
+    for (int q = 0; q < PF; ++q) {
+      const size_t r = rb + 16 * q;
+      if (r >= k1) break;
+      g4v a[GM_MT], b[GM_NT];
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+      for (int i = 0; i < GM_MT; ++i) a[i] = na[q][i];
 #pragma unroll
-      for (int i = 0; i < GM_MT; ++i)
+      for (int j = 0; j < GM_NT; ++j) b[j] = nb[q][j];
+      if (r + 16 * PF < k1) load(q, r + 16 * PF);
 #pragma unroll
-        for (int j = 0; j < GM_NT; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][t], b[j][t], acc[i][j], 0, 0, 0);
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < GM_MT; ++i)
+#pragma unroll
+          for (int j = 0; j < GM_NT; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][t], b[j][t], acc[i][j], 0, 0, 0);
+    }
   }
   double* out = part + (size_t)kc * M * N;
 #pragma unroll
@@ -74,37 +86,42 @@ __global__ void __launch_bounds__(256, 2) k_gemm_f64(const double* __restrict__ 
       }
 }
 
-// C[i] = scale sum_k part[k][i]: a block sums 32 outputs in eight slices of
-// the chunks and adds the slices in order
-constexpr int GR_SL = 8;
+// C[i] = scale sum_k part[k][i]: a block sums 256 / SL outputs in SL slices of
+// the chunks and adds the slices in order.  32 slices where eight would leave
+// most of the chip idle (180 outputs of 1728 chunks: 19.5 -> 7 us).
+template <int SL>
 __global__ void __launch_bounds__(256) k_gemm_reduce(const double* __restrict__ part, int nchunk, size_t MN,
                                                      double scale, double* __restrict__ C) {
-  __shared__ double red[GR_SL][32];
-  const int o = threadIdx.x & 31, j = threadIdx.x >> 5;
-  const size_t i = (size_t)blockIdx.x * 32 + o;
+  constexpr int W = 256 / SL;
+  __shared__ double red[SL][W];
+  const int o = threadIdx.x % W, j = threadIdx.x / W;
+  const size_t i = (size_t)blockIdx.x * W + o;
   double s = 0;
   if (i < MN)
 #pragma unroll 4
-    for (int k = j; k < nchunk; k += GR_SL) s += part[(size_t)k * MN + i];
+    for (int k = j; k < nchunk; k += SL) s += part[(size_t)k * MN + i];
   red[j][o] = s;
   __syncthreads();
   if (j == 0 && i < MN) {
     double t = 0;
 #pragma unroll
-    for (int q = 0; q < GR_SL; ++q) t += red[q][o];
+    for (int q = 0; q < SL; ++q) t += red[q][o];
     C[i] = t * scale;
   }
 }
 
 // chunks for about 2048 waves (two per SIMD), each at least 64 points
 struct GemmPlan {
-  int nmt, nnt, nchunk;
+  int mt, nt, nmt, nnt, nchunk;
   size_t chunk;
 };
 static GemmPlan gemm_plan(int M, int N, size_t K) {
   GemmPlan p;
-  p.nmt = (M + 16 * GM_MT - 1) / (16 * GM_MT);
-  p.nnt = (N + 16 * GM_NT - 1) / (16 * GM_NT);
+  const int tn = (N + 15) / 16, gn = (tn + 3) / 4;
+  p.mt = M <= 16 ? 1 : 2;
+  p.nt = (tn + gn - 1) / gn;
+  p.nmt = (M + 16 * p.mt - 1) / (16 * p.mt);
+  p.nnt = (tn + p.nt - 1) / p.nt;
   const size_t tiles = (size_t)p.nmt * p.nnt, want = std::max<size_t>(1, (2048 + tiles - 1) / tiles);
   p.chunk = std::max<size_t>(64, ((K + want - 1) / want + 15) / 16 * 16);
   p.nchunk = (int)((K + p.chunk - 1) / p.chunk);
@@ -112,15 +129,25 @@ static GemmPlan gemm_plan(int M, int N, size_t K) {
 }
 size_t gemm_part_elems(int M, int N, size_t K) { return (size_t)gemm_plan(M, N, K).nchunk * M * N; }
 
+template <int MT>
+static void gemm_go(const GemmPlan& p, const double* A, int M, const double* B, int N, size_t K, double* part,
+                    hipStream_t st) {
+  const unsigned nwave = (unsigned)p.nmt * p.nnt * p.nchunk;
+  auto k = p.nt == 1 ? k_gemm_f64<MT, 1> : p.nt == 2 ? k_gemm_f64<MT, 2> : p.nt == 3 ? k_gemm_f64<MT, 3>
+                                                                                  : k_gemm_f64<MT, 4>;
+  hipLaunchKernelGGL(k, dim3((nwave + 3) / 4), dim3(256), 0, st, A, M, B, N, K, p.chunk, p.nmt, p.nnt, nwave, part);
+}
 hipError_t launch_gemm_f64(const double* A, int M, const double* B, int N, size_t K, double scale,
                            double* part, double* C, hipStream_t st) {
   if (M < 1 || N < 1 || K % 16) return hipErrorInvalidValue;
   const GemmPlan p = gemm_plan(M, N, K);
-  const unsigned nwave = (unsigned)p.nmt * p.nnt * p.nchunk;
-  hipLaunchKernelGGL(k_gemm_f64, dim3((nwave + 3) / 4), dim3(256), 0, st, A, M, B, N, K, p.chunk, p.nmt, p.nnt, nwave,
-                     part);
+  if (p.mt == 1) gemm_go<1>(p, A, M, B, N, K, part, st);
+  else gemm_go<2>(p, A, M, B, N, K, part, st);
   const size_t MN = (size_t)M * N;
-  hipLaunchKernelGGL(k_gemm_reduce, dim3((unsigned)((MN + 31) / 32)), dim3(256), 0, st, part, p.nchunk, MN, scale, C);
+  if (MN < 32 * 256)
+    hipLaunchKernelGGL(k_gemm_reduce<32>, dim3((unsigned)((MN + 7) / 8)), dim3(256), 0, st, part, p.nchunk, MN, scale, C);
+  else
+    hipLaunchKernelGGL(k_gemm_reduce<8>, dim3((unsigned)((MN + 31) / 32)), dim3(256), 0, st, part, p.nchunk, MN, scale, C);
   return hipGetLastError();
 }
 
@@ -135,7 +162,7 @@ struct ChebStep {
   double* fn;
   double ia, b, dv;
   int first, n_o;
-  double* part;          // [blocks][6]
+  double* part;          // [blocks][6], nullable: no sums
 };
 constexpr int PJ_PT = 4;
 template <int MF, bool CHEB>
@@ -204,7 +231,7 @@ __global__ void __launch_bounds__(256, 2) k_project_f64(double* __restrict__ out
             s1 += nx * cur;
           }
         }
-      if (CHEB) {
+      if (CHEB && ch.part) {
         for (int o = 8; o > 0; o >>= 1) {
           s0 += __shfl_xor(s0, o, 16);
           s1 += __shfl_xor(s1, o, 16);
@@ -215,7 +242,7 @@ __global__ void __launch_bounds__(256, 2) k_project_f64(double* __restrict__ out
         }
       }
     }
-  if (CHEB) {
+  if (CHEB && ch.part) {
     // six sums of the block: its fields of each set, waves in order
     __syncthreads();
     if (threadIdx.x < 6) {
@@ -271,12 +298,12 @@ size_t project_part_elems(int nf, size_t ng) {
 hipError_t launch_project_cheb(const double* af, int n_o, int n_pol, const double* phi, int S, const double* C,
                                size_t ng, const double* fc, const double* fp, double* fn, double a, double b,
                                int first, double dv, double* part, double* Sk, hipStream_t st) {
-  if (n_o < 1 || n_pol < 1 || n_pol > 3 || S < 1) return hipErrorInvalidValue;
+  if (n_o < 1 || n_pol < 1 || n_pol > 3 || S < 1 || !part != !Sk) return hipErrorInvalidValue;
   const int nf = n_o * n_pol;
   const ChebStep ch{fc, fp, fn, 1.0 / a, b, dv, first, n_o, part};
   // (CHEB reads af only)
   const hipError_t e = project_go<true>(const_cast<double*>(af), nf, phi, S, C, ng, ch, st);
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || !part) return e;
   hipLaunchKernelGGL(k_project_sums, dim3(1), dim3(384), 0, st, part, (int)(project_part_elems(nf, ng) / 6), Sk);
   return hipGetLastError();
 }
