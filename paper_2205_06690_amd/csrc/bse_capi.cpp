@@ -1043,9 +1043,9 @@ void apply_a_mixed(bse_system* s, int n_vec, const double* f, double* af) {
 
 // Scratch of one call, kept for the next one while it is small: beyond
 // KEEP_BYTES in all it is given back when the call ends, also by an error
-// (64^3: up to 13 valence orbitals are kept; five allocations are well under a
-// millisecond of a recursion on more)
-constexpr size_t KEEP_BYTES = (size_t)512 << 20;
+// (at 64^3 what 28 valence orbitals take is kept; five allocations and releases
+// of 0.75 GB together add 1.7 ms to a call)
+constexpr size_t KEEP_BYTES = (size_t)1 << 30;
 struct CallScratch {
   std::vector<DBuf*> bufs;
   ~CallScratch() {
