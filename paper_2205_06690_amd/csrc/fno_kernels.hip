@@ -482,7 +482,7 @@ __global__ void __launch_bounds__(256) k_pointwise(const float* __restrict__ in,
 // takes one y at a time with the next one's loads in flight.  KQ > 0: m <= 8,
 // the z phases in registers.  Bound by the fields read and written and by
 // erff: at 64^3, 32 channels, batch 8 (all three fields) 0.20 ms for 805 MB,
-// batch 3 without zout 69 us for 201 MB, against 281 (inverse planes) + 50
+// batch 3 without zout 64 us for 201 MB, against 281 (inverse planes) + 50
 // (scatter) + 71 (clearing the work array) + 259 us (pointwise) at batch 8,
 // and in the backward pass 179 (pointwise) + 224 us (gelu').
 template <int N, int T, int KQ>
@@ -535,12 +535,29 @@ __global__ void __launch_bounds__(256, T <= 2 ? 2 : 1)
       const int j2 = j20 + jj;
       float2 v[N1];
 #pragma unroll
-      for (int k1 = 0; k1 < N1; ++k1) {
-        float2 acc = make_float2(0.f, 0.f);
-        for (int k = k1; k < m; k += N1) acc = cadd(acc, cmulc(src[(k + m) * m], twl[(j2 * k) % N]));
-        for (int k = N - N1 + k1; k >= N - m; k -= N1)
-          acc = cadd(acc, cmulc(src[(k - N + m) * m], twl[(j2 * k) % N]));
-        v[k1] = acc;
+      for (int k1 = 0; k1 < N1; ++k1) v[k1] = make_float2(0.f, 0.f);
+      // loads past the kept frequencies go to the last one and count as zero, so
+      // that those of several rounds are in flight together (32^3, 16 modes, 32
+      // channels, batch 4: 58 -> 35 us; 64^3, 32 modes, batch 1: 114 -> 67)
+#pragma unroll 4
+      for (int kb = 0; kb < m; kb += N1) {
+#pragma unroll
+        for (int k1 = 0; k1 < N1; ++k1) {
+          const int k = kb + k1;
+          float2 p = src[(min(k, m - 1) + m) * m];
+          if (k >= m) p = make_float2(0.f, 0.f);
+          v[k1] = cadd(v[k1], cmulc(p, twl[(j2 * k) % N]));
+        }
+      }
+#pragma unroll 4
+      for (int kb = N1; kb < m + N1; kb += N1) {
+#pragma unroll
+        for (int k1 = 0; k1 < N1; ++k1) {
+          const int k = N - kb + k1;
+          float2 p = src[(max(k, N - m) - N + m) * m];
+          if (k < N - m) p = make_float2(0.f, 0.f);
+          v[k1] = cadd(v[k1], cmulc(p, twl[(j2 * k) % N]));
+        }
       }
       Dft<N1, +1, float2>::run(v);
 #pragma unroll

@@ -289,3 +289,9 @@ def test_gradient_to_host_in_chunks(W, L):
     # the step is a difference of FP32 weights below 1: eps 6e-8 / lr
     say(f"chunks W {W} L {L}: {g0.nbytes / 2 ** 20:.2f} MB, max|d step| {np.abs(step - want).max():.1e}")
     assert np.abs(step - want).max() < 1e-3
+
+
+@pytest.mark.parametrize("n,W,m,L,B", [(16, 9, 7, 2, 2), (32, 6, 13, 2, 2), (32, 16, 15, 1, 1), (64, 4, 29, 1, 1)])
+def test_mode_counts_between_the_residues(n, W, m, L, B):
+    """The same at mode counts that are no multiple of the transforms' factor."""
+    test_truncated_transforms_and_layers(n, W, m, L, B)
