@@ -141,10 +141,13 @@ bse_status bse_apply_W_device(bse_system* sys, int32_t n_pairs, const int32_t* p
  * there are not changed).  target BSE_FAULT_UNPERTURBED: writes value into
  * the real part of the t = 0 unperturbed stochastic orbital `index` (< L)
  * at `point` (a finite value that changes its norm trips the norm check of
- * the cleaning steps).  The next set_orbitals restores both.  Errors:
+ * the cleaning steps).  The next set_orbitals restores both.  target
+ * BSE_FAULT_RESIDENT: the next `index` Chebyshev recursions that run with A
+ * on the chip end as if their workgroups had never been resident together
+ * (point and value unused); the calls go on with a launch per step.  Errors:
  * BSE_ERR_STATE before bse_set_orbitals; BSE_ERR_ARG for a bad target or an
  * index out of range. */
-enum { BSE_FAULT_ORBITAL = 0, BSE_FAULT_UNPERTURBED = 1 };
+enum { BSE_FAULT_ORBITAL = 0, BSE_FAULT_UNPERTURBED = 1, BSE_FAULT_RESIDENT = 2 };
 bse_status bse_inject_fault(bse_system* sys, int32_t target, int32_t index, int64_t point, double value);
 
 /* Tamm-Dancoff matrix (Eq. 1) for the highest n_o occupied and lowest n_c

@@ -305,6 +305,11 @@ class System:
         the input checks (tests of the failure path)."""
         _check(LIB.bse_inject_fault(self._h, 1 if unperturbed else 0, int(index), int(point), float(value)))
 
+    def inject_resident_miss(self, count: int):
+        """bse_inject_fault, BSE_FAULT_RESIDENT: the next ``count`` Chebyshev
+        recursions with A on the chip end as if their workgroups never met."""
+        _check(LIB.bse_inject_fault(self._h, 2, int(count), 0, 0.0))
+
     def build_a(self, n_o: int, n_c: int) -> np.ndarray:
         A = np.empty((n_o * n_c, n_o * n_c))
         _check(LIB.bse_build_A(self._h, n_o, n_c, _dptr(A)))

@@ -206,6 +206,7 @@ struct bse_system {
   // surrogate descriptors and buffers
   DBuf n0dens, vdev, fx, fy, fscale, fdots, fwpol;
   DBuf ch_ws, ch_dens;   // Chebyshev spectrum and exciton states
+  int cheb_missed = 0;   // resident recursions yet to fail (bse_inject_fault)
   DBuf mx_v, mx_pp;      // recursion vectors and partials of the mixed spectrum
   // matrix-free A f; transforms of its own (mx_work): the batch workspace is
   // sized by batches alone, so that these calls never move it under a plan
@@ -1137,11 +1138,14 @@ void cheb_res_run(bse_system* s, int n, const double* fv, double* seg, int* err,
                   const std::function<void(const double*, const double*, int, int)>& use) {
   const size_t half = cheb_seg_doubles(n, total) / 2;
   HIPC(launch_fill_zero(err, sizeof(int), s->stream));
+  const bool missed = s->cheb_missed > 0;   // bse_inject_fault
+  if (missed) --s->cheb_missed;
   const double *fc = fv, *fp = nullptr;
   for (int k0 = 0, w = 0; k0 < total; w ^= 1) {
     const int steps = std::min(CHEB_SEG, total - k0);
     double* out = seg + w * half;
-    HIPC(launch_cheb_res(s->A_d.as<double>(), n, fc, fp, out, steps, k0, a, b, err, s->stream));
+    if (missed) HIPC(launch_cheb_missed(n, out, steps, err, s->stream));
+    else HIPC(launch_cheb_res(s->A_d.as<double>(), n, fc, fp, out, steps, k0, a, b, err, s->stream));
     use(fc, out, k0, steps);
     fp = steps > 1 ? out + (size_t)(steps - 2) * 3 * n : fc;
     fc = out + (size_t)(steps - 1) * 3 * n;
@@ -2251,6 +2255,11 @@ bse_status bse_apply_W_device(bse_system* s, int32_t n_pairs, const int32_t* pq_
 bse_status bse_inject_fault(bse_system* s, int32_t target, int32_t index, int64_t point, double value) {
   API_BEGIN
   check_ready(s);
+  if (target == BSE_FAULT_RESIDENT) {
+    if (index < 0) fail(BSE_ERR_ARG, "bse_inject_fault: negative count");
+    s->cheb_missed = index;
+    return BSE_OK;
+  }
   if (target != BSE_FAULT_ORBITAL && target != BSE_FAULT_UNPERTURBED) fail(BSE_ERR_ARG, "bse_inject_fault: bad target");
   const int count = target == BSE_FAULT_ORBITAL ? s->n_orb : s->L;
   if (index < 0 || index >= count || point < 0 || (size_t)point >= s->ng)

@@ -18,6 +18,10 @@ constexpr int CHEB_SEG = 512;
 hipError_t launch_cheb_res(const double* A, int n, const double* fc, const double* fp, double* out, int steps, int k0,
                            double a, double b, int* err, hipStream_t st);
 
+// what a segment leaves whose workgroups never met (rows still empty, err
+// raised), for tests of the path behind it
+hipError_t launch_cheb_missed(int n, double* out, int steps, int* err, hipStream_t st);
+
 // S[m][0..2] = <f^m|f^m>, S[m][3..5] = <f^{m+1}|f^m> for m = k0 .. k0 + steps - 1
 // (fc = f^{k0}, out as above)
 hipError_t launch_cheb_dots(const double* fc, const double* out, int n, int k0, int steps, double* S, hipStream_t st);

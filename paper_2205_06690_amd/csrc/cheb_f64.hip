@@ -396,6 +396,15 @@ hipError_t launch_cheb_res(const double* A, int n, const double* fc, const doubl
   return cheb_res_go<2, 64, true>(A, n, fc, fp, out, steps, first, a, b, err, st);
 }
 
+__global__ void k_cheb_missed(int* err) { *err = 1; }
+hipError_t launch_cheb_missed(int n, double* out, int steps, int* err, hipStream_t st) {
+  const size_t tot = (size_t)steps * 3 * n;
+  hipLaunchKernelGGL(k_cheb_empty, dim3((unsigned)std::min<size_t>((tot + 255) / 256, 4096)), dim3(256), 0, st,
+                     reinterpret_cast<unsigned long long*>(out), tot);
+  hipLaunchKernelGGL(k_cheb_missed, dim3(1), dim3(1), 0, st, err);
+  return hipGetLastError();
+}
+
 template <int NJ>
 static hipError_t lanczos_res_go(const double* A, int n, double* V, int k0, int k1, double* alpha, double* bq,
                                  hipStream_t st) {

@@ -83,3 +83,41 @@ def test_resident_lanczos(n_o, n_c):
     assert e < 1e-9 and ea < 1e-9
     assert ed < max(1e-8, 4e-10 / gap)
     s.close()
+
+
+@pytest.mark.parametrize("n_o,n_c", [(5, 13), (3, 43), (19, 27)])
+def test_recursion_whose_workgroups_never_met(n_o, n_c):
+    """Below and above 256 rows, a resident recursion that gives up (forced: rows
+    empty, its flag raised) ends in the launch per step: the residues and the
+    interval of both entry points equal bit for bit those of a short call, which
+    always runs so (the residues of fewer moments are a prefix), the states
+    agree with the oracle, and the next call is resident again."""
+    from oracle import bse as obse
+    s, A, f0, phi = _system(n_o, n_c, 5 * n_o + n_c)
+    n, n_mom = n_o * n_c, 64
+    lo, hi = obse.spectral_bounds(A)
+    a, b = obse.chebyshev_scale(lo, hi)
+    wg = np.linspace(lo, hi, 9)[1:-1]
+    sig = 4.0 * (hi - lo) / n_mom
+    _, short, bo_s = s.chebyshev_spectrum(30, None)          # 15 steps: one launch each
+    sg_r, res_r, bo_r = s.chebyshev_spectrum(n_mom, wg, sig)
+    F_r, dn_r, _ = s.exciton_states(n_mom, wg[:3], sig, bounds=(lo, hi))
+    s.inject_resident_miss(2)
+    got = [s.chebyshev_spectrum(n_mom, wg, sig), s.chebyshev_spectrum_noalloc(n_mom, wg, sig)]
+    for sg, res, bo in got:
+        assert np.array_equal(res[:, :30], short) and np.array_equal(bo, bo_s)
+        assert np.array_equal(sg, got[0][0]) and np.array_equal(res, got[0][1])
+    e = np.abs(got[0][1] - res_r).max() / np.abs(res_r[:, 0]).max()
+    es = np.abs(got[0][0] - sg_r).max() / np.abs(sg_r).max()
+    s.inject_resident_miss(1)
+    F, dn, _ = s.exciton_states(n_mom, wg[:3], sig, bounds=(lo, hi))
+    F_o = obse.chebyshev_states(A, f0, n_mom, a, b, wg[:3], sig).transpose(0, 2, 1)
+    eF = np.abs(F - F_o).max() / np.abs(F_o).max()
+    ed = np.abs(dn - dn_r).max() / np.abs(dn_r).max()
+    say(f"n = {n}: against the resident recursion residues {e:.1e}, sigma {es:.1e}, densities {ed:.1e}; states {eF:.1e}")
+    assert max(e, es, eF, ed) < TOL
+    sg2, res2, bo2 = s.chebyshev_spectrum(n_mom, wg, sig)
+    assert np.array_equal(sg2, sg_r) and np.array_equal(res2, res_r) and np.array_equal(bo2, bo_r)
+    F2, dn2, _ = s.exciton_states(n_mom, wg[:3], sig, bounds=(lo, hi))
+    assert np.array_equal(F2, F_r) and np.array_equal(dn2, dn_r)
+    s.close()
