@@ -78,7 +78,7 @@ __global__ void __launch_bounds__(CR_T) k_cheb_res(const double* __restrict__ A,
   extern __shared__ double cr_lds[];
   double* f = cr_lds;                       // [2][16 NJ], zero past n
   double* al = cr_lds + 2 * 16 * NJ;        // [EL][CR_T]
-  __shared__ int stop;
+  __shared__ int stop[2];                   // by step parity: a wave may still read the last step's
   const int tid = threadIdx.x, c16 = tid & 15, g = tid >> 4;
   const int p = blockIdx.x / nwg, r0 = (blockIdx.x % nwg) * 32 * NI;
   double ar[ER];
@@ -93,7 +93,7 @@ __global__ void __launch_bounds__(CR_T) k_cheb_res(const double* __restrict__ A,
     f[c] = c < n ? fc[(size_t)p * n + c] : 0.0;
     f[16 * NJ + c] = 0.0;
   }
-  if (tid == 0) stop = 0;
+  if (tid < 2) stop[tid] = 0;
   // the row this lane owns after the reduction: bits 3, 2, .. of c16 pick it
   int own = 0;
 #pragma unroll
@@ -142,7 +142,7 @@ __global__ void __launch_bounds__(CR_T) k_cheb_res(const double* __restrict__ A,
           ++tries;
           if (tries == CHEB_SPIN) __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           if ((tries & 1023u) == 0 && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-            stop = 1;
+            stop[k & 1] = 1;
             break;
           }
         }
@@ -150,7 +150,7 @@ __global__ void __launch_bounds__(CR_T) k_cheb_res(const double* __restrict__ A,
       }
     }
     __syncthreads();
-    if (MULTI && stop) return;
+    if (MULTI && stop[k & 1]) return;
   }
 }
 
