@@ -1509,12 +1509,16 @@ struct Launch {
   }
   // A pair's orbitals go to several workgroups while those are fewer than the
   // chip runs at once (FP32, 10 orbitals, unsplit -> split: 16^3 2 pairs 7.7 ->
-  // 3.6 us, 32^3 8 pairs 21.7 -> 10.9, 64^3 1 pair 33 -> 13, 8 pairs 64 -> 56).
-  // In FP64 and at 112 points, where the state soon exceeds the last-level
-  // cache, only well below that (64^3 FP64 1 pair 38 -> 25, but 11 pairs 214 ->
-  // 244; 112^3 FP32 5 pairs 305 -> 326).
-  static int x_groups(int blocks, int L) {
-    return std::max(1, std::min(L, (std::is_same<T, float>::value && N <= 64 ? 4096 : 1024) / blocks));
+  // 3.6 us, 32^3 8 pairs 21.7 -> 10.9, 64^3 1 pair 33 -> 13, 8 pairs 64 -> 56),
+  // in FP64 only well below that (64^3 1 pair 58 -> 39, but 11 pairs 214 -> 244).
+  // Not at 112 points (1 pair, 5 orbitals 42 -> 48, FP64 102 -> 126), nor in FP32
+  // at 64 from 512 blocks on with a state beyond the last-level cache (4 pairs,
+  // 30 orbitals 124 -> 145; 120 orbitals 476 -> 631, but 2 pairs 716 -> 377).
+  static int x_groups(int blocks, int F, int L) {
+    constexpr bool FP32 = std::is_same<T, float>::value;
+    if (N > 64) return 1;
+    if (FP32 && N == 64 && blocks >= 512 && (double)N * N * N * L * (8.0 * F + 16.0) > 250e6) return 1;
+    return std::max(1, std::min(L, (FP32 ? 4096 : 1024) / blocks));
   }
   template <int TC>
   static hipError_t prop_x_tc(const PropXArgs<T>& a, int F, hipStream_t st, const LaunchEvents* ev) {
@@ -1523,7 +1527,7 @@ struct Launch {
     } else {
       PropXArgs<T> b = a;
       b.nf = F;
-      b.ls = a.mode == PX_ETA0 ? 1 : x_groups(F * (N * N / TC) + a.busy, a.L);
+      b.ls = a.mode == PX_ETA0 ? 1 : x_groups(F * (N * N / TC) + a.busy, F, a.L);
       const dim3 grid = field_tile_grid(a.order, F * b.ls + a.ne, N * N / TC);
       size_t sm = x_lds<N, TC, T>();
       if (a.mode == PX_ETA0)
