@@ -68,10 +68,11 @@ __global__ void k_phi_split(const float* __restrict__ phi, int S, int Sp, size_t
 }
 
 // part[kc][row][s] (row < 2F, s < S) = sum over chunk kc of D[row][r] phi_s(r),
-// D = d, finished on the fly when MID.  The column-tile-0 blocks also accumulate <E_l, d_f> over their chunk into gpart[f][kc] (E = Ph H_l
+// D = d, finished on the fly when MID.  With EDOT the column-tile-0 blocks
+// also accumulate <E_l, d_f> over their chunk into gpart[f][kc] (E = Ph H_l
 // computed in registers when MID, read from E otherwise).  Global loads of
 // stage k+1 are in flight during the matrix-core work of stage k.
-template <bool MID>
+template <bool MID, bool EDOT>
 __global__ void __launch_bounds__(256) k_coef_x3(const float2* __restrict__ d, int F, PhiSplit ps,
                                                  size_t ng, int chunk, int nrt, int nct, int nchunk,
                                                  unsigned ntile, MidArgs mid,
@@ -93,7 +94,7 @@ __global__ void __launch_bounds__(256) k_coef_x3(const float2* __restrict__ d, i
   const size_t k1 = min(ng, k0 + (size_t)chunk);
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wm = w >> 1, wn = w & 1;
-  const bool do_e = ct == 0;
+  const bool do_e = EDOT && ct == 0;
   // loader: fields f0 + qa + 16i at points pa, pa+1; state s0 + sb at points hb..hb+15
   const int qa = tid >> 4, pa = (tid & 15) * 2;
   const int sb = tid >> 1, hb = (tid & 1) * 16;
@@ -580,18 +581,20 @@ hipError_t launch_coef_x3(const float2* d, int F, const PhiSplit& ps, size_t ng,
   if (F <= 0 || ps.S <= 0 || ng % XK || chunk % XK || chunk <= 0) return hipErrorInvalidValue;
   if (mid.on && !gpart) return hipErrorInvalidValue;
   const int nchunk = (int)((ng + chunk - 1) / chunk);
-  if (gpart) {
+  // few fields: waves of 16 or 32 rows (one block of rows, or two where the
+  // states are few); more of them re-read phi for every 32 rows (120 states at
+  // 64^3: 120 orbitals 208 us against 104 of the tile; 100 states at 112^3: 16
+  // orbitals alike, 20 81 us slower a cleaning, 100 857 against 424; 30 states at
+  // 112^3: 32 orbitals 35 us faster, 64 56 slower)
+  const bool rows = !gpart && (F <= 16 || (F <= 32 && ps.S <= 48));
+  if (!rows) {
     const int nrt = (2 * F + XT - 1) / XT, nct = (ps.S + XT - 1) / XT;
     const unsigned ntile = (unsigned)nrt * nct * nchunk;
-    const dim3 g(round8(ntile)), b(256);
-    if (mid.on)
-      hipLaunchKernelGGL(k_coef_x3<true>, g, b, 0, st, d, F, ps, ng, chunk, nrt, nct, nchunk, ntile, mid, E, L, part,
-                         gpart);
-    else
-      hipLaunchKernelGGL(k_coef_x3<false>, g, b, 0, st, d, F, ps, ng, chunk, nrt, nct, nchunk, ntile, mid, E, L, part,
-                         gpart);
-    hipLaunchKernelGGL(k_edot_reduce, dim3((F + 3) / 4), dim3(256), 0, st, gpart, nchunk, F, ps.S, dv,
-                       coef);
+    auto k = mid.on ? k_coef_x3<true, true> : gpart ? k_coef_x3<false, true> : k_coef_x3<false, false>;
+    hipLaunchKernelGGL(k, dim3(round8(ntile)), dim3(256), 0, st, d, F, ps, ng, chunk, nrt, nct, nchunk, ntile, mid, E, L,
+                       part, gpart);
+    if (gpart)
+      hipLaunchKernelGGL(k_edot_reduce, dim3((F + 3) / 4), dim3(256), 0, st, gpart, nchunk, F, ps.S, dv, coef);
   } else {
     const int nct = (ps.S + 63) / 64;
     if (2 * F <= 16) {

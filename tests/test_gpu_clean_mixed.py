@@ -29,3 +29,11 @@ def test_mixed_cleaning_tile_edges(n_occ, n_stoch, n_pairs):
     e = rel(w, w_o.reshape(n_pairs, -1))
     print(f"n_occ {n_occ} L {n_stoch} pairs {n_pairs}: {e.max():.1e}", flush=True)
     assert e.max() < TOL
+
+
+@pytest.mark.parametrize("n_occ,n_stoch,n_pairs", [(64, 16, 1), (48, 17, 2), (49, 17, 2), (48, 32, 1), (49, 32, 1), (16, 33, 1),
+                                                   (130, 66, 1)])
+def test_unperturbed_coefficients_of_many_orbitals(n_occ, n_stoch, n_pairs):
+    """The same where the unperturbed set's coefficients change kernels (16 and 32
+    orbitals, 48 states)."""
+    test_mixed_cleaning_tile_edges(n_occ, n_stoch, n_pairs)
