@@ -87,8 +87,9 @@ __global__ void __launch_bounds__(256, 2) k_gemm_f64(const double* __restrict__ 
 }
 
 // C[i] = scale sum_k part[k][i]: a block sums 256 / SL outputs in SL slices of
-// the chunks and adds the slices in order.  32 slices where eight would leave
-// most of the chip idle (180 outputs of 1728 chunks: 19.5 -> 7 us).
+// the chunks and adds the slices in order.  32 slices below 1024 outputs, where
+// eight leave most of the chip idle (180 outputs of 1728 chunks: 19.5 -> 7 us;
+// 3600 of 1024: no difference to the call).
 template <int SL>
 __global__ void __launch_bounds__(256) k_gemm_reduce(const double* __restrict__ part, int nchunk, size_t MN,
                                                      double scale, double* __restrict__ C) {
@@ -144,7 +145,7 @@ hipError_t launch_gemm_f64(const double* A, int M, const double* B, int N, size_
   if (p.mt == 1) gemm_go<1>(p, A, M, B, N, K, part, st);
   else gemm_go<2>(p, A, M, B, N, K, part, st);
   const size_t MN = (size_t)M * N;
-  if (MN < 32 * 256)
+  if (MN < 1024)
     hipLaunchKernelGGL(k_gemm_reduce<32>, dim3((unsigned)((MN + 7) / 8)), dim3(256), 0, st, part, p.nchunk, MN, scale, C);
   else
     hipLaunchKernelGGL(k_gemm_reduce<8>, dim3((unsigned)((MN + 31) / 32)), dim3(256), 0, st, part, p.nchunk, MN, scale, C);
