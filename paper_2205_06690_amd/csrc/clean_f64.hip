@@ -249,7 +249,10 @@ __global__ void __launch_bounds__(256, 2) k_update_f64(double2* __restrict__ d, 
 // The split of the coefficient GEMM: column tiles of up to 64 states, evenly
 // filled, and chunks of points for about 2048 waves (two per SIMD: the
 // registers' limit), each at least 64 points; more chunks only add partial
-// sums (64^3, 120 fields, 120 states: 54 MB of them).
+// sums (64^3, 120 fields, 120 states: 30 MB of them).  At most 4096 points: one
+// accumulator over 88000 (112^3, 42 pairs, 260 states) left W after 600 steps
+// 5.6e-14 from the oracle, 4096 leave 3.2e-14 (vector FMA chains of 4096: 3.6e-14)
+// and shorter blocks fill the chip more evenly (15.0 -> 14.3 s a call).
 struct Coef64Plan {
   int ns, nct, nfg, nchunk;
   size_t chunk;
@@ -262,7 +265,7 @@ static Coef64Plan coef64_plan(int FT, int S, size_t ng) {
   p.nfg = (FT + 15) / 16;
   const size_t tiles = (size_t)p.nct * p.nfg;
   const size_t want = std::max<size_t>(1, (2048 + tiles - 1) / tiles);
-  p.chunk = std::max<size_t>(64, ((ng + want - 1) / want + 7) / 8 * 8);
+  p.chunk = std::min<size_t>(4096, std::max<size_t>(64, ((ng + want - 1) / want + 7) / 8 * 8));
   p.nchunk = (int)((ng + p.chunk - 1) / p.chunk);
   return p;
 }
