@@ -111,7 +111,9 @@ __global__ void __launch_bounds__(256) k_gemm_reduce(const double* __restrict__ 
   }
 }
 
-// chunks for about 2048 waves (two per SIMD), each at least 64 points
+// chunks for about 2048 waves (two per SIMD), each at least 64 points and, for
+// short sums, at most 4096; of large products more, so that the partial sums
+// stay below 4096 tiles of 64 x 64 (134 MB)
 struct GemmPlan {
   int mt, nt, nmt, nnt, nchunk;
   size_t chunk;
@@ -124,7 +126,10 @@ static GemmPlan gemm_plan(int M, int N, size_t K) {
   p.nmt = (M + 16 * p.mt - 1) / (16 * p.mt);
   p.nnt = (tn + p.nt - 1) / p.nt;
   const size_t tiles = (size_t)p.nmt * p.nnt, want = std::max<size_t>(1, (2048 + tiles - 1) / tiles);
-  p.chunk = std::max<size_t>(64, ((K + want - 1) / want + 15) / 16 * 16);
+  const size_t t64 = (size_t)((M + 63) / 64) * ((N + 63) / 64);
+  size_t most = 4096;
+  while (t64 * ((K + most - 1) / most) > 4096 && most < K) most *= 2;
+  p.chunk = std::min(most, std::max<size_t>(64, ((K + want - 1) / want + 15) / 16 * 16));
   p.nchunk = (int)((K + p.chunk - 1) / p.chunk);
   return p;
 }

@@ -36,3 +36,49 @@ def test_fp64_w_of_a_large_batch_at_the_paper_grid():
     e = np.sqrt(np.mean(d ** 2) / np.mean(fix["w"] ** 2))
     say(f"paper112 FP64, 42 pairs: W rel RMS {e:.2e}")
     assert e < 4.5e-14
+
+
+def test_fp64_a_sums_are_no_longer_than_needed():
+    """Elements of the FP64 A (800 x 800 at 64^3, sums of 262144 points) against
+    80-bit sums of the same products: the rounding is no larger than that of
+    chains of 16384 points, which the same sums taken so in numpy show (a third
+    of margin for the sample of 96 elements and the potentials' transforms);
+    chains of 37000 leave 1.9 times as much."""
+    from paper_2205_06690_amd import bse
+    n, h, n_o, n_c = 64, 0.4, 20, 40
+    rng = np.random.default_rng(8)
+    # smooth localised fields: Gaussians at random centres, orthonormalised
+    x = np.arange(n) * h
+    c = rng.uniform(0.3, 0.7, (n_o + n_c, 3)) * n * h
+    wd = rng.uniform(1.5, 3.0, n_o + n_c)
+    g = np.exp(-(x[None, None, :] - c[:, :, None]) ** 2 / wd[:, None, None])
+    phi = np.einsum("sx,sy,sz->sxyz", g[:, 0], g[:, 1], g[:, 2]).reshape(n_o + n_c, -1)
+    phi = np.linalg.solve(np.linalg.cholesky(phi @ phi.T), phi) / np.sqrt(h ** 3)
+    eps = np.sort(rng.uniform(-1.0, 1.0, n_o + n_c))
+    s = bse.System(n, h, np.zeros(n ** 3), n_occ=n_o, n_stoch=2, n_steps=1, clean_every=0, precision=bse.BSE_FP64,
+                   max_batch=70)
+    s.set_orbitals(phi, eps)
+    A = s.build_a(n_o, n_c)
+    w = s.valence_w()
+    s.close()
+    k = 2 * np.pi * np.fft.fftfreq(n, d=h)
+    k2 = k[:, None, None] ** 2 + k[None, :, None] ** 2 + (2 * np.pi * np.fft.rfftfreq(n, d=h))[None, None, :] ** 2
+    k2[0, 0, 0] = np.inf
+    err, chain = [], []
+    for _ in range(96):
+        i, j = rng.integers(0, n_o, 2)
+        a, b = rng.integers(0, n_c, 2)
+        if i == j and a == b:
+            continue
+        rho = np.fft.rfftn((phi[j] * phi[n_o + b]).reshape(n, n, n))
+        pot = np.fft.irfftn(rho * (4 * np.pi / k2), s=(n, n, n), axes=(0, 1, 2))
+        lo, hi = min(i, j), max(i, j)
+        t = [2 * phi[i] * phi[n_o + a] * pot.reshape(-1),
+             -phi[n_o + a] * phi[n_o + b] * w[lo * n_o - lo * (lo - 1) // 2 + (hi - lo)]]
+        exact = sum(q.astype(np.longdouble).sum() for q in t) * np.longdouble(h) ** 3
+        c16 = sum(np.cumsum(q.reshape(-1, 16384), axis=1)[:, -1].sum() for q in t) * h ** 3
+        err.append(float(A[i * n_c + a, j * n_c + b] - exact))
+        chain.append(float(c16 - exact))
+    e, ec = np.sqrt(np.mean(np.square(err))), np.sqrt(np.mean(np.square(chain)))
+    say(f"FP64 A 800 x 800 at 64^3: rms rounding {e:.2e}, of chains of 16384 {ec:.2e}")
+    assert e < 1.33 * ec
