@@ -227,15 +227,18 @@ bse_status bse_chebyshev_spectrum(bse_system* sys, int32_t n_mom, double e_min, 
  * cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc): the same arguments,
  * kernels, arithmetic and results (bit for bit), with every device buffer
- * of the call (the three recursion vectors per polarisation, the per-block
- * partial residues, the residues, the node sums, the frequency grid, the
- * Gershgorin bounds) carved from one fixed 64 MiB device array that the
- * library holds per GPU until the process ends; the start vectors and the
- * Gershgorin interval are formed on the device, so the call makes no host
- * staging copies either.  It calls no hipMalloc, hipFree or allocating
- * routine.  Limit: about 0.75 n_mom (n_o n_c) + 9 n_o n_c + 9 n_mom +
- * 2 n_w doubles must fit in the 64 MiB (e.g. n_mom up to ~13000 at
- * n_o n_c = 800); larger requests return BSE_ERR_ARG before any work.
+ * of the call carved from one fixed 64 MiB device array that the library
+ * holds per GPU until the process ends: the start vectors and two segments
+ * of up to 512 steps of the recursion where it runs with A on the chip (up
+ * to 1024 rows, 32 moments or more), else its three rotating vectors and the
+ * per-block partial residues; the residues, the node sums, the frequency
+ * grid, the Gershgorin bounds.  The start vectors and the Gershgorin interval
+ * are formed on the device, so the call makes no host staging copies either.
+ * It calls no hipMalloc, hipFree or allocating routine.  Limit: the buffers
+ * of a launch per step, about 0.75 n_mom (n_o n_c) + 9 n_o n_c + 9 n_mom +
+ * 2 n_w doubles, must fit in the 64 MiB (e.g. n_mom up to ~13000 at
+ * n_o n_c = 800); larger requests return BSE_ERR_ARG before any work.  Where
+ * only the recursion's segments would not fit, it takes a launch per step.
  * Every call on a GPU shares that GPU's array: calls that overlap on one
  * GPU (two host threads, or two streams) race and must be serialised by
  * the caller.  Nothing in the array needs to start at zero (every element

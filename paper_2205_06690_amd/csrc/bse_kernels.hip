@@ -941,7 +941,7 @@ __global__ void k_ground_density(const double* __restrict__ phi, int n_occ, size
 // per-row sums: out[b][0] = sum a*a, out[b][1] = sum a*c (c nullable), out[b][2] = sum a*d
 // A row's ROW_NB blocks leave their partial sums in part[b][block][3], which
 // k_row_sums adds in order.  One block per row took 2.26 ms for 21 rows of
-// 112^3 (5 GB/s a block); 118 MB at the memory's rate are 24 us.
+// 112^3 (5 GB/s a block); their 236 MB at the memory's rate are 48 us.
 constexpr int ROW_NB = 64;
 __global__ void __launch_bounds__(256) k_row_dots(const double* __restrict__ a,
                                                   const double* __restrict__ c,

@@ -21,8 +21,10 @@
 //   plane pass  16^3 8 pairs 19 -> 6;   24^3 8 pairs 45 -> 12;  32^3 12 pairs 63 -> 34
 //               48^3 12 pairs 256 -> 118; 64^3 11 pairs 414 -> 319 (2.9 TB/s)
 //   x pass      16^3 8 pairs 18 -> 5;   24^3 8 pairs 22 -> 9;   32^3 12 pairs 32 -> 24
-// What bounds them now: on the small grids latency, at 64^3 the registers (two
-// waves on a SIMD), which keep memory and matrix cores from overlapping fully.
+// What bounds them now: on the small grids latency; at 64^3 occupancy: a plane
+// and its tables are 82944 bytes of LDS, 2 KB over half a CU, so one block of
+// four waves runs on a CU, one wave a SIMD, and memory and matrix cores overlap
+// little.
 #include <hip/hip_ext.h>
 
 #include "fft_lines.h"
